@@ -51,11 +51,13 @@ typedef struct codec_plan codec_plan_t;         /* opaque, library-owned, immuta
 typedef struct {
     int32_t num_q_heads;
     int32_t num_kv_heads;       /* must divide num_q_heads; group = ratio, 1..64        */
-    int32_t head_dim;           /* 128; or 64 or 256, which run in the task shape for few
-                                   rows only: group <= 16, query sets are tiled 32 (64
-                                   channels) or 16 (256 channels) rows at a time (max_rows
-                                   is capped), so a shared node is read once per tile, the
-                                   repeats from cache                                   */
+    int32_t head_dim;           /* 128; or 64 or 256: group <= 16, and the plan tiles query
+                                   sets 32 (64 channels) or 16 (256 channels) rows at a time
+                                   (max_rows is capped).  Where that shortens the schedule
+                                   the kernels run sibling tiles of a slice as one task of up
+                                   to 256 (128) rows, never more than max_rows asks for, on
+                                   slots of their own (one workgroup per CU at most), so that
+                                   a shared node is read once for all of them           */
     int32_t dtype;              /* CODEC_DTYPE_*: type of q, K, V and out               */
     int32_t page_size;          /* tokens per KV page, a power of two, 16..4096         */
     float   scale;              /* softmax scale, 1/sqrt(head_dim) in Eq. 1             */
@@ -203,7 +205,8 @@ typedef struct {
 /*
  * Read-only host view of a plan; pointers stay valid until codec_plan_destroy.
  * node_q lists, per node, the requests whose path contains it (ascending);
- * slot s runs tasks slot_tasks[slot_off[s] .. slot_off[s+1]) in that order;
+ * slot s runs tasks slot_tasks[slot_off[s] .. slot_off[s+1]) in that order (unless the
+ * kernels run sibling row tiles together, see head_dim);
  * request r merges the partials whose first rows are
  * req_part[req_part_off[r] .. req_part_off[r+1]) (root to leaf, slices in order).
  */

@@ -261,12 +261,12 @@ int partial_attention(const codec_plan_t *plan, const void *q, const void *k_pag
     while ((1 << pp.page_shift) < d.head.page_size) ++pp.page_shift;
     pp.part_rows = d.part_rows;
     pp.scale_log2e = d.head.scale * 1.4426950408889634f;
-    pp.num_slots = d.num_slots;
+    pp.num_slots = L.num_slots;
     if (d.schedule == 1) {
         pp.queue_off = reinterpret_cast<const int32_t *>(meta + L.queue_off);
         pp.queue_recs = reinterpret_cast<const codec::DevTask *>(meta + L.queue_recs);
         pp.counters = reinterpret_cast<int32_t *>(const_cast<char *>(meta) + L.counters);
-        pp.num_entries = int32_t(d.queue_off.size()) - 1;
+        pp.num_entries = L.num_entries;
     }
     if (!d.req_mask_off.empty()) {
         pp.nodeq_mask = reinterpret_cast<const int32_t *>(meta + L.nodeq_mask);
@@ -276,7 +276,7 @@ int partial_attention(const codec_plan_t *plan, const void *q, const void *k_pag
         pp.merge = merge_params(plan, workspace, fused_out);
         pp.arrive = reinterpret_cast<int32_t *>(const_cast<char *>(meta) + L.arrive);
     }
-    if (int e = codec::launch_pac(pp, d.head.dtype, d.head.head_dim, d.num_slots, plan->max_task_rows, stream))
+    if (int e = codec::launch_pac(pp, d.head.dtype, d.head.head_dim, L.num_slots, plan->max_task_rows, !d.packs.empty(), stream))
         return hip_failure("partial attention launch", e);
     return CODEC_OK;
 }

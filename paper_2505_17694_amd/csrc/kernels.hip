@@ -17,7 +17,7 @@
 // with the matching token-to-lane map.  Softmax statistics stay in fp32, in log2
 // units.
 //
-// Two task shapes share that arithmetic:
+// Three task shapes share that arithmetic:
 //  * "stream" (tasks of at most 16 rows, in both launch variants): 16 x 16 x 32
 //    tiles; the waves of the workgroup take interleaved 32-token blocks of the
 //    slice as one team, each with all rows; K and V go from HBM straight to
@@ -30,6 +30,8 @@
 //    and read by all waves, V through transposing LDS reads (ds_read_b64_tr_b16).
 //    Long slices under at most 128 rows put two waves on each row group, on
 //    alternate blocks.
+//  * "tile" (64 and 256 channels): sibling row tiles of one slice packed into one
+//    task of up to 256 (128) rows; 16 x 16 x 32 tiles, blocks shared through LDS.
 //
 // K and V slices that a single task reads, in plans that read little twice, are
 // loaded with the streaming (nontemporal) hint; the plan marks those tasks.
@@ -52,6 +54,8 @@ constexpr int kHeadDim = 128;       // the dense path; the stream path and the r
                                     // dimension D (64, 128 or 256) as a template parameter
 constexpr int kNarrowWaves = 4;     // stream-only kernel variant: 4 waves, two workgroups per CU
 constexpr int kWideWaves = 8;       // all task shapes: 8 waves (two per SIMD), one workgroup per CU
+// Waves of a workgroup: with 256 channels a wave needs a SIMD's registers for itself
+constexpr int kernel_waves(int wide, int d) { return wide && d <= 128 ? kWideWaves : kNarrowWaves; }
 // Row tiles of the stream path in the narrow variant: one tile of 16 rows, or two (32 rows) with 64
 // channels, where the accumulators of a second tile still fit the registers.
 constexpr int stream_tiles(int d) { return d == 64 ? 2 : 1; }
@@ -258,11 +262,11 @@ __device__ __forceinline__ void load_block(const SliceCtx &c, int tb, uint32_t k
 // first finite score raises the reference and wipes (multiplies by exp2 of -1e30) whatever it scaled.
 constexpr float kNoReference = -1e30f;
 
-template <int NT, int D>
+template <int NT, int D, int CTILES = channel_tiles(D)>
 struct RowState {
-    static constexpr int CT = channel_tiles(D);
+    static constexpr int CT = CTILES;
     f32x4 o[NT][CT];    // [row tile][dt]: row = 16*nt + lane%16; channel of component e is
-                        // 128*(dt/8) + 32*(lane/16) + 8*e + dt%8
+                        // 128*(dt/8) + 32*(lane/16) + 8*e + dt%8 (tile path: 16*dt + 4*(lane/16) + e)
     float m[NT];        // reference subtracted before exponentiation, log2 units (same in the 4 lanes
                         // that share a row); kNoReference until the row has seen a score above -inf
     float l[NT];        // the lane's share of the row sum; the row sum after finish()
@@ -354,8 +358,8 @@ __device__ __forceinline__ void lane_maxima(const f32x4 (&s)[2][NT], float scale
     }
 }
 
-template <int NT, int D>
-__device__ __forceinline__ bool outgrown(const float (&lm)[NT], const RowState<NT, D> &st)
+template <int NT, class State>
+__device__ __forceinline__ bool outgrown(const float (&lm)[NT], const State &st)
 {
     bool any = false;
 #pragma unroll
@@ -364,8 +368,8 @@ __device__ __forceinline__ bool outgrown(const float (&lm)[NT], const RowState<N
 }
 
 // Move every row's reference up to its true running maximum and rescale its accumulators.
-template <int NT, int D>
-__device__ __forceinline__ void raise_reference(const float (&lm)[NT], RowState<NT, D> &st)
+template <int NT, class State>
+__device__ __forceinline__ void raise_reference(const float (&lm)[NT], State &st)
 {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -376,15 +380,15 @@ __device__ __forceinline__ void raise_reference(const float (&lm)[NT], RowState<
         const float alpha = fast_exp2(st.m[nt] - m_new);       // 0 on the first block (m = -inf)
         st.l[nt] *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < RowState<NT, D>::CT; ++dt) st.o[nt][dt] *= alpha;
+        for (int dt = 0; dt < State::CT; ++dt) st.o[nt][dt] *= alpha;
         st.m[nt] = m_new;
     }
 }
 
 // P = exp2(scale * S - m), rounded to 16 bits in B-operand layout; the lane adds its 8 exponentials to
 // its share of the row sum.
-template <int DT, int NT, int D>
-__device__ __forceinline__ void probabilities(const f32x4 (&s)[2][NT], RowState<NT, D> &st,
+template <int DT, int NT, class State>
+__device__ __forceinline__ void probabilities(const f32x4 (&s)[2][NT], State &st,
                                               float scale_log2e, u32x4 (&pb)[NT])
 {
 #pragma unroll
@@ -553,7 +557,7 @@ __device__ __forceinline__ float weight(float a, float m) { return a == m ? 1.f 
 // `wave` is the wave's index in its team.  A team of one wave (W = 1) uses no LDS and no barrier, so
 // several such waves may work on different tasks at the same time.
 template <int DT, bool ONCE, int NT, int W, int D>
-__device__ void run_stream(const PacParams &P, const DevTask &t, int head, char *lds_raw, int wave,
+__device__ __forceinline__ void run_stream(const PacParams &P, const DevTask &t, int head, char *lds_raw, int wave,
                            char *stage = nullptr)      // W = 1, up to 128 channels: the wave's staging area
 {
     constexpr int KS = D / 32, CT = channel_tiles(D);
@@ -600,9 +604,9 @@ __device__ void run_stream(const PacParams &P, const DevTask &t, int head, char 
         }
         float lm[NT];
         lane_maxima<NT>(s, P.scale_log2e, lm);
-        if (__any(outgrown<NT, D>(lm, st))) raise_reference<NT, D>(lm, st);
+        if (__any(outgrown<NT>(lm, st))) raise_reference<NT>(lm, st);
         u32x4 pb[NT];
-        probabilities<DT, NT, D>(s, st, P.scale_log2e, pb);
+        probabilities<DT, NT>(s, st, P.scale_log2e, pb);
         accumulate<DT, NT, D>(r.v, pb, st);
     };
 
@@ -765,7 +769,6 @@ __device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c)
 // Keeps the computation of `x` where it is written (the compiler otherwise sinks work whose result
 // is only used after the next barrier below that barrier).
 __device__ __forceinline__ void pin(u32x4 &x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin(float &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void pin(int &x) { asm volatile("" : "+v"(x)); }
 
 // Roles of a wave in a dense task.  A wave with rows owns 32 of them; in the two live roles the halves
@@ -1233,6 +1236,325 @@ __device__ void run_dense32(const PacParams &P, const DevTask &t, int head, char
     }
 }
 
+// ---- tile path: 17 .. 256 rows of 64 channels, 17 .. 128 rows of 256 ------------------------------------
+//
+// With 64 and 256 channels the plan tiles query sets 32 (16) rows at a time.  Sibling row tiles of one KV
+// slice run here as ONE task (the device image packs them, DevTask): the slice then travels HBM -> LDS once
+// for all of them instead of once per tile through the CU's memory pipeline, which is what bounds such
+// plans (a CU streams 24-27 GB/s from HBM whatever its waves do).  Measured, whole step, a tree of a
+// 2048-token root, 16 nodes of 8192 tokens and ragged leaves of 32 .. 512: 128 requests with 64 / 8 heads of
+// 64 channels 100.3 -> 76.7 us, 256 requests with 16 / 8 heads of 256 channels 369 -> 289 us.  A task of up to
+// 64 rows streams at 5.2 (64 channels) and 6.0 TB/s (256) where its row tiles took 4.1 and 3.0; 128 rows
+// at 3.8 and 4.8 where they took 2.4 and 1.6 (4096 tokens, all CUs busy).
+//
+// One workgroup per CU: eight waves with 64 channels, four (one per SIMD, for its registers) with 256.
+// 16 x 16 x 32 tiles and the arithmetic of the stream path; a wave owns NT row tiles of 16, which share
+// every operand read.  K is the A operand by 16-byte LDS reads, V by transposing LDS reads, so that
+// register e of channel tile dt is channel 16*dt + 4*(lane/16) + e.  Blocks are copied asynchronously
+// (dma16_pair's instruction) into a ring of 128 KB, an interval of 32 KB (four blocks of 64 channels, one
+// of 256) per barrier and all but one interval of the ring requested ahead.
+template <int D>
+struct TilePath {
+    static constexpr int kWaves = kernel_waves(1, D);
+    static constexpr int kRowBytes = D * 2;
+    static constexpr int kHalf = 32 * kRowBytes;            // K (or V) of a block
+    static constexpr int kBlock = 2 * kHalf;
+    static constexpr int kBlocks = D == 64 ? 4 : 1;         // blocks of an interval
+    static constexpr int kInterval = kBlocks * kBlock;
+    static constexpr int kMine = kBlocks * 4 / kWaves;      // blocks of an interval of which a wave copies eight tokens
+    static constexpr int kIntervals = 131072 / kInterval;   // slots of the ring
+    static constexpr int kRingBytes = kIntervals * kInterval;
+    static constexpr int kPieces = 8 * kRowBytes / 1024;    // 1 KB copies of eight tokens of one pool
+    static constexpr int kCopies = kMine * 2 * kPieces;     // copies per wave and interval
+    static constexpr int CT = D / 16;
+    // state of NT row tiles as a wave hands it to another, in floats
+    static constexpr int state_floats(int nt) { return nt * CT * 64 * 4 + nt * 64 * 2; }
+    static_assert((kIntervals - 2) * kCopies < 64, "outstanding copies fit the wait counter");
+};
+
+// Copies 1 KB: each lane 16 bytes from gbase + voff to lds_addr + 16 * lane.
+__device__ __forceinline__ void dma16(uint32_t lds_addr, uint32_t voff, const char *gbase, int read_once)
+{
+    // wave-uniform: kept in scalar registers also where the compiler has lost track of that
+    const uint64_t g = uint64_t(uintptr_t(gbase));
+    gbase = reinterpret_cast<const char *>(uintptr_t(
+        uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(g >> 32)))) << 32 | uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(g)))));
+    uint32_t m0_saved;
+    if (read_once)
+        asm volatile("s_mov_b32 %0, m0\n\t"
+                     "s_mov_b32 m0, %1\n\t"
+                     "s_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, %3 nt\n\t"
+                     "s_mov_b32 m0, %0\n"
+                     : "=&s"(m0_saved)
+                     : "s"(lds_addr), "v"(voff), "s"(gbase)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 %0, m0\n\t"
+                     "s_mov_b32 m0, %1\n\t"
+                     "s_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, %3\n\t"
+                     "s_mov_b32 m0, %0\n"
+                     : "=&s"(m0_saved)
+                     : "s"(lds_addr), "v"(voff), "s"(gbase)
+                     : "memory");
+}
+
+// NT: row tiles of 16 per wave.  SHARE: waves that share a row group; they take turns with the blocks of
+// every interval and merge their states at the end.
+template <int DT, int D, int NT, int SHARE>
+__device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t, int head, char *lds)
+{
+    using T = TilePath<D>;
+    constexpr int RB = T::kRowBytes, KS = D / 32, CT = T::CT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = opaque_lane();
+    const int l16 = lane & 15, grp = lane >> 4;
+    const int rows = t.n_req * P.group;
+    constexpr int GROUPS = T::kWaves / SHARE;
+    const int group = wave % GROUPS, phase = wave / GROUPS;
+    const int row0 = group * 16 * NT;
+    const bool live = row0 < rows;                          // else: the wave only helps moving blocks
+    const SliceCtx c = make_ctx(P, t, head);
+    const int nblk = (t.kv_len + 31) >> 5;
+    constexpr int NB = T::kBlocks, R = T::kIntervals;
+    static_assert(NB % SHARE == 0 && (SHARE & (SHARE - 1)) == 0, "every wave of a group takes as many blocks of an interval");
+    static_assert(SHARE == 1 || T::kWaves / 2 * T::state_floats(NT) * 4 <= T::kRingBytes, "hand-over areas fit the ring");
+    const int nint = (nblk + NB - 1) / NB;
+    // what the wave copies of every interval: eight tokens of block my_block and, with kMine = 2, of my_block + 2
+    const int my_block = wave >> 2, my_token = (wave & 3) * 8;
+    constexpr int MINE = T::kMine, STEP = T::kWaves / 4;
+
+    // Copies, 1024 / RB tokens each.  A K row keeps its
+    // 16-byte column g in slot g ^ fk(token), a V row in slot g ^ fv(token), applied on the global side:
+    // the sixteen rows of a K read, and the eight rows (32 bytes each) that 32 lanes of a transposing V
+    // read take, then lie in different banks.
+    //   256 channels (a row is twice the 256 bytes of banks):  fk = token % 16,        fv = 2 * (token % 8)
+    //    64 channels (a row is half of them):                  fk = (token / 2) % 8,   fv = 2 * ((token / 2) % 4)
+    constexpr int LPR = RB / 16;                            // lanes per row of a copy
+    constexpr int TPC = 64 / LPR;                           // tokens per copy
+    auto fk = [](int token) { return D == 256 ? token & 15 : (token >> 1) & 7; };
+    auto fv = [](int token) { return D == 256 ? 2 * (token & 7) : 2 * ((token >> 1) & 3); };
+    const uint32_t lds_base = uint32_t(uintptr_t(lds));
+    uint32_t voff_k[T::kPieces], voff_v[T::kPieces];
+#pragma unroll
+    for (int i = 0; i < T::kPieces; ++i) {
+        const int in_copy = lane / LPR, token = my_token + i * TPC + in_copy;
+        voff_k[i] = uint32_t(i * TPC + in_copy) * c.token_bytes + uint32_t(((lane % LPR) ^ fk(token)) << 4);
+        voff_v[i] = uint32_t(i * TPC + in_copy) * c.token_bytes + uint32_t(((lane % LPR) ^ fv(token)) << 4);
+    }
+    // eight tokens past the end of the slice are redirected to its first ones (masked later): no address
+    // leaves the slice's pages, and every interval has the same number of copies
+    auto first_token = [&](int i, int u) {
+        const int tok0 = (NB * i + my_block + u * STEP) * 32 + my_token;
+        return tok0 >= c.kv_len ? 0 : tok0;
+    };
+    auto page_issue = [&](int i, int u) { return uniform_load(c.pages, first_token(i, u) >> c.page_shift); };
+    const uint32_t my_slot = lds_base + uint32_t(my_block) * T::kBlock + uint32_t(my_token) * RB;
+    auto request = [&](int i, const int (&pg)[MINE]) __attribute__((always_inline)) {  // interval i; pg: page_issue(i, .)
+#pragma unroll
+        for (int u = 0; u < MINE; ++u) {
+            const uint32_t at = my_slot + uint32_t(i % R) * T::kInterval + uint32_t(u * STEP) * T::kBlock;
+            const int64_t off = page_offset(c, pg[u], first_token(i, u) & c.page_mask);
+#pragma unroll
+            for (int n = 0; n < T::kPieces; ++n) dma16(at + n * 1024, voff_k[n], c.k_head + off, c.read_once);
+#pragma unroll
+            for (int n = 0; n < T::kPieces; ++n) dma16(at + T::kHalf + n * 1024, voff_v[n], c.v_head + off, c.read_once);
+        }
+    };
+
+    // Operand reads.  K, token tile j, k-step ks: lane (l16, grp) reads 16-byte column 4*ks + grp of token
+    // 16*j + l16.  V, channel tile dt, h: lane (k, q) of lane group grp addresses token 16*h + 4*grp + k,
+    // channels 16*dt + 4*q .. +3, and receives channel 16*dt + l16 of tokens 16*h + 4*grp .. +3.
+    const uint32_t k_lane = uint32_t(l16 * RB + ((grp ^ fk(l16)) << 4));
+    const int vtok = 4 * grp + (l16 >> 2), vq = l16 & 3;
+    const uint32_t v_lane = uint32_t(vtok * RB + (((vq >> 1) ^ fv(vtok)) << 4) + 8 * (vq & 1));
+    typedef const u32x4 __attribute__((address_space(3))) *lds_u32x4_ptr;
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
+
+    u32x4 qb[NT][KS];
+    RowState<NT, D, CT> st;
+    st.clear();
+
+    auto compute = [&](int b, uint32_t kb) __attribute__((always_inline)) {
+        f32x4 s[2][NT];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) s[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const u32x4 kr = reinterpret_cast<lds_u32x4_ptr>(uintptr_t(kb + (k_lane ^ uint32_t(ks << 6))))[j * RB];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) s[j][nt] = mfma16<DT>(kr, qb[nt][ks], s[j][nt]);
+            }
+        }
+        // the V operands of the first half of the channel tiles travel during the softmax
+        u32x4 va[CT];
+        auto load_value = [&](int dt) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const lds_s16x4_ptr at = reinterpret_cast<lds_s16x4_ptr>(uintptr_t(kb + (v_lane ^ uint32_t(dt << 5))));
+                const uint2 w = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(at + (T::kHalf + h * 16 * RB) / 8));
+                va[dt][2 * h] = w.x;
+                va[dt][2 * h + 1] = w.y;
+            }
+        };
+        constexpr int AHEAD = NT == 1 ? CT : CT / 2;
+#pragma unroll
+        for (int dt = 0; dt < AHEAD; ++dt) load_value(dt);
+        __builtin_amdgcn_sched_barrier(0);
+        const int valid = c.kv_len - b * 32;
+        if (valid < 32) mask_scores<NT>(s, valid, grp);
+        float lm[NT];
+        lane_maxima<NT>(s, P.scale_log2e, lm);
+        if (__any(outgrown<NT>(lm, st))) raise_reference<NT>(lm, st);
+        u32x4 pb[NT];
+        probabilities<DT, NT>(s, st, P.scale_log2e, pb);
+#pragma unroll
+        for (int dt = AHEAD; dt < CT; ++dt) load_value(dt);
+#pragma unroll
+        for (int dt = 0; dt < CT; ++dt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) st.o[nt][dt] = mfma16<DT>(va[dt], pb[nt], st.o[nt][dt]);
+    };
+
+    // V rows of the last block past the end of the slice count as zero (their memory may hold anything):
+    // each wave clears the ones that it copied
+    auto clear_tail = [&]() __attribute__((always_inline)) {
+        const int valid = c.kv_len - (nblk - 1) * 32, last = (nblk - 1) % NB;
+        if (last % STEP != my_block) return;
+        const uint32_t at = lds_base + uint32_t((nint - 1) % R) * T::kInterval + uint32_t(last) * T::kBlock + T::kHalf
+                            + uint32_t(my_token) * RB + uint32_t(lane) * 16;
+#pragma unroll
+        for (int n = 0; n < T::kPieces; ++n)
+            if (my_token + n * TPC + lane / LPR >= valid)
+                *reinterpret_cast<u32x4 __attribute__((address_space(3))) *>(uintptr_t(at + n * 1024)) = u32x4{0u, 0u, 0u, 0u};
+    };
+
+    // Start: the first interval's copies, then the query rows; waiting for the rows (the compiler waits for
+    // every load in flight) waits for that interval too, so the others are requested behind it.
+    int pg[R][MINE];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int u = 0; u < MINE; ++u) pg[i][u] = page_issue(i, u);
+    request(0, pg[0]);
+    if (live) gather_q<NT, D>(P, t, head, row0, rows, l16, grp, qb);
+    else {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qb[nt][ks] = u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) pin(qb[nt][ks]);
+#pragma unroll
+    for (int i = 1; i + 1 < R; ++i)
+        if (i < nint) request(i, pg[i]);
+    int pg_next[MINE];
+#pragma unroll
+    for (int u = 0; u < MINE; ++u) pg_next[u] = pg[R - 1][u];
+    auto enter_interval = [&](int i) __attribute__((always_inline)) {
+        // interval i has landed once at most the copies of the intervals requested after it are outstanding
+        if (i + R - 2 < nint) __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 2) * T::kCopies));
+        else                  __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (i == nint - 1 && (c.kv_len & 31)) clear_tail();
+        __syncthreads();                    // everyone's part has landed; interval i - 1 has been read by all
+        if (i + R - 1 < nint) {
+            request(i + R - 1, pg_next);
+#pragma unroll
+            for (int u = 0; u < MINE; ++u) pg_next[u] = page_issue(i + R, u);
+        }
+    };
+    if (live) {
+#pragma unroll 1
+        for (int i = 0; i < nint; ++i) {
+            enter_interval(i);
+            const uint32_t kb = lds_base + uint32_t(i % R) * T::kInterval;
+            if constexpr (NB == 1) {
+                compute(i, kb);
+            } else {
+                const int end = nblk - NB * i < NB ? nblk - NB * i : NB;
+#pragma unroll 1
+                for (int u = phase; u < end; u += SHARE) compute(NB * i + u, kb + uint32_t(u) * T::kBlock);
+            }
+        }
+    } else {
+#pragma unroll 1
+        for (int i = 0; i < nint; ++i) enter_interval(i);
+    }
+    st.finish();
+    // the waves of a row group hand their states over pairwise: phases [h, 2h) to phases [0, h)
+    if constexpr (SHARE > 1) {
+        __syncthreads();                    // every block has been read: the ring is free
+#pragma unroll 1
+        for (int h = SHARE / 2; h >= 1; h >>= 1) {
+            float *x = reinterpret_cast<float *>(lds) + (phase % h * GROUPS + group) * T::state_floats(NT);
+            f32x4 *xo = reinterpret_cast<f32x4 *>(x);       // [NT][CT][64]
+            float *xs = x + NT * CT * 64 * 4;
+            if (phase >= h && phase < 2 * h) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int dt = 0; dt < CT; ++dt) xo[(nt * CT + dt) * 64 + lane] = st.o[nt][dt];
+                    xs[nt * 64 + lane] = st.m[nt];
+                    xs[(NT + nt) * 64 + lane] = st.l[nt];
+                }
+            }
+            __syncthreads();
+            if (phase < h) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const float m2 = xs[nt * 64 + lane], mm = fmaxf(st.m[nt], m2);
+                    const float a = weight(st.m[nt], mm), b = weight(m2, mm);
+                    st.l[nt] = st.l[nt] * a + xs[(NT + nt) * 64 + lane] * b;
+                    st.m[nt] = mm;
+#pragma unroll
+                    for (int dt = 0; dt < CT; ++dt) st.o[nt][dt] = st.o[nt][dt] * a + xo[(nt * CT + dt) * 64 + lane] * b;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (live && phase == 0) {
+        const int tile_rows = (t.flags >> kTaskTileShift) & 255, stride = ~t.single_req;
+        const int last_tile = (rows - 1) / tile_rows, last_back = t.flags >> kTaskLastShift;
+        const bool coherent = P.arrive != nullptr;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int row = row0 + nt * 16 + l16;
+            if (row < rows) {
+                const int tile = row / tile_rows;
+                const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + int64_t(tile) * stride
+                                     + (row - tile * tile_rows) - (tile == last_tile ? last_back : 0);
+                float *po = P.part_o + prow * D + grp * 4;
+#pragma unroll
+                for (int dt = 0; dt < CT; ++dt) st16_partial(po + dt * 16, st.o[nt][dt], coherent);
+                if (grp == 0) st8_partial(P.part_ml + prow * 2, st.m[nt], st.l[nt], coherent);
+            }
+        }
+    }
+    __syncthreads();                        // every block has been read: the ring is free for the next task
+}
+
+template <int DT, int D>
+__device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, int head, char *lds)
+{
+    const int rows = t.n_req * P.group;
+    if constexpr (D == 64) {            // row groups of 32: up to two, four, eight
+        if (rows <= 64)       run_tile_of<DT, D, 2, 4>(P, t, head, lds);
+        else if (rows <= 128) run_tile_of<DT, D, 2, 2>(P, t, head, lds);
+        else                  run_tile_of<DT, D, 2, 1>(P, t, head, lds);
+    } else {                            // a row group per wave, of 16 or of 32 rows
+        if (rows <= 64) run_tile_of<DT, D, 1, 1>(P, t, head, lds);
+        else            run_tile_of<DT, D, 2, 1>(P, t, head, lds);
+    }
+}
+
 // Partial output reduction (Alg. 3), n-ary: one wave folds the partials of RPW consecutive query heads
 // of one request (hq .. hq + RPW - 1, all of one KV head) in list order.  Partials are taken eight or
 // fifteen at a time: their loads are issued together, then they are folded against their common maximum
@@ -1388,9 +1710,10 @@ __device__ __forceinline__ bool deliver(const PacParams &P, const DevTask &t, in
     return true;
 }
 
-// A task that the whole workgroup ran (every thread calls this after the task).
+// A task that the whole workgroup ran (every thread calls this after the task).  Inline without fail, as all
+// device functions here: one real call makes the compiler keep the kernel's parameters in scratch memory.
 template <int DT, int D>
-__device__ void task_delivered_by_workgroup(const PacParams &P, const DevTask &t, int head, char *lds_raw, int waves)
+__device__ __forceinline__ void task_delivered_by_workgroup(const PacParams &P, const DevTask &t, int head, char *lds_raw, int waves)
 {
     int *count = reinterpret_cast<int *>(lds_raw), *ready = count + 1;
     __syncthreads();                    // every wave has waited for its stores of partial rows; LDS is free
@@ -1416,7 +1739,7 @@ __device__ void task_delivered_by_workgroup(const PacParams &P, const DevTask &t
 
 // A task that one wave ran on its own (no barrier: the other waves are inside other tasks).
 template <int DT, int D>
-__device__ void task_delivered_by_wave(const PacParams &P, const DevTask &t, int head)
+__device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const DevTask &t, int head)
 {
     const int lane = threadIdx.x & 63;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // waits for the wave's stores of partial rows
@@ -1435,16 +1758,17 @@ __device__ void task_delivered_by_wave(const PacParams &P, const DevTask &t, int
     }
 }
 
-// WIDE: kRingBytes of dynamic LDS.  The dense path XORs the channel tile into operand addresses, so
-// the ring must start on a 256-byte boundary (no static LDS in that variant).
+// WIDE: a ring of dynamic LDS (kRingBytes, TilePath::kRingBytes).  The dense and tile paths XOR channel
+// tiles into operand addresses, so the ring must start on a 512-byte boundary (no static LDS there).
 extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
 
 template <int DT, int WIDE, int D>
-__global__ void __launch_bounds__(WIDE ? kWideWaves * 64 : kNarrowWaves * 64, D > 128 ? 1 : 2)
+__global__ void __launch_bounds__(kernel_waves(WIDE, D) * 64, D > 128 ? 1 : 2)
 pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in registers need a wave per SIMD
 {
-    static_assert(WIDE == 0 || D == kHeadDim, "the dense path exists for 128 channels only");
-    constexpr int W = WIDE ? kWideWaves : kNarrowWaves;
+    // WIDE = 1: the dense path (128 channels, eight waves) or the tile path (64 and 256 channels)
+    constexpr bool DENSE = WIDE != 0 && D == kHeadDim, TILES = WIDE != 0 && D != kHeadDim;
+    constexpr int W = kernel_waves(WIDE, D);
     char *lds;
     if constexpr (WIDE != 0) {
         lds = dyn_lds;
@@ -1458,7 +1782,10 @@ pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in regi
     // staging area of this wave for tasks it runs on its own: behind the area in which a team merges its
     // states (in the wide variant both lie in the ring, which only dense tasks fill)
     static_assert(merge_bytes(kWideWaves, 1, kHeadDim) + kWideWaves * solo_stage_bytes(kHeadDim) <= kRingBytes, "staging areas fit the ring");
-    char *stage = lds + merge_bytes(W, WIDE ? 1 : stream_tiles(D), D) + wave * solo_stage_bytes(D);
+    if constexpr (TILES)
+        static_assert(merge_bytes(W, stream_tiles(D), D) + W * solo_stage_bytes(D) <= TilePath<D>::kRingBytes,
+                      "staging areas fit the ring");
+    char *stage = lds + merge_bytes(W, DENSE ? 1 : stream_tiles(D), D) + wave * solo_stage_bytes(D);
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in
@@ -1495,11 +1822,15 @@ pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in regi
                 __syncthreads();                // the counter is done with before LDS is used again
                 i += n;
             } else {
-                if (t.n_req * P.group <= 16) {
+                bool tiles = false;             // sibling row tiles packed into one task
+                if constexpr (TILES) tiles = (t.flags & kTaskTiles) != 0;
+                if (tiles) {
+                    if constexpr (TILES) run_tile<DT, D>(P, t, head, lds);
+                } else if (t.n_req * P.group <= 16) {
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 1, W, D>(P, t, head, lds, wave);
                     else             run_stream<DT, false, 1, W, D>(P, t, head, lds, wave);
                 }
-                else if constexpr (WIDE != 0) run_dense32<DT>(P, t, head, lds);
+                else if constexpr (DENSE) run_dense32<DT>(P, t, head, lds);
                 else if constexpr (stream_tiles(D) == 2) {      // 17 .. 32 rows of 64 channels: two row tiles
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head, lds, wave);
                     else             run_stream<DT, false, 2, W, D>(P, t, head, lds, wave);
@@ -1598,23 +1929,33 @@ int prepare_kernels()
     if (dev < 0 || dev >= kMaxDevices) return int(hipErrorInvalidDevice);
     std::lock_guard<std::mutex> guard(lock);
     if (done[dev]) return 0;
-    if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, 1, 128>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kRingBytes))
-        return int(e);
-    if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, 1, 128>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kRingBytes))
-        return int(e);
+    const struct { const void *kernel; int bytes; } kernels[] = {
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, 1, 128>), kRingBytes},
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, 1, 128>), kRingBytes},
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, 1, 64>), TilePath<64>::kRingBytes},
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, 1, 64>), TilePath<64>::kRingBytes},
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, 1, 256>), TilePath<256>::kRingBytes},
+        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, 1, 256>), TilePath<256>::kRingBytes},
+    };
+    for (const auto &k : kernels)
+        if (hipError_t e = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes)) return int(e);
     done[dev] = true;
     return 0;
 }
 
+// 64 and 256 channels: the kernel with the tile path where the plan holds packed row tiles, else without
 template <int DT, int D>
-void launch_narrow(const PacParams &p, dim3 grid, hipStream_t s)
+void launch_narrow(const PacParams &p, dim3 grid, bool tiles, hipStream_t s)
 {
+    if constexpr (D != kHeadDim)
+        if (tiles) {
+            hipLaunchKernelGGL((pac_kernel<DT, 1, D>), grid, dim3(TilePath<D>::kWaves * 64), TilePath<D>::kRingBytes, s, p);
+            return;
+        }
     hipLaunchKernelGGL((pac_kernel<DT, 0, D>), grid, dim3(kNarrowWaves * 64), 0, s, p);
 }
 
-int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, void *stream)
+int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, void *stream)
 {
     if (head_dim != 64 && head_dim != 128 && head_dim != 256) return int(hipErrorInvalidValue);
     const bool wide = head_dim == kHeadDim && max_rows_in_plan > 16;
@@ -1627,11 +1968,11 @@ int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int m
         if (f16) hipLaunchKernelGGL((pac_kernel<CODEC_DTYPE_FP16, 1, 128>), grid, block, kRingBytes, s, p);
         else     hipLaunchKernelGGL((pac_kernel<CODEC_DTYPE_BF16, 1, 128>), grid, block, kRingBytes, s, p);
     } else if (head_dim == 64) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 64>(p, grid, s); else launch_narrow<CODEC_DTYPE_BF16, 64>(p, grid, s);
+        if (f16) launch_narrow<CODEC_DTYPE_FP16, 64>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 64>(p, grid, tiles, s);
     } else if (head_dim == 128) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 128>(p, grid, s); else launch_narrow<CODEC_DTYPE_BF16, 128>(p, grid, s);
+        if (f16) launch_narrow<CODEC_DTYPE_FP16, 128>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 128>(p, grid, tiles, s);
     } else if (head_dim == 256) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 256>(p, grid, s); else launch_narrow<CODEC_DTYPE_BF16, 256>(p, grid, s);
+        if (f16) launch_narrow<CODEC_DTYPE_FP16, 256>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 256>(p, grid, tiles, s);
     } else {
         return int(hipErrorInvalidValue);
     }

@@ -95,68 +95,201 @@ void schedule_lpt(const std::vector<Sub> &sub, int m, bool keep_lists, Schedule 
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Run-time queue.  Short tasks (the ones a single wave runs) are bundled, in order of decreasing cost, into
+// entries that a workgroup hands out one wave each, like a run of short tasks in a slot's list; every other
+// task is an entry of its own.  The bundle size is the smallest that lets every entry have a workgroup of
+// its own (then no entry is ever fetched at run time and the queue costs nothing), at most kQueueBundle.
+// Entries are ordered by decreasing cost, a bundle counting as the sum of its tasks, ties to the entry with
+// the lower first task: the order in which the greedy schedule would deal them.
+template <class Cost, class Short>
+TaskLists queue_entries(int32_t num_tasks, int32_t num_slots, Cost cost, Short is_short)
+{
+    std::vector<int32_t> order(static_cast<size_t>(num_tasks));
+    for (size_t i = 0; i < order.size(); ++i) order[i] = int32_t(i);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return cost(a) > cost(b); });
+    int64_t n_short = 0;
+    for (int32_t i : order) n_short += is_short(i);
+    const int64_t n_long = int64_t(order.size()) - n_short;
+    int64_t bundle = kQueueBundle;
+    if (n_long < num_slots) bundle = std::min<int64_t>(kQueueBundle, std::max<int64_t>(1, ceil_div(n_short, num_slots - n_long)));
+    struct Entry { int64_t cost; std::vector<int32_t> tasks; };
+    std::vector<Entry> entries;
+    int64_t open_bundle = -1;
+    for (int32_t i : order) {
+        if (is_short(i) && open_bundle >= 0 && int64_t(entries[open_bundle].tasks.size()) < bundle) {
+            entries[open_bundle].tasks.push_back(i);
+            entries[open_bundle].cost += cost(i);
+            continue;
+        }
+        entries.push_back({cost(i), {i}});
+        open_bundle = is_short(i) ? int64_t(entries.size()) - 1 : open_bundle;
+        if (is_short(i) && bundle == 1) open_bundle = -1;
+    }
+    std::stable_sort(entries.begin(), entries.end(), [](const Entry &a, const Entry &b) { return a.cost > b.cost; });
+    TaskLists q;
+    q.off.assign(1, 0);
+    for (const Entry &e : entries) {
+        q.tasks.insert(q.tasks.end(), e.tasks.begin(), e.tasks.end());
+        q.off.push_back(int32_t(q.tasks.size()));
+    }
+    return q;
+}
+
+// Cost of a task of 64 or 256 channels, from the plan's estimate for 16 rows: that of a slice `extra` tokens
+// longer (what a task of several row tiles spends outside its blocks), times a percentage.  `packed`: in the
+// kernel variant that runs packed row tiles, one workgroup per CU instead of two that share it.  Fitted to
+// plans of equal nodes of 512 / 2048 / 4096 tokens that fill the chip; us per node and workgroup slot:
+//   64 channels, two workgroups per CU:  16 rows 10.1 / 41.9 / 87.3,  32 rows 15.5 / 50.3 / 95.2
+//   64 channels, one, packed:            64 rows 11.6 / 28.4 / 50.9, 128 rows 14.5 / 39.6 / 70.6, 256 rows 20.3 / 61.3 / 110
+//   256 channels (one per CU):           16 rows 22.4 / 82.3 / 174,   64 rows 30.0 / 96.7 / 176,  128 rows 42.6 / 122 / 220
+// (without packs the same nodes of 64 / 128 rows took 23.4 / 71.7 / 129 and 45.3 / 123 / 222 with 64 channels,
+// two per CU, and 95 / 335 / 709 and 173 / 614 / 1311 with 256).
+int64_t task_cost(const PlanData &p, int32_t rows, int32_t len, bool packed)
+{
+    int32_t extra = 0, percent = 100;
+    if (p.head.head_dim == 64) {
+        percent = packed ? 50 : 100;
+        if (rows > 128)     { extra = 512; percent = 108; }
+        else if (rows > 64) { extra = 512; percent = 68; }
+        else if (rows > 32) { extra = 512; }
+        else if (rows > 16) { extra = 384; }
+    } else {
+        if (rows > 64)      { extra = 400; percent = 113; }
+        else if (rows > 16) { extra = 200; percent = 95; }
+    }
+    return std::max<int64_t>(1, p.table.estimate(std::min(rows, kSoloMaxRows), int64_t(len) + extra) * percent / 100);
+}
+
+// Packs sibling row tiles of the same slice, `width` rows at most (0: none).  Tiles of one node are
+// neighbours among the items; they pack when their slices are the same and the node carries no masks.
+std::vector<DeviceTask> pack_tiles(const PlanData &p, int32_t width)
+{
+    std::vector<uint8_t> masked_node(size_t(p.num_nodes), 0);
+    for (int32_t r = 0; r < p.num_requests && !p.req_mask_off.empty(); ++r)
+        if (p.req_mask_off[r + 1] > p.req_mask_off[r]) masked_node[p.req_node[r]] = 1;
+    std::vector<int32_t> first_task(p.items.size() + 1, 0);
+    for (size_t j = 0; j < p.items.size(); ++j) first_task[j + 1] = first_task[j] + p.items[j].b;
+    std::vector<DeviceTask> out;
+    size_t j = 0;
+    while (j < p.items.size()) {
+        const codec_item &it = p.items[j];
+        size_t e = j + 1;
+        int32_t rows = it.rows;
+        // only the last tile of a pack may have fewer rows than the first
+        while (e < p.items.size() && p.items[e].node == it.node && p.items[e].b == it.b && !masked_node[it.node] &&
+               p.items[e - 1].rows == it.rows && p.items[e].rows <= it.rows && rows + p.items[e].rows <= width &&
+               int64_t(it.b) * (it.rows - p.items[e].rows) <= kTaskLastMax)
+            rows += p.items[e++].rows;
+        for (int32_t s = 0; s < it.b; ++s) {
+            const codec_task &t = p.tasks[first_task[j] + s];
+            const int64_t cost = p.head.head_dim == 128 ? t.cost : task_cost(p, rows, t.kv_len, width > 0);
+            out.push_back({first_task[j] + s, it.b, int32_t(e - j), rows, cost});
+        }
+        j = e;
+    }
+    return out;
+}
+
+// With 64 and 256 channels sibling row tiles are packed where that shortens the schedule: packs of up to 64,
+// 128 (and 32 with 256 channels, 256 with 64) rows are dealt longest first, like the plan's own tasks, onto
+// one workgroup per CU, and the shortest of these schedules runs if it is shorter than the plan without packs
+// (ties: the narrower packs).  Packs read a slice once instead of once per tile, but fewer tasks may leave
+// workgroups idle.  `max_rows`: the caller's limit on the rows of a task; flat plans share nothing.
+void choose_packs(PlanData &p, int32_t max_rows)
+{
+    p.packs.clear();
+    max_rows = std::min(max_rows, pack_max_rows(p.head.head_dim));
+    if (p.head.head_dim == 128 || !p.share || max_rows < 2 * max_task_rows(p.head.head_dim)) return;
+    const std::vector<DeviceTask> plain = pack_tiles(p, 0);
+    std::vector<DeviceTask> trial = pack_tiles(p, max_rows);
+    if (trial.size() == plain.size()) return;               // no siblings
+    const int32_t one_per_cu = std::min(p.num_slots, std::max(1, 256 / p.head.num_kv_heads));
+    auto deal = [&](const std::vector<DeviceTask> &d, int32_t m, bool keep) {
+        std::vector<Sub> sub(d.size());
+        for (size_t i = 0; i < d.size(); ++i) sub[i] = {d[i].cost, int32_t(i), 0, 0, 0};
+        Schedule s;
+        schedule_lpt(sub, m, keep, s);
+        return s;
+    };
+    // The plan as it is: two workgroups share a CU with 64 channels (a lone one takes about 60 % of the time of
+    // one that shares), and run one after the other with 256.  Unpacked siblings that run side by side find
+    // their slice in L2, which the estimates of 64 channels do not know: over 16 drawn forests a schedule with
+    // packs took 1.25 times as long against its estimate as the plan without them, and packs at less than that
+    // margin lost up to 17 %.
+    const int64_t margin = p.head.head_dim == 64 ? 125 : 100;
+    int64_t sum = 0, longest = 0;
+    for (const DeviceTask &d : plain) {
+        sum += d.cost;
+        longest = std::max(longest, d.cost);
+    }
+    int64_t best_span;
+    if (p.head.head_dim == 64) best_span = std::max(sum / p.num_slots, longest * 6 / 10);
+    else best_span = deal(plain, p.num_slots, false).makespan * ceil_div(std::min<int64_t>(p.num_slots, int64_t(plain.size())), one_per_cu);
+    for (int32_t width = 2 * max_task_rows(p.head.head_dim); width <= max_rows; width *= 2) {
+        trial = pack_tiles(p, width);
+        const int64_t span = deal(trial, one_per_cu, false).makespan;
+        if (trial.size() < plain.size() && (p.packs.empty() ? span * margin / 100 : span) < best_span) {
+            best_span = span;
+            p.packs = std::move(trial);
+        }
+    }
+    if (p.packs.empty()) return;
+    const Schedule s = deal(p.packs, one_per_cu, true);
+    p.pack_slots.off.assign(1, 0);
+    p.pack_slots.tasks.clear();
+    for (const std::vector<int32_t> &l : s.lists) {
+        p.pack_slots.tasks.insert(p.pack_slots.tasks.end(), l.begin(), l.end());
+        p.pack_slots.off.push_back(int32_t(p.pack_slots.tasks.size()));
+    }
+}
+
 // Host image of the device metadata: task records, slot lists, query lists, page table, partial lists.
 void build_device_image(PlanData &p)
 {
     const int32_t ps = p.head.page_size;
     DevLayout &L = p.layout;
+    // visibility masks: which (node, request) entries carry one (the node ends the request)
+    const bool masks = !p.req_mask_off.empty();
+    std::vector<int32_t> nodeq_mask;
+    if (masks) {
+        nodeq_mask.assign(p.node_q.size(), -1);
+        for (int32_t n = 0; n < p.num_nodes; ++n)
+            for (int32_t e = p.node_q_off[n]; e < p.node_q_off[n + 1]; ++e) {
+                const int32_t r = p.node_q[e];
+                if (p.req_node[r] == n && p.req_mask_off[r + 1] > p.req_mask_off[r]) nodeq_mask[e] = p.req_mask_off[r];
+            }
+    }
+    auto short_task = [&](const codec_task &t) { return t.n_req * p.group <= kSoloMaxRows && t.kv_len <= kSoloMaxLen; };
+    {
+        TaskLists q = queue_entries(int32_t(p.tasks.size()), p.num_slots, [&](int32_t i) { return p.tasks[i].cost; },
+                                    [&](int32_t i) { return short_task(p.tasks[i]); });
+        p.queue_off = std::move(q.off);
+        p.queue_tasks = std::move(q.tasks);
+    }
+    // what the kernels run: the plan's tasks, its slots and its queue, or packed row tiles with their own
+    const bool packed = !p.packs.empty();
+    const std::vector<DeviceTask> dev = packed ? p.packs : pack_tiles(p, 0);
+    const TaskLists slots = packed ? p.pack_slots : TaskLists{p.slot_off, p.slot_tasks};
+    L.num_slots = int32_t(slots.off.size()) - 1;
+    auto is_short = [&](int32_t i) { return dev[i].rows <= kSoloMaxRows && p.tasks[dev[i].first].kv_len <= kSoloMaxLen; };
+    TaskLists queue{p.queue_off, p.queue_tasks};
+    if (packed) queue = queue_entries(int32_t(dev.size()), L.num_slots, [&](int32_t i) { return dev[i].cost; }, is_short);
+    L.num_entries = int32_t(queue.off.size()) - 1;
     size_t off = 0;
     auto place = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes, 256); return at; };
-    L.slot_recs = place(p.slot_tasks.size() * sizeof(DevTask));
-    L.slot_off = place(p.slot_off.size() * 4);
+    L.slot_recs = place(slots.tasks.size() * sizeof(DevTask));
+    L.slot_off = place(slots.off.size() * 4);
     L.node_q = place(p.node_q.size() * 4);
     L.page_ids = place(p.page_ids.size() * 4);
     L.req_part_off = place(p.req_part_off.size() * 4);
     L.req_part = place(p.req_part.size() * 4);
     L.req_inline = place(size_t(p.num_requests) * (kInlineParts + 1) * 4);
-    // Run-time queue.  Short tasks (the ones a single wave runs) are bundled, in order of decreasing
-    // cost, into entries that a workgroup hands out one wave each, like a run of short tasks in a
-    // slot's list; every other task is an entry of its own.  The bundle size is the smallest that lets
-    // every entry have a workgroup of its own (then no entry is ever fetched at run time and the queue
-    // costs nothing), at most kQueueBundle.  Entries are ordered by decreasing cost, a bundle counting
-    // as the sum of its tasks, ties to the entry with the lower first task: the order in which the
-    // greedy schedule would deal them.
-    {
-        std::vector<int32_t> order(p.tasks.size());
-        for (size_t i = 0; i < order.size(); ++i) order[i] = int32_t(i);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int32_t a, int32_t b) { return p.tasks[a].cost > p.tasks[b].cost; });
-        auto is_short = [&](int32_t i) {
-            return p.tasks[i].n_req * p.group <= kSoloMaxRows && p.tasks[i].kv_len <= kSoloMaxLen;
-        };
-        int64_t n_short = 0;
-        for (int32_t i : order) n_short += is_short(i);
-        const int64_t n_long = int64_t(order.size()) - n_short;
-        int64_t bundle = kQueueBundle;
-        if (n_long < p.num_slots) bundle = std::min<int64_t>(kQueueBundle, std::max<int64_t>(1, ceil_div(n_short, p.num_slots - n_long)));
-        struct Entry { int64_t cost; std::vector<int32_t> tasks; };
-        std::vector<Entry> entries;
-        int64_t open_bundle = -1;
-        for (int32_t i : order) {
-            if (is_short(i) && open_bundle >= 0 && int64_t(entries[open_bundle].tasks.size()) < bundle) {
-                entries[open_bundle].tasks.push_back(i);
-                entries[open_bundle].cost += p.tasks[i].cost;
-                continue;
-            }
-            entries.push_back({p.tasks[i].cost, {i}});
-            open_bundle = is_short(i) ? int64_t(entries.size()) - 1 : open_bundle;
-            if (is_short(i) && bundle == 1) open_bundle = -1;
-        }
-        std::stable_sort(entries.begin(), entries.end(), [](const Entry &a, const Entry &b) { return a.cost > b.cost; });
-        p.queue_off.assign(1, 0);
-        p.queue_tasks.clear();
-        for (const Entry &e : entries) {
-            p.queue_tasks.insert(p.queue_tasks.end(), e.tasks.begin(), e.tasks.end());
-            p.queue_off.push_back(int32_t(p.queue_tasks.size()));
-        }
-    }
     if (p.schedule == 2)
         p.schedule = int64_t(p.queue_off.size()) - 1 >= int64_t(kAutoQueueEntriesPerSlot) * p.num_slots ? 1 : 0;
-    L.queue_off = place(p.queue_off.size() * 4);
-    L.queue_recs = place(p.queue_tasks.size() * sizeof(DevTask));
+    L.queue_off = place(queue.off.size() * 4);
+    L.queue_recs = place(queue.tasks.size() * sizeof(DevTask));
     L.counters = place(size_t(p.head.num_kv_heads) * 2 * 4);               // zero: nothing taken, nobody done
     L.arrive = place(size_t(p.head.num_kv_heads) * size_t(p.num_requests) * 4);   // zero: nothing arrived
-    const bool masks = !p.req_mask_off.empty();
     L.nodeq_mask = place(masks ? p.node_q.size() * 4 : 0);
     L.mask_words = place(masks ? p.req_mask.size() * 4 : 0);
     // one workgroup may end up last for every request: more query rows than a workgroup reduces in a
@@ -171,28 +304,22 @@ void build_device_image(PlanData &p)
     // like the flat plan of a tree with shared prefixes, lose up to 15 % when their single-reader
     // slices carry the hint, plans that read everything about once gain up to 12 %.
     std::vector<int32_t> readers(size_t(p.num_nodes), 0);
-    for (const codec_item &it : p.items) ++readers[it.node];
     int64_t tokens_read = 0, tokens_held = 0;
-    for (const codec_task &t : p.tasks) tokens_read += t.kv_len;
+    for (const DeviceTask &d : dev) {
+        const codec_task &t = p.tasks[d.first];
+        readers[t.node] += t.kv_begin == 0;         // one per row tile or pack of row tiles
+        tokens_read += t.kv_len;
+    }
     for (int32_t len : p.node_len) tokens_held += len;
     const bool streaming_plan = 4 * tokens_read <= 5 * tokens_held;
-    // visibility masks: which (node, request) entries carry one (the node ends the request)
-    std::vector<int32_t> nodeq_mask;
-    if (masks) {
-        nodeq_mask.assign(p.node_q.size(), -1);
-        for (int32_t n = 0; n < p.num_nodes; ++n)
-            for (int32_t e = p.node_q_off[n]; e < p.node_q_off[n + 1]; ++e) {
-                const int32_t r = p.node_q[e];
-                if (p.req_node[r] == n && p.req_mask_off[r + 1] > p.req_mask_off[r]) nodeq_mask[e] = p.req_mask_off[r];
-            }
-    }
     auto record = [&](int32_t i) {
-        const codec_task &t = p.tasks[i];
+        const DeviceTask &d = dev[i];
+        const codec_task &t = p.tasks[d.first];
         DevTask r{};
         r.page_off = p.node_page_off[t.node] + t.kv_begin / ps;
         r.kv_len = t.kv_len;
         r.q_off = t.q_off;
-        r.n_req = t.n_req;
+        r.n_req = d.rows / p.group;
         r.part_row_base = t.part_row_base;
         r.solo_run = 0;
         r.flags = streaming_plan && readers[t.node] == 1 ? kTaskReadOnce : 0;
@@ -200,6 +327,15 @@ void build_device_image(PlanData &p)
             for (int32_t e = t.q_off; e < t.q_off + t.n_req; ++e)
                 if (nodeq_mask[e] >= 0) r.flags |= kTaskMasked;
         r.single_req = t.n_req == 1 ? p.node_q[t.q_off] : -1;
+        if (d.tiles > 1) {
+            // tile k's partial rows start k * stride rows after tile 0's; those of a last tile with fewer rows
+            // start earlier, by the rows its earlier slices do not have
+            const int32_t tile_rows = t.n_req * p.group, full = d.step * tile_rows;      // step: slices per tile
+            const int32_t last_base = p.tasks[d.first + (d.tiles - 1) * d.step].part_row_base;
+            r.flags |= kTaskTiles | tile_rows << kTaskTileShift
+                       | (t.part_row_base + (d.tiles - 1) * full - last_base) << kTaskLastShift;
+            r.single_req = ~full;
+        }
         return r;
     };
     // A slot's records in the order the workgroup runs them: the tasks that need the whole workgroup
@@ -207,26 +343,23 @@ void build_device_image(PlanData &p)
     // decreasing cost).  Every run ends with waves waiting for the last one; one run per slot pays that
     // once, at the end of the launch, where the short tasks also even out what the long ones left.
     DevTask *by_slot = reinterpret_cast<DevTask *>(p.blob.data() + L.slot_recs);
-    auto is_short = [&](int32_t i) {
-        return p.tasks[i].n_req * p.group <= kSoloMaxRows && p.tasks[i].kv_len <= kSoloMaxLen;
-    };
-    for (int32_t sl = 0; sl < p.num_slots; ++sl) {
-        std::vector<int32_t> order(p.slot_tasks.begin() + p.slot_off[sl], p.slot_tasks.begin() + p.slot_off[sl + 1]);
+    for (int32_t sl = 0; sl < L.num_slots; ++sl) {
+        std::vector<int32_t> order(slots.tasks.begin() + slots.off[sl], slots.tasks.begin() + slots.off[sl + 1]);
         std::stable_partition(order.begin(), order.end(), [&](int32_t i) { return !is_short(i); });
         int32_t run = 0;
         for (int32_t k = int32_t(order.size()) - 1; k >= 0; --k) {       // runs of single-wave tasks, back to front
-            DevTask &r = by_slot[p.slot_off[sl] + k];
+            DevTask &r = by_slot[slots.off[sl] + k];
             r = record(order[k]);
             run = is_short(order[k]) ? run + 1 : 0;
             r.solo_run = run;
         }
     }
     DevTask *by_entry = reinterpret_cast<DevTask *>(p.blob.data() + L.queue_recs);
-    for (size_t i = 0; i < p.queue_tasks.size(); ++i) by_entry[i] = record(p.queue_tasks[i]);
+    for (size_t i = 0; i < queue.tasks.size(); ++i) by_entry[i] = record(queue.tasks[i]);
     auto put = [&](size_t at, const std::vector<int32_t> &v) {
         if (!v.empty()) std::memcpy(p.blob.data() + at, v.data(), v.size() * 4);
     };
-    put(L.slot_off, p.slot_off);
+    put(L.slot_off, slots.off);
     put(L.node_q, p.node_q);
     put(L.page_ids, p.page_ids);
     put(L.req_part_off, p.req_part_off);
@@ -239,7 +372,7 @@ void build_device_image(PlanData &p)
             for (int32_t j = 0; j < kInlineParts; ++j) line[1 + j] = j < cnt ? p.req_part[e0 + j] : 0;
         }
     }
-    put(L.queue_off, p.queue_off);
+    put(L.queue_off, queue.off);
     if (masks) {
         put(L.nodeq_mask, nodeq_mask);
         if (!p.req_mask.empty()) std::memcpy(p.blob.data() + L.mask_words, p.req_mask.data(), p.req_mask.size() * 4);
@@ -626,6 +759,7 @@ int build_plan(const codec_tree &tree, const codec_head_config &head,
         p.req_part_off[r + 1] = int32_t(p.req_part.size());
     }
 
+    choose_packs(p, opt.max_rows > 0 ? opt.max_rows : 256);
     build_device_image(p);
     return CODEC_OK;
 }
@@ -715,6 +849,7 @@ int refresh_plan(PlanData &p, const int32_t *node_len, const int32_t *node_page_
         makespan = std::max(makespan, load);
     }
     p.makespan = makespan;
+    for (DeviceTask &d : p.packs) d.cost = task_cost(p, d.rows, p.tasks[d.first].kv_len, true);  // packs and slots stay
     build_device_image(p);
     return CODEC_OK;
 }

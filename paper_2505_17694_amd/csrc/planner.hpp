@@ -49,11 +49,18 @@ struct DevTask {
     int32_t part_row_base;  // first partial row
     int32_t solo_run;       // number of consecutive single-wave tasks in the slot's list from this one on
     int32_t flags;          // kTaskReadOnce: no other task reads this KV slice (its node has a single row
-                            // tile); kTaskMasked: some request of the task has a visibility mask over this node
-    int32_t single_req;     // n_req == 1: the request itself (saves the read of node_q); else -1
+                            // tile); kTaskMasked: some request of the task has a visibility mask over this node;
+                            // kTaskTiles: sibling row tiles packed into one task, of (flags >> kTaskTileShift)
+                            // & 255 rows each; the last one may have fewer, its partial rows then start
+                            // flags >> kTaskLastShift rows before their place by single_req
+    int32_t single_req;     // n_req == 1: the request itself (saves the read of node_q); kTaskTiles: ~(distance
+                            // of two tiles' first partial rows); else -1
 };
 
-enum : int32_t { kTaskReadOnce = 1, kTaskMasked = 2 };
+enum : int32_t { kTaskReadOnce = 1, kTaskMasked = 2, kTaskTiles = 4, kTaskTileShift = 8, kTaskLastShift = 16 };
+constexpr int32_t kTaskLastMax = 32767;
+// Most rows of packed row tiles (64 and 256 channels): eight waves of 32 rows, four with 256 channels.
+constexpr int32_t pack_max_rows(int32_t head_dim) { return head_dim == 64 ? 256 : 128; }
 
 // Per request, the reduction kernel reads one 64-byte line: the number of partial rows on the request's
 // path and, if there are at most kInlineParts of them, the rows themselves; longer lists are read
@@ -68,6 +75,20 @@ struct DevLayout {
            nodeq_mask = 0,  // per entry of node_q: first word of that request's mask if the node ends the request, else -1
            mask_words = 0,
            total = 0;
+    int32_t num_entries = 0;    // entries of the run-time queue as the kernels see it
+    int32_t num_slots = 0;      // workgroups per KV head
+};
+
+// Lists of task indices with their offsets.
+struct TaskLists {
+    std::vector<int32_t> off, tasks;
+};
+
+// What the kernels run as one task: a task of the plan, or `tiles` sibling row tiles of one KV slice (64 and
+// 256 channels, whose tasks hold at most 32 and 16 rows), tile k being the plan's task first + k * step.
+struct DeviceTask {
+    int32_t first, step, tiles, rows;
+    int64_t cost;
 };
 
 struct PlanData {
@@ -88,6 +109,10 @@ struct PlanData {
     std::vector<int32_t> req_part_off, req_part;
     int64_t cost_l = 0, makespan = 0;
     int32_t part_rows = 0;
+
+    // Packed row tiles (empty: the kernels run the plan's tasks, slots and queue as they are)
+    std::vector<DeviceTask> packs;
+    TaskLists pack_slots;               // indices into packs, per workgroup of a KV head
 
     CostTable table;                    // the table the plan was estimated with (for refresh_plan)
 

@@ -131,6 +131,52 @@ def test_two_row_tiles_with_64_channels(hq, hkv, requests, dtype):
         assert max(rows) <= 32 and max(rows) > 16
 
 
+def _image_bytes_without_packs(view, paged, head):
+    """Size of the device metadata when the kernels run the plan's tasks as they are (codec_plan_device_bytes)."""
+    pad = lambda n: (n + 255) // 256 * 256
+    tasks, reqs = len(view["tasks"]), len(view["req_part_off"]) - 1
+    sizes = [tasks * 32, (view["num_slots"] + 1) * 4, len(view["node_q"]) * 4, len(paged.page_ids) * 4, (reqs + 1) * 4,
+             len(view["req_part"]) * 4, reqs * 64, len(view["queue_off"]) * 4, tasks * 32, head.num_kv_heads * 8,
+             head.num_kv_heads * reqs * 4]
+    return sum(pad(n) for n in sizes)
+
+
+@pytest.mark.parametrize("d,hq,hkv,requests,packed", [
+    (64, 8, 2, 16, True), (64, 8, 2, 17, True), (64, 8, 2, 32, True), (64, 8, 2, 33, True), (64, 8, 2, 64, True),
+    (64, 8, 2, 70, True), (64, 4, 4, 41, True), (64, 12, 4, 43, True), (256, 8, 2, 8, True), (256, 8, 2, 9, True),
+    (256, 8, 2, 16, True), (256, 8, 2, 17, True), (256, 8, 2, 32, True), (256, 8, 2, 35, True), (256, 4, 4, 19, True),
+    (256, 12, 4, 27, True), (64, 8, 2, 8, False), (256, 8, 2, 4, False)])
+@pytest.mark.parametrize("opts", [{"num_slots": 2, "split_align": 32}, {"num_slots": 3, "split_align": 4096},
+                                  {"num_slots": 2, "schedule": 1, "split_align": 64}, {"num_slots": 2, "fused": 1}])
+def test_packed_row_tiles(d, hq, hkv, requests, packed, opts):
+    """Sibling row tiles of 64 and 256 channels run as one task: two tiles, full packs of every width (one, two
+    and four waves per row group), packs with a smaller last tile, several packs per node; slices of one block
+    up to whole nodes, ragged ones, lengths around the depth of the block ring; beside single-wave tasks, and
+    after the lengths have grown.  One tile per node: nothing to pack."""
+    C = _C()
+    lens = [1, 31, 33, 97, 127, 129, 161, 513, 700, 1025]
+    f = two_level_forest(lens[0], [43] * requests)
+    for n in lens[1:]:
+        f = concat_forests(f, two_level_forest(n, [5 + n % 40] * requests))
+    w = make_workload(f"packs-{d}-{hq}-{hkv}-{requests}", f, HeadConfig(hq, hkv, d, DTYPE_BF16), seed=700 + d + requests,
+                      poison=True, layout="htd" if requests % 2 else "thd")
+    _, view = check(w, **opts)
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", **opts)
+    assert (C.codec_plan_device_bytes(pa.plan) < _image_bytes_without_packs(view, w.paged, w.head)) == packed
+    # the longest root grows inside its last page: the packs stay
+    node = int(np.argmax(f.node_len))
+    grown = f.node_len.copy()
+    grown[node] += 3
+    w2 = make_workload("grown", Forest(f.parent, grown, f.req_node), w.head, seed=5, poison=True, paged=w.paged)
+    wd = w2.to("cuda:0")
+    pa.refresh(grown)
+    out = pa.decode(wd.q, wd.k_pool, wd.v_pool)
+    torch.cuda.synchronize()
+    pa.close()
+    ref, _ = A.decode_attention_workload(w2)
+    assert np.max(np.abs(out.double().cpu().numpy() - ref)) <= TOL
+
+
 @pytest.mark.parametrize("max_rows", [8, 16, 32, 48, 64, 100, 128, 200, 256])
 def test_row_tiles(max_rows):
     """70 requests x group 4 = 280 rows under the root: stream and dense task shapes, row tiling."""

@@ -26,7 +26,7 @@
 //    LDS at the end.  Runs of short tasks are handed out one wave each instead.
 //  * "dense" (tasks of 17..256 rows, wide variant): 32 x 32 x 16 tiles; eight waves
 //    split the rows (32 each) and walk the slice together; blocks are copied HBM ->
-//    LDS asynchronously into a ring of 16 KB slots (six or eight blocks in flight)
+//    LDS asynchronously into a ring of 16 KB slots (five or six blocks in flight)
 //    and read by all waves, V through transposing LDS reads (ds_read_b64_tr_b16).
 //    Long slices under at most 128 rows put two waves on each row group, on
 //    alternate blocks.
@@ -675,7 +675,7 @@ __device__ __forceinline__ void run_stream(const PacParams &P, const DevTask &t,
 //
 // Blocks travel HBM -> LDS without passing through registers (global_load_lds_dwordx4: every lane
 // moves 16 bytes, a wave fills 1 KB of consecutive LDS).  A ring of kRing block slots (16 KB each:
-// 32 K rows then 32 V rows of 256 B) keeps six (eight with two-block intervals) blocks in flight per
+// 32 K rows then 32 V rows of 256 B) keeps five (six with two-block intervals) blocks in flight per
 // workgroup.  Rows are stored unpadded; the 16-byte column index is XORed with a function of the row so
 // that the operand reads spread over all banks.  The swizzle is applied on the global side: the lane that fills LDS
 // column c of a row fetches column c ^ f(row).
@@ -979,13 +979,17 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         pin(p[tt]);
     };
 
-    // Common to all roles.  Blocks 0 .. 7 are requested up front; interval j (j = 0 .. nint-1) starts
-    // with a barrier behind which blocks S*j+8 .. S*j+8+S-1 (S = STRIDE) are requested into the slots
-    // that blocks S*j .. S*j+S-1 have left, so those are read from LDS before that barrier.  The LDS
-    // reads of interval j reach up to block S*j + 3*S - 1, which must have landed at its barrier: each
-    // wave issues 2 loads per block and loads complete in order, so a block has landed once at most
-    // 2 * (blocks issued after it) loads are outstanding; near the end of the slice, where fewer blocks
-    // follow, the wait is for everything.
+    // Common to all roles.  All but S = STRIDE blocks of the ring are requested up front; interval j
+    // (j = 0 .. nint-1) starts with a barrier behind which S blocks are requested into the slots of the
+    // blocks of interval j-1.  Those were consumed before the barrier; the LDS reads issued last, of blocks
+    // that interval j uses, may still be under way: the barrier waits for no LDS read (one that did, with
+    // the slots of interval j's own blocks refilled, cost 1.1 % on a six-level binary tree of 32 .. 1024
+    // rows: 40.3 against 39.9 us, 1.3 % on 64 requests of 4 rows below a 4096-token root: 26.5 against
+    // 26.1 us, nothing on a 131072-token root under 512 rows, whose rate the clock sets).  The LDS
+    // reads of interval j reach up to block S*j + 3*S - 1, which must have landed at its barrier: each wave
+    // issues 2 loads per block and loads complete in order, so a block has landed once at most 2 * (blocks
+    // issued after it) loads are outstanding; near the end of the slice, where fewer blocks follow, the
+    // wait is for everything.
     const int nblk = (t.kv_len + 31) >> 5;
     const int nint = (nblk + STRIDE - 1) / STRIDE - 1;                  // the same for every wave
     // Start of the task.  What the first matrix instruction waits for is a chain of dependent reads:
@@ -995,6 +999,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     // LDS like the blocks (dma16_rows): each wave parks its 8 KB in the last four slots of the ring,
     // whose blocks are requested once every wave has taken its rows into registers, behind the barrier
     // that ends this start-up; the other blocks of the ring are requested right behind the rows.
+    constexpr int LAG = STRIDE;                                         // slots left free when an interval starts
     constexpr int EARLY = RING - 4;                                     // blocks requested ahead of that barrier
     static_assert(EARLY >= 2 * STRIDE && 8 * 8192 == 4 * kBlockBytes, "the rows' parking space is the last four slots");
     int pg_late[4];
@@ -1046,26 +1051,29 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     }
     int pg_next[STRIDE];                                                // pages of the blocks interval 0 requests
 #pragma unroll
-    for (int u = 0; u < STRIDE; ++u) pg_next[u] = page_issue(RING + u);
+    for (int u = 0; u < STRIDE; ++u) pg_next[u] = pg_late[4 - LAG + u];
     __syncthreads();
 #pragma unroll
-    for (int d = 0; d < 4; ++d)
+    for (int d = 0; d < 4 - LAG; ++d)
         if (EARLY + d < nblk) dma_block(EARLY + d, pg_late[d]);
 
-    // more: blocks S*j+8 .. S*j+8+S-1 all exist
-    auto wait_and_sync = [&](auto more) {
-        if constexpr (decltype(more)::value) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * (RING - 3 * STRIDE)));
-        else                                 __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();                    // blocks up to S*j+3S-1 are complete; everyone is done with block(s) S*j ..
+    // more: the blocks that interval j requests all exist
+    auto wait_and_sync = [&](auto more) {   // then blocks up to S*j+3S-1 are complete, and everyone is done with those below S*j
+        if constexpr (decltype(more)::value) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" : : "n"(2 * (RING - LAG - 3 * STRIDE)) : "memory");
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            __syncthreads();
+        }
     };
     auto request_blocks = [&](int j, auto more) {                       // any time inside interval j
         if constexpr (decltype(more)::value) {
 #pragma unroll
-            for (int u = 0; u < STRIDE; ++u) dma_block(STRIDE * j + RING + u, pg_next[u]);
+            for (int u = 0; u < STRIDE; ++u) dma_block(STRIDE * j + RING - LAG + u, pg_next[u]);
 #pragma unroll
-            for (int u = 0; u < STRIDE; ++u) pg_next[u] = page_issue(STRIDE * (j + 1) + RING + u);
+            for (int u = 0; u < STRIDE; ++u) pg_next[u] = page_issue(STRIDE * (j + 1) + RING - LAG + u);
         } else if constexpr (STRIDE == 2) {
-            if (2 * j + RING < nblk) dma_block(2 * j + RING, pg_next[0]);         // an odd block left over
+            if (2 * j + RING - LAG < nblk) dma_block(2 * j + RING - LAG, pg_next[0]);         // an odd block left over
         }
     };
     auto enter_interval = [&](int j, auto more) {                       // j < nint
@@ -1075,7 +1083,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     using yes = std::true_type;
     using no = std::false_type;
     auto short_block = [&](int b) { return c.kv_len - b * 32; };        // valid tokens if below 32
-    auto more_follow = [&](int j) { return STRIDE * j + RING + STRIDE - 1 < nblk; };
+    auto more_follow = [&](int j) { return STRIDE * j + RING - LAG + STRIDE - 1 < nblk; };
 
     if constexpr (LIVE) {
         // The wave's k-th block is b_k = blk(k), nmine of them.  Per block a vector half V(b_k) (scores

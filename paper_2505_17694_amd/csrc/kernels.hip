@@ -1441,21 +1441,34 @@ __device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t
                 *reinterpret_cast<u32x4 __attribute__((address_space(3))) *>(uintptr_t(at + n * 1024)) = u32x4{0u, 0u, 0u, 0u};
     };
 
-    // Start: the first interval's copies, then the query rows; waiting for the rows (the compiler waits for
-    // every load in flight) waits for that interval too, so the others are requested behind it.
+    // Start: the rows' requests and the page ids, read together; then the first interval's copies and the query
+    // rows.  Waiting for the rows (the compiler waits for every load in flight) waits for that interval too, so
+    // the others are requested behind it.
     int pg[R][MINE];
 #pragma unroll
     for (int i = 0; i < R; ++i)
 #pragma unroll
         for (int u = 0; u < MINE; ++u) pg[i][u] = page_issue(i, u);
-    request(0, pg[0]);
-    if (live) gather_q<NT, D>(P, t, head, row0, rows, l16, grp, qb);
-    else {
+    const char *qp[NT];
+    bool row_live[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qb[nt][ks] = u32x4{0u, 0u, 0u, 0u};
+    for (int nt = 0; nt < NT; ++nt) {
+        const int row = row0 + nt * 16 + l16;
+        row_live[nt] = row < rows;
+        const int qi = row_live[nt] ? row / P.group : 0;    // a dead row reads the task's first
+        const int hj = row_live[nt] ? row - qi * P.group : 0;
+        int req = P.node_q[t.q_off + qi];
+        pin(req);                                           // the wait for it stands here, ahead of the copies
+        qp[nt] = static_cast<const char *>(P.q) + (int64_t(req) * P.h_q + int64_t(head) * P.group + hj) * (D * 2) + grp * 16;
     }
+    request(0, pg[0]);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            qb[nt][ks] = ld16(qp[nt] + ks * 64);
+            if (!row_live[nt]) qb[nt][ks] = u32x4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll

@@ -344,7 +344,8 @@ int codec_decode_attention(const codec_plan_t *plan, const void *q,
  * codec_partial_attention runs the scheduled partial attention tasks and fills
  * `workspace`; codec_partial_reduction merges the partials in `workspace` into
  * `out`.  Same arguments, checks and stream semantics as codec_decode_attention,
- * which is exactly the first followed by the second.
+ * whose output is that of the first followed by the second (it leaves
+ * the partials out where every request has exactly one).
  */
 int codec_partial_attention(const codec_plan_t *plan, const void *q,
                             const void *k_pages, const void *v_pages,

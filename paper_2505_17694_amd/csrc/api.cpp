@@ -15,6 +15,7 @@ struct codec_plan {
     void *device_meta = nullptr;
     int32_t max_page_id = -1;
     int32_t max_task_rows = 0;
+    bool single_parts = false;      // every request has one partial result, in a task of at most 16 rows
 };
 
 namespace {
@@ -72,6 +73,7 @@ int codec_plan_create(const codec_tree *tree, const codec_head_config *head,
         const int32_t rows = t.n_req * p->d.group;
         p->max_task_rows = rows > p->max_task_rows ? rows : p->max_task_rows;
     }
+    p->single_parts = p->max_task_rows <= codec::kSoloMaxRows && int32_t(p->d.req_part.size()) == p->d.num_requests;
     *out = p;
     return CODEC_OK;
 }
@@ -215,7 +217,8 @@ codec::MergeParams merge_params(const codec_plan_t *plan, const void *workspace,
     return mp;
 }
 
-// Partial attention over the plan's tasks; with `fused_out` the launch also reduces (single-launch mode).
+// Partial attention over the plan's tasks; with `fused_out` the launch also reduces (single-launch mode), or
+// has nothing to reduce (single_parts).
 int partial_attention(const codec_plan_t *plan, const void *q, const void *k_pages,
                       const void *v_pages, const codec_kv_layout *layout,
                       void *workspace, size_t workspace_bytes, void *fused_out, void *stream)
@@ -274,7 +277,8 @@ int partial_attention(const codec_plan_t *plan, const void *q, const void *k_pag
     }
     if (fused_out) {
         pp.merge = merge_params(plan, workspace, fused_out);
-        pp.arrive = reinterpret_cast<int32_t *>(const_cast<char *>(meta) + L.arrive);
+        if (plan->single_parts) pp.part_o = nullptr;
+        else pp.arrive = reinterpret_cast<int32_t *>(const_cast<char *>(meta) + L.arrive);
     }
     if (int e = codec::launch_pac(pp, d.head.dtype, d.head.head_dim, L.num_slots, plan->max_task_rows, !d.packs.empty(), stream))
         return hip_failure("partial attention launch", e);
@@ -314,7 +318,8 @@ int codec_decode_attention(const codec_plan_t *plan, const void *q, const void *
 {
     if (plan && plan->d.num_requests == 0) return layout ? CODEC_OK : CODEC_ERR_INVALID_ARGUMENT;
     if (!out || !aligned16(out)) return CODEC_ERR_INVALID_ARGUMENT;
-    if (plan && plan->d.fused)          // one launch: the last workgroup to arrive at a request reduces it
+    // one launch: the last workgroup to arrive at a request reduces it, or there is nothing to reduce
+    if (plan && (plan->d.fused || plan->single_parts))
         return partial_attention(plan, q, k_pages, v_pages, layout, workspace, workspace_bytes, out, stream);
     if (int st = codec_partial_attention(plan, q, k_pages, v_pages, layout, workspace, workspace_bytes, stream))
         return st;

@@ -27,7 +27,9 @@ struct PacParams {
     const int32_t *slot_off;
     const int32_t *node_q;
     const int32_t *page_ids;
-    float *part_o;                  // [h_kv][part_rows][head_dim] unnormalised partial outputs
+    // [h_kv][part_rows][head_dim] unnormalised partial outputs; nullptr (no task of more than 16 rows): every
+    // request has a single partial result, tasks write finished rows into merge.out
+    float *part_o;
     float *part_ml;                 // [h_kv][part_rows][2]   (max in log2 units, sum of exponentials)
     int32_t h_q, h_kv, group, page_shift, part_rows;    // page_shift = log2(tokens per page)
     float scale_log2e;              // scale * log2(e): scores are kept in log2 units

@@ -177,6 +177,40 @@ def test_packed_row_tiles(d, hq, hkv, requests, packed, opts):
     assert np.max(np.abs(out.double().cpu().numpy() - ref)) <= TOL
 
 
+@pytest.mark.parametrize("d,hq,hkv,dtype", [(128, 8, 2, DTYPE_BF16), (128, 7, 7, DTYPE_FP16), (128, 28, 4, DTYPE_FP16),
+                                            (128, 32, 2, DTYPE_BF16), (64, 8, 2, DTYPE_FP16), (64, 16, 1, DTYPE_BF16),
+                                            (256, 6, 2, DTYPE_BF16), (256, 16, 1, DTYPE_FP16)])
+@pytest.mark.parametrize("opts", [{}, {"num_slots": 2}, {"num_slots": 3, "schedule": 1}, {"num_slots": 2, "fused": 1}])
+def test_requests_with_a_single_partial(d, hq, hkv, dtype, opts):
+    """Plans in which every request has one partial result: one launch writes finished rows (the workspace
+    stays as it was), bit for bit what the two phases on their own give.  Undivided contexts of a team of
+    waves and of single-wave runs, lengths around a block, several requests in one task (ending at one
+    node), a masked node, 1 to 16 rows per request."""
+    C = _C()
+    lens = [1, 15, 31, 32, 33, 200, 700, 2049, 2500]
+    f = unshared_forest(lens)
+    if hq // hkv <= 8:                                   # two requests of one node share a task
+        f = Forest(f.parent, f.node_len, np.concatenate([f.req_node, np.array([4, 6], np.int32)]))
+    n, b = len(lens), len(f.req_node)
+    masks = [[]] * (b - 1) + [[0x80000001]]              # a masked request over a 32-token node of its own
+    f = Forest(np.append(f.parent, -1), np.append(f.node_len, 32), np.append(f.req_node[:b - 1], n),
+               np.concatenate([[0], np.cumsum([len(m) for m in masks])]), np.array([w for m in masks for w in m], np.uint32))
+    w = make_workload(f"single-{d}-{hq}-{hkv}", f, HeadConfig(hq, hkv, d, dtype), seed=800 + d, poison=True)
+    check(w, split_align=4096, **opts)
+    wd = w.to("cuda:0")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", split_align=4096, **opts)
+    pa.workspace.fill_(0x5A)
+    one = pa.decode(wd.q, wd.k_pool, wd.v_pool)
+    torch.cuda.synchronize()
+    assert bool((pa.workspace == 0x5A).all())
+    two = torch.empty_like(one)
+    pa.partial_attention(wd.q, wd.k_pool, wd.v_pool)
+    pa.partial_reduction(two)
+    torch.cuda.synchronize()
+    pa.close()
+    assert torch.equal(one.view(torch.int16), two.view(torch.int16))
+
+
 @pytest.mark.parametrize("max_rows", [8, 16, 32, 48, 64, 100, 128, 200, 256])
 def test_row_tiles(max_rows):
     """70 requests x group 4 = 280 rows under the root: stream and dense task shapes, row tiling."""

@@ -1815,10 +1815,18 @@ __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const
 // tiles into operand addresses, so the ring must start on a 512-byte boundary (no static LDS there).
 extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
 
-template <int DT, int FORM, int D>
+// FUSED: with the code of the single-launch mode (used if P.arrive).  The kernels without it are shorter and
+// need fewer registers, which shows where a step is a few dozen microseconds: 32 layers of document questions
+// 843 -> 833 us, a six-level tree with one KV head 39.9 -> 39.4 us, three-level documents 161.2 -> 160.5 us, a
+// lone request 15.1 -> 14.8 us.  Only the tile path of 256 channels was allocated worse without it (three-level
+// documents 289 -> 299 us), so its one kernel serves both modes (one_kernel).
+constexpr bool one_kernel(int form, int d) { return form == kFormWide && d == 256; }
+template <int DT, int FORM, int D, bool FUSED>
 __global__ void __launch_bounds__(kernel_waves(FORM, D) * 64, D > 128 ? 1 : 2)
-pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in registers need a wave per SIMD
+pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in registers need a wave per SIMD
 {
+    PacParams P = params;
+    if constexpr (!FUSED) P.arrive = nullptr;
     // kFormWide: the dense path (128 channels, eight waves) or the tile path (64 and 256 channels)
     constexpr bool WIDE = FORM == kFormWide, DENSE = WIDE && D == kHeadDim, TILES = WIDE && D != kHeadDim;
     constexpr bool FINISH = FORM == kFormFinish;
@@ -1868,7 +1876,7 @@ pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in regi
                     const DevTask mine = recs[i + k];
                     if (mine.flags & kTaskReadOnce) run_stream<DT, true, 1, 1, D, FINISH>(P, mine, head, lds, 0, stage);
                     else                run_stream<DT, false, 1, 1, D, FINISH>(P, mine, head, lds, 0, stage);
-                    if constexpr (!FINISH)
+                    if constexpr (FUSED)
                         if (P.arrive) task_delivered_by_wave<DT, D>(P, mine, head);
                     k = 0;
                     if ((threadIdx.x & 63) == 0) k = atomicAdd(next, 1);
@@ -1890,7 +1898,7 @@ pac_kernel(const PacParams P)     // 256 channels: two blocks of K and V in regi
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head, lds, wave);
                     else             run_stream<DT, false, 2, W, D>(P, t, head, lds, wave);
                 }
-                if constexpr (!FINISH)
+                if constexpr (FUSED)
                     if (P.arrive) task_delivered_by_workgroup<DT, D>(P, t, head, lds, W);
                 ++i;
             }
@@ -1954,6 +1962,14 @@ __global__ void __launch_bounds__(256) stream_read_kernel(const char *buf, uint6
 // handle for hipGetSymbolAddress; kernels get the address that call returns, as an ordinary argument.
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
+// dynamic LDS of the forms with the dense and the tile path
+template <int D>
+constexpr int wide_lds_bytes()
+{
+    if constexpr (D == kHeadDim) return kRingBytes;
+    else                         return TilePath<D>::kRingBytes;
+}
+
 int static_scratch_address(void **ptr)
 {
     // one lookup per device, with that device current; the table is filled under a lock and read-only after
@@ -1985,13 +2001,22 @@ int prepare_kernels()
     if (dev < 0 || dev >= kMaxDevices) return int(hipErrorInvalidDevice);
     std::lock_guard<std::mutex> guard(lock);
     if (done[dev]) return 0;
-    const struct { const void *kernel; int bytes; } kernels[] = {
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, kFormWide, 128>), kRingBytes},
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, kFormWide, 128>), kRingBytes},
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, kFormWide, 64>), TilePath<64>::kRingBytes},
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, kFormWide, 64>), TilePath<64>::kRingBytes},
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_FP16, kFormWide, 256>), TilePath<256>::kRingBytes},
-        {reinterpret_cast<const void *>(pac_kernel<CODEC_DTYPE_BF16, kFormWide, 256>), TilePath<256>::kRingBytes},
+    struct Kernel { const void *kernel; int bytes; };
+    auto wide = [](auto dt, auto d, auto fused) {
+        constexpr int D = decltype(d)::value;
+        return Kernel{reinterpret_cast<const void *>(pac_kernel<decltype(dt)::value, kFormWide, D, decltype(fused)::value>), wide_lds_bytes<D>()};
+    };
+    using f16 = std::integral_constant<int, CODEC_DTYPE_FP16>;
+    using b16 = std::integral_constant<int, CODEC_DTYPE_BF16>;
+    using d64 = std::integral_constant<int, 64>;
+    using d128 = std::integral_constant<int, 128>;
+    using d256 = std::integral_constant<int, 256>;
+    using no = std::false_type;
+    using yes = std::true_type;
+    const Kernel kernels[] = {
+        wide(f16{}, d128{}, no{}), wide(b16{}, d128{}, no{}), wide(f16{}, d128{}, yes{}), wide(b16{}, d128{}, yes{}),
+        wide(f16{}, d64{}, no{}),  wide(b16{}, d64{}, no{}),  wide(f16{}, d64{}, yes{}),  wide(b16{}, d64{}, yes{}),
+        wide(f16{}, d256{}, yes{}), wide(b16{}, d256{}, yes{}),
     };
     for (const auto &k : kernels)
         if (hipError_t e = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes)) return int(e);
@@ -1999,44 +2024,34 @@ int prepare_kernels()
     return 0;
 }
 
-// 64 and 256 channels: the kernel with the tile path where the plan holds packed row tiles, else without
 template <int DT, int D>
-void launch_narrow(const PacParams &p, dim3 grid, bool tiles, hipStream_t s)
+void launch_pac_of(const PacParams &p, dim3 grid, bool wide, hipStream_t s)
 {
-    if (!p.part_o) {
-        hipLaunchKernelGGL((pac_kernel<DT, kFormFinish, D>), grid, dim3(kNarrowWaves * 64), 0, s, p);
-        return;
-    }
-    if constexpr (D != kHeadDim)
-        if (tiles) {
-            hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D>), grid, dim3(TilePath<D>::kWaves * 64), TilePath<D>::kRingBytes, s, p);
-            return;
-        }
-    hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D>), grid, dim3(kNarrowWaves * 64), 0, s, p);
+    const bool fused = p.arrive != nullptr;
+    constexpr bool kOne = one_kernel(kFormWide, D);
+    const dim3 block((wide ? kernel_waves(kFormWide, D) : kNarrowWaves) * 64);
+    const size_t lds = wide ? wide_lds_bytes<D>() : 0;
+    if (!p.part_o)          hipLaunchKernelGGL((pac_kernel<DT, kFormFinish, D, false>), grid, block, lds, s, p);
+    else if (wide && fused) hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, true>), grid, block, lds, s, p);
+    else if (wide)          hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, kOne>), grid, block, lds, s, p);
+    else if (fused)         hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, true>), grid, block, lds, s, p);
+    else                    hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, false>), grid, block, lds, s, p);
 }
 
 int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, void *stream)
 {
     if (head_dim != 64 && head_dim != 128 && head_dim != 256) return int(hipErrorInvalidValue);
-    const bool wide = head_dim == kHeadDim && max_rows_in_plan > 16;
-    // the planner never builds a plan with more rows per task than the variant runs
+    // all task shapes: dense tasks with 128 channels, packed row tiles with 64 and 256
+    const bool wide = head_dim == kHeadDim ? max_rows_in_plan > 16 : tiles;
+    // the planner never builds a plan with more rows per task than the kernel runs
     if (!wide && max_rows_in_plan > 16 * stream_tiles(head_dim)) return int(hipErrorInvalidValue);
-    if (!p.part_o && (tiles || max_rows_in_plan > 16)) return int(hipErrorInvalidValue);
-    const dim3 grid(unsigned(num_slots) * unsigned(p.h_kv)), block((wide ? kWideWaves : kNarrowWaves) * 64);
+    if (!p.part_o && (wide || max_rows_in_plan > 16)) return int(hipErrorInvalidValue);
+    const dim3 grid(unsigned(num_slots) * unsigned(p.h_kv));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool f16 = dtype == CODEC_DTYPE_FP16;
-    if (wide) {
-        if (f16) hipLaunchKernelGGL((pac_kernel<CODEC_DTYPE_FP16, kFormWide, 128>), grid, block, kRingBytes, s, p);
-        else     hipLaunchKernelGGL((pac_kernel<CODEC_DTYPE_BF16, kFormWide, 128>), grid, block, kRingBytes, s, p);
-    } else if (head_dim == 64) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 64>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 64>(p, grid, tiles, s);
-    } else if (head_dim == 128) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 128>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 128>(p, grid, tiles, s);
-    } else if (head_dim == 256) {
-        if (f16) launch_narrow<CODEC_DTYPE_FP16, 256>(p, grid, tiles, s); else launch_narrow<CODEC_DTYPE_BF16, 256>(p, grid, tiles, s);
-    } else {
-        return int(hipErrorInvalidValue);
-    }
+    const bool half = dtype == CODEC_DTYPE_FP16;
+    if (head_dim == 64)       half ? launch_pac_of<CODEC_DTYPE_FP16, 64>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 64>(p, grid, wide, s);
+    else if (head_dim == 128) half ? launch_pac_of<CODEC_DTYPE_FP16, 128>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 128>(p, grid, wide, s);
+    else                      half ? launch_pac_of<CODEC_DTYPE_FP16, 256>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 256>(p, grid, wide, s);
     return int(hipGetLastError());
 }
 

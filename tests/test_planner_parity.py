@@ -505,3 +505,41 @@ def test_other_head_dimensions_plan(head_dim, name, hq, hkv, share):
         ref = P.plan(f.parent, f.node_len, f.req_node, group, m, 256, cap, bool(share), _default_table(0),
                      slack=True, diagonal=True)
     _compare(view, ref)
+
+
+# ---- which plans of 64 and 256 channels run sibling row tiles as one task ----
+@pytest.mark.parametrize("d,tile", [(64, 32), (256, 16)])
+@pytest.mark.parametrize("opts,packed", [({}, True), ({"max_rows": 256}, True), ({"schedule": 1}, True), ({"fused": 1}, True),
+                                         ({"share": 0}, False), ({"max_rows": "tile"}, False), ({"max_rows": 16}, False),
+                                         ({"masked": True}, False), ({"head_dim": 128}, False)])
+def test_which_plans_pack_row_tiles(d, tile, opts, packed):
+    """The device image holds fewer task records than the plan where sibling row tiles of a slice are packed:
+    not in flat plans, not beyond the caller's max_rows, not at nodes that end masked requests, not with 128
+    channels.  The exported plan has its tiles either way."""
+    opts = dict(opts)
+    head_dim = opts.pop("head_dim", d)
+    if opts.get("max_rows") == "tile":
+        opts["max_rows"] = tile
+    if opts.pop("masked", False):                   # 64 queries of one 32-token node, every one masked
+        b = 64
+        f = Forest(np.array([-1]), np.array([32]), np.zeros(b, np.int32), np.arange(b + 1), np.full(b, 0x80000001, np.uint32))
+    else:
+        f = two_level_forest(2000, [20] * 64)
+        for n in (500, 900, 1300):                  # enough tiles for the padded image to show
+            f = concat_forests(f, two_level_forest(n, [20] * 64))
+    head = HeadConfig(8, 2, head_dim)
+    paged = build_paged_kv(f, head, 3)
+    pa = C.PlannedAttention(f, paged, head, device="cpu", num_slots=2, **opts)
+    view = pa.export()
+    pad = lambda n: (n + 255) // 256 * 256
+    tasks, reqs = len(view["tasks"]), len(view["req_part_off"]) - 1
+    sizes = [tasks * 32, (view["num_slots"] + 1) * 4, len(view["node_q"]) * 4, len(paged.page_ids) * 4, (reqs + 1) * 4,
+             len(view["req_part"]) * 4, reqs * 64, len(view["queue_off"]) * 4, tasks * 32, 2 * 8, 2 * reqs * 4]
+    if f.req_mask_off is not None:
+        sizes += [len(view["node_q"]) * 4, len(f.req_mask) * 4]
+    plain = sum(pad(n) for n in sizes)
+    have = C.codec_plan_device_bytes(pa.plan)
+    assert have < plain if packed else have == plain
+    if head_dim != 128:
+        assert max(t["n_req"] * 4 for t in view["tasks"]) <= tile
+    pa.close()

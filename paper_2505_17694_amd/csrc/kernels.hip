@@ -1748,9 +1748,9 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
 // first word of the request's line) makes the delivering workgroup reduce that request's rows of this
 // KV head right away, and put the counter back to zero for the next launch.  In this mode partial rows
 // are written and read with device-coherent accesses (st8_device / ld8_device), so no cache has to be
-// written back or invalidated: a delivering wave waits until its stores have been acknowledged (they are
-// then visible device-wide), and only then counts; the workgroup that sees the last count reads the rows
-// after that.  (Fences at device scope instead, with plain accesses, cost a write-back and an
+// written back or invalidated: every wave that has stored rows waits until its stores have been acknowledged
+// (they are then visible device-wide), and only then is the delivery counted; the workgroup that sees the
+// last count reads the rows after that.  (Fences at device scope instead, with plain accesses, cost a write-back and an
 // invalidation of the whole L2 per task: measured, several times the launch they were to save.)
 __device__ __forceinline__ bool deliver(const PacParams &P, const DevTask &t, int head, int i, int &req)
 {
@@ -1763,13 +1763,19 @@ __device__ __forceinline__ bool deliver(const PacParams &P, const DevTask &t, in
     return true;
 }
 
+// Waits until the wave's stores have been acknowledged.  No barrier or fence at workgroup scope does that on
+// this target: they order LDS, and the wave's own path to the vector cache keeps global stores in order for
+// the workgroup; rows that another workgroup will read need the wait of every wave that has stored some.
+__device__ __forceinline__ void stores_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // A task that the whole workgroup ran (every thread calls this after the task).  Inline without fail, as all
 // device functions here: one real call makes the compiler keep the kernel's parameters in scratch memory.
 template <int DT, int D>
 __device__ __forceinline__ void task_delivered_by_workgroup(const PacParams &P, const DevTask &t, int head, char *lds_raw, int waves)
 {
     int *count = reinterpret_cast<int *>(lds_raw), *ready = count + 1;
-    __syncthreads();                    // every wave has waited for its stores of partial rows; LDS is free
+    stores_acknowledged();              // the rows of a task may come from every wave (dense and tile path)
+    __syncthreads();                    // ... and all have waited when a thread counts; LDS is free
     if (threadIdx.x == 0) *count = 0;
     __syncthreads();
     if (int(threadIdx.x) < t.n_req) {
@@ -1795,7 +1801,7 @@ template <int DT, int D>
 __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const DevTask &t, int head)
 {
     const int lane = threadIdx.x & 63;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // waits for the wave's stores of partial rows
+    stores_acknowledged();
     int req = 0;
     const bool last = lane < t.n_req && deliver(P, t, head, lane, req);
     unsigned long long ready = __ballot(last);

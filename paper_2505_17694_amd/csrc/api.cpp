@@ -15,7 +15,7 @@ struct codec_plan {
     void *device_meta = nullptr;
     int32_t max_page_id = -1;
     int32_t max_task_rows = 0;
-    bool single_parts = false;      // every request has one partial result, in a task of at most 16 rows
+    bool single_parts = false;      // codec::single_parts(d)
 };
 
 namespace {
@@ -73,7 +73,7 @@ int codec_plan_create(const codec_tree *tree, const codec_head_config *head,
         const int32_t rows = t.n_req * p->d.group;
         p->max_task_rows = rows > p->max_task_rows ? rows : p->max_task_rows;
     }
-    p->single_parts = p->max_task_rows <= codec::kSoloMaxRows && int32_t(p->d.req_part.size()) == p->d.num_requests;
+    p->single_parts = codec::single_parts(p->d);
     *out = p;
     return CODEC_OK;
 }

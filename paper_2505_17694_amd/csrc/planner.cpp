@@ -854,4 +854,12 @@ int refresh_plan(PlanData &p, const int32_t *node_len, const int32_t *node_page_
     return CODEC_OK;
 }
 
+bool single_parts(const PlanData &p)
+{
+    if (!p.packs.empty() || int32_t(p.req_part.size()) != p.num_requests) return false;
+    for (const codec_task &t : p.tasks)
+        if (t.n_req * p.group > kSoloMaxRows) return false;
+    return true;
+}
+
 }  // namespace codec

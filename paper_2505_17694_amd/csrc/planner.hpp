@@ -137,4 +137,8 @@ int build_best_plan(const codec_tree &tree, const codec_head_config &head,
 // makespan are re-estimated, the device image is rebuilt.  On error `plan` is left as it was.
 int refresh_plan(PlanData &plan, const int32_t *node_len, const int32_t *node_page_off, const int32_t *page_ids);
 
+// Every request has one partial result and the kernels run nothing but tasks of at most 16 rows: the attention
+// launch writes finished rows and there is nothing to reduce.  Packed row tiles hold more rows than that.
+bool single_parts(const PlanData &plan);
+
 }  // namespace codec

@@ -211,6 +211,28 @@ def test_requests_with_a_single_partial(d, hq, hkv, dtype, opts):
     assert torch.equal(one.view(torch.int16), two.view(torch.int16))
 
 
+@pytest.mark.parametrize("d,hq,hkv,length,samples", [(256, 16, 8, 256, 16), (256, 16, 8, 1024, 32), (256, 32, 8, 200, 16),
+                                                     (64, 16, 8, 500, 32)])
+@pytest.mark.parametrize("opts", [{}, {"schedule": 1}, {"fused": 1}, {"share": 2, "schedule": 2, "fused": 2, "extensions": 3}])
+def test_samples_of_undivided_prompts(d, hq, hkv, length, samples, opts):
+    """n samples of a prompt at the first step: every request has one partial result, and the row tiles of a
+    prompt are packed.  The one-call form equals the two phases, bit for bit."""
+    C = _C()
+    prompts = 32
+    f = Forest(np.full(prompts, -1), np.full(prompts, length), np.repeat(np.arange(prompts), samples))
+    w = make_workload(f"samples-{d}-{hq}-{length}", f, HeadConfig(hq, hkv, d, DTYPE_BF16), seed=900 + d, poison=True)
+    got, _ = check(w, **opts)
+    wd = w.to("cuda:0")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", **opts)
+    two = torch.empty_like(wd.q)
+    pa.partial_attention(wd.q, wd.k_pool, wd.v_pool)
+    pa.partial_reduction(two)
+    one = pa.decode(wd.q, wd.k_pool, wd.v_pool)
+    torch.cuda.synchronize()
+    pa.close()
+    assert np.array_equal(two.double().cpu().numpy(), got) and torch.equal(one.view(torch.int16), two.view(torch.int16))
+
+
 @pytest.mark.parametrize("max_rows", [8, 16, 32, 48, 64, 100, 128, 200, 256])
 def test_row_tiles(max_rows):
     """70 requests x group 4 = 280 rows under the root: stream and dense task shapes, row tiling."""

@@ -12,6 +12,7 @@ import pytest
 import paper_2505_17694_amd as C
 from oracle import planner as P
 from golden_tables import load_table2
+from plan_image import plan_image
 from workloads import (two_level_forest, three_level_forest, random_forest, unshared_forest,
                        concat_forests, degenerate_forest, full_kary_forest, draft_tree_forest, draft_masked_forest, Forest,
                        HeadConfig, build_paged_kv)
@@ -543,3 +544,21 @@ def test_which_plans_pack_row_tiles(d, tile, opts, packed):
     if head_dim != 128:
         assert max(t["n_req"] * 4 for t in view["tasks"]) <= tile
     pa.close()
+
+
+@pytest.mark.parametrize("d,hq,hkv,prompts,length,samples", [
+    (256, 16, 8, 32, 256, 16), (256, 16, 8, 32, 1024, 16), (256, 16, 8, 32, 4000, 32), (256, 32, 8, 16, 200, 16),
+    (256, 8, 2, 1, 4096, 64), (64, 16, 8, 32, 1024, 32), (64, 32, 8, 64, 300, 16)])
+@pytest.mark.parametrize("opts", [{}, {"schedule": 1}, {"fused": 1}, {"share": 2, "schedule": 2, "fused": 2, "extensions": 3},
+                                  {"num_slots": 2, "split_align": 4096}])
+def test_packed_plans_are_reduced(d, hq, hkv, prompts, length, samples, opts):
+    """Many requests end at each undivided prompt: one partial result per request, yet sibling row tiles packed
+    into tasks of more than 16 rows, which write partial rows only.  Such a plan is not one of finished rows."""
+    f = Forest(np.full(prompts, -1), np.full(prompts, length), np.repeat(np.arange(prompts), samples))
+    im = plan_image(f, HeadConfig(hq, hkv, d), **opts)
+    assert not (im["packs"] and im["single_parts"])
+    group = hq // hkv
+    if im["single_parts"]:
+        assert max(im["slot_recs"]["n_req"]) * group <= 16
+    if d == 256 and opts in ({}, {"schedule": 1}, {"fused": 1}) and prompts == 32:
+        assert im["packs"]                          # the case does pack

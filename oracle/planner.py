@@ -346,3 +346,103 @@ def plan_best(parent, node_len, req_node, group: int, align: int, max_rows: int,
         if best is None or p["makespan"] < best["makespan"]:
             best = p
     return best
+
+
+# ---- 64 and 256 channels: sibling row tiles that run as one task -----------------------------------------
+#
+# A choice of the library, not of the paper: how the plan's tasks are grouped for its kernels.  `plan_out` is
+# a plan as `plan` returns it (or the library exports it); nothing in it changes.
+
+
+def pack_max_rows(head_dim: int) -> int:
+    return {64: 256, 256: 128}[head_dim]
+
+
+def device_cost(table: Dict, head_dim: int, rows: int, n: int, packed: bool) -> int:
+    """Cost of `rows` rows on `n` tokens as the library's kernels run them, from the table's entry for 16 rows:
+    that of a slice `extra` tokens longer, times a percentage (64 channels: half, one workgroup per CU)."""
+    if head_dim == 64:
+        extra = 0 if rows <= 16 else 384 if rows <= 32 else 512
+        percent = 108 if rows > 128 else 68 if rows > 64 else 50 if packed else 100
+    else:
+        extra = 0 if rows <= 16 else 200 if rows <= 64 else 400
+        percent = 100 if rows <= 16 else 95 if rows <= 64 else 113
+    return max(1, c_est(table, min(rows, 16), n + extra) * percent // 100)
+
+
+def pack_tiles(plan_out: Dict, table: Dict, head_dim: int, group: int, width: int, masked_nodes=()) -> List[Dict]:
+    """Groups of equal row tiles of one node (only the last may be smaller) of at most `width` rows, one device
+    task per KV slice; width 0: every tile on its own."""
+    first, out, run = 0, [], []
+    items, tasks = plan_out["items"], plan_out["tasks"]
+    firsts = []
+    for it in items:
+        firsts.append(first)
+        first += it["b"]
+
+    def emit():
+        a = items[run[0]]
+        rows = sum(items[j]["rows"] for j in run)
+        for s in range(a["b"]):
+            t = tasks[firsts[run[0]] + s]
+            out.append({"first": firsts[run[0]] + s, "step": a["b"], "tiles": len(run), "rows": rows,
+                        "cost": device_cost(table, head_dim, rows, t["kv_len"], width > 0)})
+
+    for j, it in enumerate(items):
+        if run:
+            a, prev = items[run[0]], items[run[-1]]
+            fits = (it["node"] == a["node"] and it["b"] == a["b"] and it["node"] not in masked_nodes
+                    and prev["rows"] == a["rows"] and it["rows"] <= a["rows"]
+                    and sum(items[i]["rows"] for i in run) + it["rows"] <= width
+                    and a["b"] * (a["rows"] - it["rows"]) <= 32767)
+            if not fits:
+                emit()
+                run = []
+        run.append(j)
+    if run:
+        emit()
+    return out
+
+
+def packs(plan_out: Dict, table: Dict, head_dim: int, group: int, num_kv_heads: int, max_rows: int = 0,
+          masked_nodes=(), share: bool = True) -> Dict:
+    """The device tasks a plan of 64 or 256 channels runs: {"packs": [] or the packs, "slots": lists of pack
+    indices, "plain": estimate of the plan without packs, "span": of the packs, None without}."""
+    m = len(plan_out["slot_off"]) - 1
+    masked_nodes = set(int(n) for n in masked_nodes)
+    tile = max_task_rows(head_dim)
+    limit = min(max_rows if max_rows > 0 else 256, pack_max_rows(head_dim))
+    plain = pack_tiles(plan_out, table, head_dim, group, 0, masked_nodes)
+    one_per_cu = min(m, max(1, 256 // num_kv_heads))
+    costs = [d["cost"] for d in plain]
+
+    def span_of(dev, slots):
+        return lpt([(d["cost"], i, 0) for i, d in enumerate(dev)], slots)
+
+    if head_dim == 64:      # two workgroups share a CU; a lone one takes about 60 % of the time
+        estimate = max(sum(costs) // m, max(costs, default=0) * 6 // 10)
+    else:                   # one workgroup per CU: the slots run in rounds
+        estimate = span_of(plain, m)[0] * _ceil_div(min(m, len(plain)), one_per_cu)
+    out = {"packs": [], "slots": [], "plain": estimate, "span": None}
+    if not share or limit < 2 * tile:
+        return out
+    width = 2 * tile
+    while width <= limit:
+        trial = pack_tiles(plan_out, table, head_dim, group, width, masked_nodes)
+        if len(trial) < len(plain):
+            span, _, lists = span_of(trial, one_per_cu)
+            if out["span"] is None or span < out["span"]:
+                out.update(packs=trial, slots=lists, span=span)
+        width *= 2
+    # packs have to be shorter by a margin: with 64 channels a quarter, and more where all slices are short, with
+    # the share of the tokens (beyond a quarter of them) read by tasks of no more rows than a tile
+    lens = [(d["rows"], plan_out["tasks"][d["first"]]["kv_len"]) for d in out["packs"]]
+    margin = 100
+    if head_dim == 64 and lens:
+        margin = 125
+        if max(n for _, n in lens) < 2560:
+            lone = 100 * sum(n for rows, n in lens if rows <= tile) // sum(n for _, n in lens)
+            margin += max(0, 60 * (lone - 25) // 100)
+    if lens and out["span"] * margin // 100 >= estimate:
+        out.update(packs=[], slots=[], span=None)
+    return out

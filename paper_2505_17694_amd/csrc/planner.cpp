@@ -193,8 +193,8 @@ std::vector<DeviceTask> pack_tiles(const PlanData &p, int32_t width)
 // With 64 and 256 channels sibling row tiles are packed where that shortens the schedule: packs of up to 64,
 // 128 (and 32 with 256 channels, 256 with 64) rows are dealt longest first, like the plan's own tasks, onto
 // one workgroup per CU, and the shortest of these schedules runs if it is shorter than the plan without packs
-// (ties: the narrower packs).  Packs read a slice once instead of once per tile, but fewer tasks may leave
-// workgroups idle.  `max_rows`: the caller's limit on the rows of a task; flat plans share nothing.
+// by a margin (ties: the narrower packs).  Packs read a slice once instead of once per tile, but fewer tasks
+// may leave workgroups idle.  `max_rows`: the caller's limit on the rows of a task; flat plans share nothing.
 void choose_packs(PlanData &p, int32_t max_rows)
 {
     p.packs.clear();
@@ -212,27 +212,45 @@ void choose_packs(PlanData &p, int32_t max_rows)
         return s;
     };
     // The plan as it is: two workgroups share a CU with 64 channels (a lone one takes about 60 % of the time of
-    // one that shares), and run one after the other with 256.  Unpacked siblings that run side by side find
-    // their slice in L2, which the estimates of 64 channels do not know: over 16 drawn forests a schedule with
-    // packs took 1.25 times as long against its estimate as the plan without them, and packs at less than that
-    // margin lost up to 17 %.
-    const int64_t margin = p.head.head_dim == 64 ? 125 : 100;
-    int64_t sum = 0, longest = 0;
+    // one that shares), and run one after the other with 256.
+    int64_t sum = 0, longest = 0, plain_span;
     for (const DeviceTask &d : plain) {
         sum += d.cost;
         longest = std::max(longest, d.cost);
     }
-    int64_t best_span;
-    if (p.head.head_dim == 64) best_span = std::max(sum / p.num_slots, longest * 6 / 10);
-    else best_span = deal(plain, p.num_slots, false).makespan * ceil_div(std::min<int64_t>(p.num_slots, int64_t(plain.size())), one_per_cu);
+    if (p.head.head_dim == 64) plain_span = std::max(sum / p.num_slots, longest * 6 / 10);
+    else plain_span = deal(plain, p.num_slots, false).makespan * ceil_div(std::min<int64_t>(p.num_slots, int64_t(plain.size())), one_per_cu);
+    int64_t best_span = 0;
     for (int32_t width = 2 * max_task_rows(p.head.head_dim); width <= max_rows; width *= 2) {
         trial = pack_tiles(p, width);
         const int64_t span = deal(trial, one_per_cu, false).makespan;
-        if (trial.size() < plain.size() && (p.packs.empty() ? span * margin / 100 : span) < best_span) {
+        if (trial.size() < plain.size() && (p.packs.empty() || span < best_span)) {
             best_span = span;
             p.packs = std::move(trial);
         }
     }
+    // The margin, in percent of the packs' span.  What the estimates of 64 channels do not know: unpacked siblings
+    // that run side by side find their slice in L2; and tasks that hold no more rows than one tile, which packing
+    // spares nothing, run alone on a CU that two workgroups shared.  Where all slices are short, their starts
+    // and ends are then no longer hidden behind the other workgroup, so the margin grows with the share of the
+    // tokens that such tasks read.  Measured on 800 drawn forests with siblings that a margin of 125 alone packed
+    // (1 to 16 KV heads, both types and layouts), time without packs over time with, geometric mean: 1.087 if
+    // all pack, 214 of them losing more than 2 % and 106 more than 10 %; 1.102 by this rule, 94 and 40.  600 of
+    // 256 channels, where any gain counts: 1.208, 34 losing more than 2 %, and none of such rules does better.
+    int64_t margin = 100;
+    if (p.head.head_dim == 64) {
+        int64_t tokens = 0, lone_tokens = 0;
+        int32_t longest_slice = 0;
+        for (const DeviceTask &d : p.packs) {
+            const int32_t len = p.tasks[d.first].kv_len;
+            tokens += len;
+            if (d.rows <= max_task_rows(64)) lone_tokens += len;
+            longest_slice = std::max(longest_slice, len);
+        }
+        margin = 125;
+        if (longest_slice < 2560) margin += std::max<int64_t>(0, 60 * (100 * lone_tokens / std::max<int64_t>(1, tokens) - 25) / 100);
+    }
+    if (best_span * margin / 100 >= plain_span) p.packs.clear();
     if (p.packs.empty()) return;
     const Schedule s = deal(p.packs, one_per_cu, true);
     p.pack_slots.off.assign(1, 0);

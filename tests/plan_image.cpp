@@ -29,6 +29,19 @@ void image_layout(int64_t *v)
     std::memcpy(v, x, sizeof x);
 }
 
+// per pack: first, step, tiles, rows, cost; then, per slot of the packs, its end in the list of pack indices
+void image_packs(int64_t *packs, int32_t *slot_off, int32_t *slot_packs)
+{
+    for (const codec::DeviceTask &d : plan.packs) {
+        const int64_t x[] = {d.first, d.step, d.tiles, d.rows, d.cost};
+        std::memcpy(packs, x, sizeof x);
+        packs += 5;
+    }
+    if (plan.packs.empty()) return;
+    std::memcpy(slot_off, plan.pack_slots.off.data(), plan.pack_slots.off.size() * 4);
+    std::memcpy(slot_packs, plan.pack_slots.tasks.data(), plan.pack_slots.tasks.size() * 4);
+}
+
 const unsigned char *image_blob() { return plan.blob.data(); }
 int64_t image_bytes() { return int64_t(plan.blob.size()); }
 

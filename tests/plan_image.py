@@ -34,7 +34,7 @@ def _probe():
 
 def plan_image(f, head, num_slots=0, split_align=0, max_rows=0, share=1, fixed_slices=0, schedule=0, fused=0,
                extensions=0, refreshed_len=None, paged=None):
-    """The layout words and the task records of the plan, by slot and by queue entry."""
+    """The layout words, the packs and the task records of the plan, by slot and by queue entry."""
     lib = _probe()
     paged = paged if paged is not None else build_paged_kv(f, head, 3)
     a = {k: np.ascontiguousarray(v, np.int32) for k, v in (
@@ -55,6 +55,11 @@ def plan_image(f, head, num_slots=0, split_align=0, max_rows=0, share=1, fixed_s
     v = (ctypes.c_int64 * len(LAYOUT))()
     lib.image_layout(v)
     out = dict(zip(LAYOUT, list(v)))
+    n = out["packs"]
+    packs, slot_off, slot_packs = np.zeros((n, 5), np.int64), np.zeros(out["num_slots"] + 1, np.int32), np.zeros(n, np.int32)
+    lib.image_packs(packs.ctypes.data_as(ctypes.c_void_p), B._ptr(slot_off), slot_packs.ctypes.data_as(ctypes.c_void_p))
+    out["packs"] = [dict(zip(("first", "step", "tiles", "rows", "cost"), p)) for p in packs.tolist()]
+    out["pack_slots"] = [slot_packs[a:b].tolist() for a, b in zip(slot_off, slot_off[1:])] if n else []
     blob = np.ctypeslib.as_array(ctypes.cast(lib.image_blob(), ctypes.POINTER(ctypes.c_uint8)), (lib.image_bytes(),)).copy()
 
     def ints(at, n):

@@ -145,8 +145,10 @@ typedef struct {
                                The queue keeps two counters per KV head in the plan's device metadata:
                                one launch of a plan at a time; 2 = the library chooses: the queue if it
                                has at least six entries per slot (measured on irregular forests: with
-                               that many the queue is 3-6 % faster, with few it changes nothing), else
-                               static.  The plan view reports the schedule in use (0 or 1)           */
+                               that many the queue is 3-6 % faster, with few it changes nothing), or
+                               five where sibling row tiles run as one task (see head_dim; entries and
+                               slots as they run, which the view does not show), else static.  The
+                               plan view reports the schedule in use (0 or 1)                        */
     int32_t fused;          /* 0 = Alg. 4 in two launches (partial attention, then reduction); 1 = one
                                launch: the workgroup whose task completes a request's set of partial
                                results (the last to arrive, counted per request and KV head in the

@@ -302,8 +302,8 @@ void build_device_image(PlanData &p)
     L.req_part_off = place(p.req_part_off.size() * 4);
     L.req_part = place(p.req_part.size() * 4);
     L.req_inline = place(size_t(p.num_requests) * (kInlineParts + 1) * 4);
-    if (p.schedule == 2)
-        p.schedule = int64_t(p.queue_off.size()) - 1 >= int64_t(kAutoQueueEntriesPerSlot) * p.num_slots ? 1 : 0;
+    if (p.schedule == 2)        // by the entries and slots that run
+        p.schedule = L.num_entries >= int64_t(packed ? kAutoQueueEntriesPerSlotPacked : kAutoQueueEntriesPerSlot) * L.num_slots ? 1 : 0;
     L.queue_off = place(queue.off.size() * 4);
     L.queue_recs = place(queue.tasks.size() * sizeof(DevTask));
     L.counters = place(size_t(p.head.num_kv_heads) * 2 * 4);               // zero: nothing taken, nobody done

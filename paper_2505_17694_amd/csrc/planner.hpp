@@ -31,6 +31,9 @@ constexpr int32_t kSoloMaxLen = 2048;
 constexpr int32_t kQueueBundle = 4;
 // schedule = 2 takes the run-time queue from this many entries per slot on.
 constexpr int32_t kAutoQueueEntriesPerSlot = 6;
+// ... of packed row tiles.  Static time over queue time of 150 drawn plans with packs, geometric mean by entries
+// per slot: 64 channels 1.05 at 3.5 .. 4.5, 1.15 at 4.5 .. 5.5, 1.08 beyond; 256 channels 1.00, 1.01 and 1.05.
+constexpr int32_t kAutoQueueEntriesPerSlotPacked = 5;
 // fused = 2 reduces inside the attention launch when the estimated makespan (ns) is below this: where a
 // second launch (about 5 us with the gap in front of it) is a large part of the step.
 constexpr int64_t kAutoFusedMakespanNs = 40000;

@@ -635,3 +635,18 @@ def test_short_slices_of_few_rows_stay_unpacked(seed):
     lens = [(p["rows"], view["tasks"][p["first"]]["kv_len"]) for p in dev]
     assert len(dev) < len(view["tasks"]) and sum(n for r, n in lens if r <= 32) > 0.6 * sum(n for _, n in lens)
     assert im["packs"] == []
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(64, 32, 8), (64, 64, 8), (256, 16, 8), (256, 32, 8)])
+def test_automatic_schedule_counts_what_runs(d, hq, hkv):
+    """schedule = 2 with packed row tiles: from five entries per slot on, counted as the kernels have them."""
+    picked = set()
+    for leaves in (60, 150, 300, 600):
+        f = random_forest(leaves, 5, 2.0, 500, 1.0, 16, 8000, seed=leaves)
+        view, im, _ = _plan_of(f, HeadConfig(hq, hkv, d), schedule=2, extensions=3)
+        assert im["schedule"] == view["schedule"] == int(im["num_entries"] >= (5 if im["packs"] else 6) * im["num_slots"])
+        if im["packs"]:
+            own = len(view["queue_off"]) - 1 >= 6 * view["num_slots"]
+            picked.add((im["schedule"], own))
+    if d == 256:
+        assert (1, False) in picked                     # the plan's own queue, unpacked, is too short

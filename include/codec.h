@@ -156,11 +156,15 @@ typedef struct {
                                of the parallel reduction of Sec. 4.3, for trees whose step time is
                                of the order of a kernel launch); 2 = the library chooses: one launch
                                if the estimated makespan is below 40000 cost units (40 us with the
-                               built-in tables) and the batch has at most 64 query rows per KV head
-                               (one workgroup may be the last for all of them).  Only codec_decode_attention
+                               built-in tables), the batch has at most 64 query rows per KV head
+                               (one workgroup may be the last for all of them) and no sibling row tiles
+                               run as one task (see head_dim).  Only codec_decode_attention
                                (and its static variant) fuse; the two phase calls stay separate.  As
                                with the run-time queue, launches of one plan must not overlap.  The
-                               plan view reports 0 or 1                                             */
+                               plan view reports 0 or 1.  Whatever is asked for, a plan in which every
+                               request has one partial result, in a task of at most 16 rows, takes one
+                               launch, which writes finished rows and keeps no count (the view's value
+                               is then without effect)                                              */
     int32_t extensions;     /* 0 = the solver of Sec. 5.1 as printed: slice counts bounded by
                                ceil(C_est / cost_l) (Eq. 5), one node-by-node pass of the grid search.
                                Bits add this library's own extensions of it (CODEC_PLAN_EXT_*)       */

@@ -311,9 +311,12 @@ void build_device_image(PlanData &p)
     L.nodeq_mask = place(masks ? p.node_q.size() * 4 : 0);
     L.mask_words = place(masks ? p.req_mask.size() * 4 : 0);
     // one workgroup may end up last for every request: more query rows than a workgroup reduces in a
-    // few rounds make the single launch slower than two (cfg2, 256 rows per KV head: 89 against 26 us)
+    // few rounds make the single launch slower than two (cfg2, 256 rows per KV head: 89 against 26 us).  A pack
+    // delivers to all its requests at once, so that with packs one workgroup does the reductions of many even
+    // where there are few: of 120 drawn plans with packs and at most 64 rows none was faster in one launch
+    // (two to sixty percent slower; 8 requests on a four-level binary tree, 32 / 8 heads of 256 channels: 29.0 against 46.4 us).
     if (p.fused == 2)
-        p.fused = p.makespan < kAutoFusedMakespanNs && int64_t(p.num_requests) * p.group <= kAutoFusedMaxRows ? 1 : 0;
+        p.fused = !packed && p.makespan < kAutoFusedMakespanNs && int64_t(p.num_requests) * p.group <= kAutoFusedMaxRows ? 1 : 0;
     L.total = std::max<size_t>(off, 256);
     p.blob.assign(L.total, 0);
     // Streaming hint (kernels.hip): a task reads its slice with it when no other task reads that slice

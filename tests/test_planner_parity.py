@@ -650,3 +650,16 @@ def test_automatic_schedule_counts_what_runs(d, hq, hkv):
             picked.add((im["schedule"], own))
     if d == 256:
         assert (1, False) in picked                     # the plan's own queue, unpacked, is too short
+
+
+@pytest.mark.parametrize("d,hq,hkv,f", [
+    (256, 32, 8, lambda: full_kary_forest(2, 4, lambda lvl: 700)), (256, 16, 8, lambda: two_level_forest(3000, [40] * 20)),
+    (256, 16, 8, lambda: three_level_forest(600, [900] * 2, 12, [60] * 24)), (64, 64, 8, lambda: two_level_forest(3000, [40] * 8))])
+def test_packed_plans_choose_two_launches(d, hq, hkv, f):
+    """fused = 2 on plans with packed row tiles: two launches, however few rows and however short; fused = 1 stays."""
+    f, head = f(), HeadConfig(hq, hkv, d)
+    _, im, _ = _plan_of(f, head, fused=2)
+    assert f.num_requests * (hq // hkv) <= 64 and im["makespan"] < 40000
+    assert im["fused"] == (0 if im["packs"] else 1)
+    assert im["packs"] or d == 64
+    assert _plan_of(f, head, fused=1)[1]["fused"] == 1

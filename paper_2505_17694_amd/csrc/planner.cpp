@@ -286,17 +286,25 @@ void build_device_image(PlanData &p)
     }
     // what the kernels run: the plan's tasks, its slots and its queue, or packed row tiles with their own
     const bool packed = !p.packs.empty();
-    const std::vector<DeviceTask> dev = packed ? p.packs : pack_tiles(p, 0);
-    const TaskLists slots = packed ? p.pack_slots : TaskLists{p.slot_off, p.slot_tasks};
-    L.num_slots = int32_t(slots.off.size()) - 1;
+    std::vector<DeviceTask> own;        // of the plan's tasks only what the records need
+    if (!packed) {
+        own.resize(p.tasks.size());
+        for (size_t i = 0; i < own.size(); ++i) own[i] = {int32_t(i), 1, 1, p.tasks[i].n_req * p.group, 0};
+    }
+    const std::vector<DeviceTask> &dev = packed ? p.packs : own;
+    const std::vector<int32_t> &slot_off = packed ? p.pack_slots.off : p.slot_off;
+    const std::vector<int32_t> &slot_tasks = packed ? p.pack_slots.tasks : p.slot_tasks;
+    L.num_slots = int32_t(slot_off.size()) - 1;
     auto is_short = [&](int32_t i) { return dev[i].rows <= kSoloMaxRows && p.tasks[dev[i].first].kv_len <= kSoloMaxLen; };
-    TaskLists queue{p.queue_off, p.queue_tasks};
-    if (packed) queue = queue_entries(int32_t(dev.size()), L.num_slots, [&](int32_t i) { return dev[i].cost; }, is_short);
-    L.num_entries = int32_t(queue.off.size()) - 1;
+    TaskLists pack_queue{{0}, {}};      // stays empty under the static schedule
+    if (packed && p.schedule != 0) pack_queue = queue_entries(int32_t(dev.size()), L.num_slots, [&](int32_t i) { return dev[i].cost; }, is_short);
+    const std::vector<int32_t> &queue_off = packed ? pack_queue.off : p.queue_off;
+    const std::vector<int32_t> &queue_tasks = packed ? pack_queue.tasks : p.queue_tasks;
+    L.num_entries = int32_t(queue_off.size()) - 1;
     size_t off = 0;
     auto place = [&](size_t bytes) { size_t at = off; off = align_up(off + bytes, 256); return at; };
-    L.slot_recs = place(slots.tasks.size() * sizeof(DevTask));
-    L.slot_off = place(slots.off.size() * 4);
+    L.slot_recs = place(slot_tasks.size() * sizeof(DevTask));
+    L.slot_off = place(slot_off.size() * 4);
     L.node_q = place(p.node_q.size() * 4);
     L.page_ids = place(p.page_ids.size() * 4);
     L.req_part_off = place(p.req_part_off.size() * 4);
@@ -304,8 +312,8 @@ void build_device_image(PlanData &p)
     L.req_inline = place(size_t(p.num_requests) * (kInlineParts + 1) * 4);
     if (p.schedule == 2)        // by the entries and slots that run
         p.schedule = L.num_entries >= int64_t(packed ? kAutoQueueEntriesPerSlotPacked : kAutoQueueEntriesPerSlot) * L.num_slots ? 1 : 0;
-    L.queue_off = place(queue.off.size() * 4);
-    L.queue_recs = place(queue.tasks.size() * sizeof(DevTask));
+    L.queue_off = place(queue_off.size() * 4);
+    L.queue_recs = place(queue_tasks.size() * sizeof(DevTask));
     L.counters = place(size_t(p.head.num_kv_heads) * 2 * 4);               // zero: nothing taken, nobody done
     L.arrive = place(size_t(p.head.num_kv_heads) * size_t(p.num_requests) * 4);   // zero: nothing arrived
     L.nodeq_mask = place(masks ? p.node_q.size() * 4 : 0);
@@ -365,22 +373,22 @@ void build_device_image(PlanData &p)
     // once, at the end of the launch, where the short tasks also even out what the long ones left.
     DevTask *by_slot = reinterpret_cast<DevTask *>(p.blob.data() + L.slot_recs);
     for (int32_t sl = 0; sl < L.num_slots; ++sl) {
-        std::vector<int32_t> order(slots.tasks.begin() + slots.off[sl], slots.tasks.begin() + slots.off[sl + 1]);
+        std::vector<int32_t> order(slot_tasks.begin() + slot_off[sl], slot_tasks.begin() + slot_off[sl + 1]);
         std::stable_partition(order.begin(), order.end(), [&](int32_t i) { return !is_short(i); });
         int32_t run = 0;
         for (int32_t k = int32_t(order.size()) - 1; k >= 0; --k) {       // runs of single-wave tasks, back to front
-            DevTask &r = by_slot[slots.off[sl] + k];
+            DevTask &r = by_slot[slot_off[sl] + k];
             r = record(order[k]);
             run = is_short(order[k]) ? run + 1 : 0;
             r.solo_run = run;
         }
     }
     DevTask *by_entry = reinterpret_cast<DevTask *>(p.blob.data() + L.queue_recs);
-    for (size_t i = 0; i < queue.tasks.size(); ++i) by_entry[i] = record(queue.tasks[i]);
+    for (size_t i = 0; i < queue_tasks.size(); ++i) by_entry[i] = record(queue_tasks[i]);
     auto put = [&](size_t at, const std::vector<int32_t> &v) {
         if (!v.empty()) std::memcpy(p.blob.data() + at, v.data(), v.size() * 4);
     };
-    put(L.slot_off, slots.off);
+    put(L.slot_off, slot_off);
     put(L.node_q, p.node_q);
     put(L.page_ids, p.page_ids);
     put(L.req_part_off, p.req_part_off);
@@ -393,7 +401,7 @@ void build_device_image(PlanData &p)
             for (int32_t j = 0; j < kInlineParts; ++j) line[1 + j] = j < cnt ? p.req_part[e0 + j] : 0;
         }
     }
-    put(L.queue_off, queue.off);
+    put(L.queue_off, queue_off);
     if (masks) {
         put(L.nodeq_mask, nodeq_mask);
         if (!p.req_mask.empty()) std::memcpy(p.blob.data() + L.mask_words, p.req_mask.data(), p.req_mask.size() * 4);

@@ -1752,13 +1752,19 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
 // (they are then visible device-wide), and only then is the delivery counted; the workgroup that sees the
 // last count reads the rows after that.  (Fences at device scope instead, with plain accesses, cost a write-back and an
 // invalidation of the whole L2 per task: measured, several times the launch they were to save.)
-__device__ __forceinline__ bool deliver(const PacParams &P, const DevTask &t, int head, int i, int &req)
+//
+// expect(): request i of the task and the length of its list, read ahead of the wait for the stores so that the
+// two reads travel beside them.  deliver(): counts; true for the delivery that completes the list.
+__device__ __forceinline__ int2 expect(const PacParams &P, const DevTask &t, int i)
 {
-    req = t.single_req >= 0 ? t.single_req : P.node_q[t.q_off + i];
-    const int want = P.merge.req_inline[int64_t(req) * (kInlineParts + 1)];
-    int32_t *c = P.arrive + int64_t(head) * P.merge.num_requests + req;
+    const int req = t.single_req >= 0 ? t.single_req : P.node_q[t.q_off + i];
+    return int2{req, P.merge.req_inline[int64_t(req) * (kInlineParts + 1)]};
+}
+__device__ __forceinline__ bool deliver(const PacParams &P, int head, int2 expected)
+{
+    int32_t *c = P.arrive + int64_t(head) * P.merge.num_requests + expected.x;
     const int old = __hip_atomic_fetch_add(c, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1 != want) return false;
+    if (old + 1 != expected.y) return false;
     __hip_atomic_store(c, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // nobody else counts on it in this launch
     return true;
 }
@@ -1774,14 +1780,14 @@ template <int DT, int D>
 __device__ __forceinline__ void task_delivered_by_workgroup(const PacParams &P, const DevTask &t, int head, char *lds_raw, int waves)
 {
     int *count = reinterpret_cast<int *>(lds_raw), *ready = count + 1;
+    const bool mine = int(threadIdx.x) < t.n_req;
+    int2 expected{0, 0};
+    if (mine) expected = expect(P, t, threadIdx.x);
     stores_acknowledged();              // the rows of a task may come from every wave (dense and tile path)
     __syncthreads();                    // ... and all have waited when a thread counts; LDS is free
     if (threadIdx.x == 0) *count = 0;
     __syncthreads();
-    if (int(threadIdx.x) < t.n_req) {
-        int req;
-        if (deliver(P, t, head, threadIdx.x, req)) ready[atomicAdd(count, 1)] = req;
-    }
+    if (mine && deliver(P, head, expected)) ready[atomicAdd(count, 1)] = expected.x;
     __syncthreads();
     const int n = *count * P.group;
     if (n > 0) {
@@ -1801,9 +1807,10 @@ template <int DT, int D>
 __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const DevTask &t, int head)
 {
     const int lane = threadIdx.x & 63;
+    int2 expected{0, 0};
+    if (lane < t.n_req) expected = expect(P, t, lane);
     stores_acknowledged();
-    int req = 0;
-    const bool last = lane < t.n_req && deliver(P, t, head, lane, req);
+    const bool last = lane < t.n_req && deliver(P, head, expected);
     unsigned long long ready = __ballot(last);
     if (ready == 0) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -1811,7 +1818,7 @@ __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const
     while (ready) {
         const int src = __builtin_ctzll(ready);
         ready &= ready - 1;
-        const int r = __shfl(req, src);
+        const int r = __shfl(expected.x, src);
 #pragma unroll 1
         for (int hj = 0; hj < P.group; ++hj) merge_one<DT, true, D>(P.merge, r, head * P.group + hj, lane);
     }

@@ -2,7 +2,7 @@
 import numpy as np
 import torch
 
-from workloads import bits_to_float64
+from workloads import bits_to_float64, concat_forests, two_level_forest
 
 
 def token_slot(w, node, t):
@@ -45,3 +45,21 @@ def set_token(w, node, t, kvh, k_row=None, v_row=None):
 
 def q_float64(w):
     return w.q.to(torch.float64).numpy()
+
+
+# Packed row tiles of divided nodes: (channels, query heads, KV heads, requests per node, most rows of a pack with
+# slices and a last tile smaller than the others or not).  64 channels: four, two and one waves per row group;
+# 256 channels: one and two row tiles per wave.
+DIVIDED_PACKS = [(64, 8, 2, 16, 64, False), (64, 8, 2, 32, 128, False), (64, 8, 2, 64, 256, False), (64, 4, 4, 41, 41, True),
+                 (64, 12, 4, 43, 120, False), (64, 4, 4, 150, 150, True), (256, 8, 2, 16, 64, False),
+                 (256, 8, 2, 32, 128, False), (256, 12, 4, 27, 81, True)]
+DIVIDED_PACKS_OPTS = [{"num_slots": 2, "split_align": 32, "fixed_slices": 3},
+                      {"num_slots": 2, "schedule": 1, "split_align": 64, "fixed_slices": 4},
+                      {"num_slots": 2, "fused": 1, "fixed_slices": 2}]
+
+
+def divided_packs_forest(requests):
+    f = two_level_forest(33, [43] * requests)
+    for n in (97, 513, 1000):
+        f = concat_forests(f, two_level_forest(n, [5 + n % 40] * requests))
+    return f

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+from helpers import DIVIDED_PACKS, DIVIDED_PACKS_OPTS, divided_packs_forest
 from oracle import attention as A
 from workloads import (HeadConfig, Forest, make_workload, make_small_config, make_config,
                        two_level_forest, three_level_forest, unshared_forest, random_forest,
@@ -150,8 +151,8 @@ def _image_bytes_without_packs(view, paged, head):
                                   {"num_slots": 2, "schedule": 1, "split_align": 64}, {"num_slots": 2, "fused": 1}])
 def test_packed_row_tiles(d, hq, hkv, requests, packed, opts):
     """Sibling row tiles of 64 and 256 channels run as one task: two tiles, full packs of every width (one, two
-    and four waves per row group), packs with a smaller last tile, several packs per node; slices of one block
-    up to whole nodes, ragged ones, lengths around the depth of the block ring; beside single-wave tasks, and
+    and four waves per row group), packs with a smaller last tile, several packs per node; undivided nodes of one
+    block and more, ragged ones, lengths around the depth of the block ring; beside single-wave tasks, and
     after the lengths have grown.  One tile per node: nothing to pack."""
     C = _C()
     lens = [1, 31, 33, 97, 127, 129, 161, 513, 700, 1025]
@@ -209,6 +210,17 @@ def test_requests_with_a_single_partial(d, hq, hkv, dtype, opts):
     torch.cuda.synchronize()
     pa.close()
     assert torch.equal(one.view(torch.int16), two.view(torch.int16))
+
+
+@pytest.mark.parametrize("d,hq,hkv,requests,widest,uneven", DIVIDED_PACKS)
+@pytest.mark.parametrize("opts", DIVIDED_PACKS_OPTS)
+@pytest.mark.parametrize("dtype", [DTYPE_BF16, DTYPE_FP16])
+def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts, dtype):
+    """Packed row tiles on several slices of a node, both types, every width of a pack, even and uneven last tiles
+    (what these plans pack is asserted on the host, in the planner tests)."""
+    w = make_workload(f"divided-{d}-{hq}-{requests}", divided_packs_forest(requests), HeadConfig(hq, hkv, d, dtype),
+                      seed=1000 + d + requests, poison=True, layout="thd" if requests % 2 else "htd")
+    check(w, **opts)
 
 
 @pytest.mark.parametrize("d,hq,hkv,length,samples", [(256, 16, 8, 256, 16), (256, 16, 8, 1024, 32), (256, 32, 8, 200, 16),

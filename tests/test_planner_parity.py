@@ -12,6 +12,7 @@ import pytest
 import paper_2505_17694_amd as C
 from oracle import planner as P
 from golden_tables import load_table2
+from helpers import DIVIDED_PACKS, DIVIDED_PACKS_OPTS, divided_packs_forest
 from plan_image import plan_image
 from workloads import (two_level_forest, three_level_forest, random_forest, unshared_forest,
                        concat_forests, degenerate_forest, full_kary_forest, draft_tree_forest, draft_masked_forest, Forest,
@@ -667,3 +668,15 @@ def test_packed_plans_choose_two_launches(d, hq, hkv, f):
     assert im["fused"] == (0 if im["packs"] else 1)
     assert im["packs"] or d == 64
     assert _plan_of(f, head, fused=1)[1]["fused"] == 1
+
+
+@pytest.mark.parametrize("d,hq,hkv,requests,widest,uneven", DIVIDED_PACKS)
+@pytest.mark.parametrize("opts", DIVIDED_PACKS_OPTS)
+def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts):
+    """The plans that the GPU parity test of the same name runs: packs of every width, on several slices of a node,
+    whose last tile, if it is smaller, has its partial rows in another place than equal tiles would."""
+    im = plan_image(divided_packs_forest(requests), HeadConfig(hq, hkv, d), **opts)
+    assert max(p["rows"] for p in im["packs"]) == widest and max(p["step"] for p in im["packs"] if p["tiles"] > 1) >= 2
+    records = im["slot_recs"]
+    shifts = records["flags"][(records["flags"] & 4) != 0] >> 16
+    assert (max(shifts) > 0) == uneven

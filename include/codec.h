@@ -211,8 +211,11 @@ typedef struct {
 /*
  * Read-only host view of a plan; pointers stay valid until codec_plan_destroy.
  * node_q lists, per node, the requests whose path contains it (ascending);
- * slot s runs tasks slot_tasks[slot_off[s] .. slot_off[s+1]) in that order (unless the
- * kernels run sibling row tiles together, see head_dim);
+ * slot s runs tasks slot_tasks[slot_off[s] .. slot_off[s+1]) in that order.  Where the
+ * kernels run sibling row tiles together (see head_dim), num_slots, the slots' lists, the
+ * queue and makespan describe the plan before that: what runs are the same tasks, several
+ * at a time, on slots and from a queue of their own.  Items, tasks, partial rows and the
+ * requests' lists hold either way;
  * request r merges the partials whose first rows are
  * req_part[req_part_off[r] .. req_part_off[r+1]) (root to leaf, slices in order).
  */

@@ -26,7 +26,7 @@
 //    LDS at the end.  Runs of short tasks are handed out one wave each instead.
 //  * "dense" (tasks of 17..256 rows, wide variant): 32 x 32 x 16 tiles; eight waves
 //    split the rows (32 each) and walk the slice together; blocks are copied HBM ->
-//    LDS asynchronously into a ring of 16 KB slots (five or six blocks in flight)
+//    LDS asynchronously into a ring of 16 KB slots (five blocks in flight, four with two-block intervals)
 //    and read by all waves, V through transposing LDS reads (ds_read_b64_tr_b16).
 //    Long slices under at most 128 rows put two waves on each row group, on
 //    alternate blocks.
@@ -707,7 +707,7 @@ __device__ __forceinline__ void run_stream(const PacParams &P, const DevTask &t,
 //
 // Blocks travel HBM -> LDS without passing through registers (global_load_lds_dwordx4: every lane
 // moves 16 bytes, a wave fills 1 KB of consecutive LDS).  A ring of kRing block slots (16 KB each:
-// 32 K rows then 32 V rows of 256 B) keeps five (six with two-block intervals) blocks in flight per
+// 32 K rows then 32 V rows of 256 B) keeps five (four with two-block intervals) blocks in flight per
 // workgroup.  Rows are stored unpadded; the 16-byte column index is XORed with a function of the row so
 // that the operand reads spread over all banks.  The swizzle is applied on the global side: the lane that fills LDS
 // column c of a row fetches column c ^ f(row).
@@ -1014,10 +1014,11 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     // Common to all roles.  All but S = STRIDE blocks of the ring are requested up front; interval j
     // (j = 0 .. nint-1) starts with a barrier behind which S blocks are requested into the slots of the
     // blocks of interval j-1.  Those were consumed before the barrier; the LDS reads issued last, of blocks
-    // that interval j uses, may still be under way: the barrier waits for no LDS read (one that did, with
-    // the slots of interval j's own blocks refilled, cost 1.1 % on a six-level binary tree of 32 .. 1024
-    // rows: 40.3 against 39.9 us, 1.3 % on 64 requests of 4 rows below a 4096-token root: 26.5 against
-    // 26.1 us, nothing on a 131072-token root under 512 rows, whose rate the clock sets).  The LDS
+    // that interval j uses, may still be under way: the barrier waits for no LDS read.  Against one that did,
+    // with the slots of interval j's own blocks refilled, which kept a block (two) more in flight: 32 layers of
+    // 64 requests of 4 rows below a 4096-token root 853 -> 835 us, a six-level binary tree of 32 .. 1024 rows
+    // 40.0 -> 39.2, three-level documents 161.4 -> 160.5, long slices under 64 and 128 rows 0.5-1.5 % faster
+    // (109.7 -> 108.7), nothing on a 131072-token root under 512 rows, whose rate the clock sets.  The LDS
     // reads of interval j reach up to block S*j + 3*S - 1, which must have landed at its barrier: each wave
     // issues 2 loads per block and loads complete in order, so a block has landed once at most 2 * (blocks
     // issued after it) loads are outstanding; near the end of the slice, where fewer blocks follow, the
@@ -1283,7 +1284,7 @@ __device__ void run_dense32(const PacParams &P, const DevTask &t, int head, char
 // for all of them instead of once per tile through the CU's memory pipeline, which is what bounds such
 // plans (a CU streams 24-27 GB/s from HBM whatever its waves do).  Measured, whole step, a tree of a
 // 2048-token root, 16 nodes of 8192 tokens and ragged leaves of 32 .. 512: 128 requests with 64 / 8 heads of
-// 64 channels 100.3 -> 76.7 us, 256 requests with 16 / 8 heads of 256 channels 369 -> 289 us.  A task of up to
+// 64 channels 100.6 -> 74.7 us, 256 requests with 16 / 8 heads of 256 channels 370 -> 290 us.  A task of up to
 // 64 rows streams at 5.2 (64 channels) and 6.0 TB/s (256) where its row tiles took 4.1 and 3.0; 128 rows
 // at 3.8 and 4.8 where they took 2.4 and 1.6 (4096 tokens, all CUs busy).
 //
@@ -1829,9 +1830,10 @@ __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const
 extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
 
 // FUSED: with the code of the single-launch mode (used if P.arrive).  The kernels without it are shorter and
-// need fewer registers, which shows where a step is a few dozen microseconds: 32 layers of document questions
-// 843 -> 833 us, a six-level tree with one KV head 39.9 -> 39.4 us, three-level documents 161.2 -> 160.5 us, a
-// lone request 15.1 -> 14.8 us.  Only the tile path of 256 channels was allocated worse without it (three-level
+// need fewer registers, which shows where a step is a few dozen microseconds (both builds in turn on one box,
+// whose runs differ by 0.1-0.7 %): 32 layers of document questions 842 -> 833 us, a six-level tree with one KV
+// head 39.7 -> 39.1, a lone request 15.1 -> 14.8, documents of 64 channels 75.8 -> 74.9, three-level documents
+// 161.5 -> 160.2; nothing on steps of 250 us and more.  Only the tile path of 256 channels was allocated worse without it (three-level
 // documents 289 -> 299 us), so its one kernel serves both modes (one_kernel).
 constexpr bool one_kernel(int form, int d) { return form == kFormWide && d == 256; }
 template <int DT, int FORM, int D, bool FUSED>

@@ -1830,7 +1830,7 @@ __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const
 extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
 
 // FUSED: with the code of the single-launch mode (used if P.arrive).  The kernels without it are shorter and
-// need fewer registers, which shows where a step is a few dozen microseconds (both builds in turn on one box,
+// need fewer registers, which shows where a step is a few dozen microseconds (both builds in turn on one card,
 // whose runs differ by 0.1-0.7 %): 32 layers of document questions 842 -> 833 us, a six-level tree with one KV
 // head 39.7 -> 39.1, a lone request 15.1 -> 14.8, documents of 64 channels 75.8 -> 74.9, three-level documents
 // 161.5 -> 160.2; nothing on steps of 250 us and more.  Only the tile path of 256 channels was allocated worse without it (three-level

@@ -146,20 +146,57 @@ __device__ __forceinline__ float2 ld8_device(const float *p)
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return __builtin_bit_cast(float2, v);
 }
-// 16 bytes of a partial row: plain (the row is read by a later launch) or device-coherent
-__device__ __forceinline__ void st16_partial(float *p, f32x4 v, bool coherent)
+// How the partial rows of a task are stored.
+//  kRowsPlain     read by a later launch; the lines stay in the L2 of the XCD, where the reduction finds them
+//  kRowsThrough   the same, written through at once (the `sc1` form): dense and tile tasks with K and V still to
+//                 read behind them
+//  kRowsCoherent  read by other workgroups of this launch (single-launch mode)
+// Lines that wait in L2 for their write-back are pushed out by the K and V that stream through it, a few at a
+// time, and HBM turns around between reads and writes for each: 2 KB stored for every 15 blocks of 16 KB
+// read take a stream of 256 workgroups from 6.74 to 5.82 TB/s, written through to 6.14; for every 31 blocks 6.36
+// and 6.56.  Rows written through are not in L2, though, when the reduction reads them: with all rows stored like
+// that a lone request goes 14.8 -> 16.6 us.  Stream tasks store 16 bytes of each of 16 lines per instruction, which
+// only L2 puts together: theirs stay plain (written through, two drawn plans with heads of 64 channels lost 4 and 6 %).
+enum RowStore { kRowsPlain, kRowsThrough, kRowsCoherent };
+// Rows behind a buffer descriptor (base the same for the wave, `bytes` long; stores behind its end are dropped):
+// the compiler has no other 16-byte store that is written through, and it keeps the distance that this target wants
+// between a store of this width and the next write to its data registers (inline assembly would not).
+typedef __amdgpu_buffer_rsrc_t Rows;
+__device__ __forceinline__ Rows rows_at(float *base, int bytes)
 {
-    if (coherent) {
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);   // word 3: 32-bit raw data
+}
+template <RowStore HOW>
+__device__ __forceinline__ void st16_rows(Rows rows, int offset, f32x4 v)
+{
+    static_assert(HOW != kRowsCoherent, "two 8-byte stores: st16_partial");
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, offset, 0, HOW == kRowsThrough ? 16 /* sc1 */ : 0);
+}
+// The same through a pointer: plain or coherent.
+template <RowStore HOW>
+__device__ __forceinline__ void st16_partial(float *p, f32x4 v)
+{
+    static_assert(HOW != kRowsThrough, "st16_rows");
+    if constexpr (HOW == kRowsCoherent) {
         st8_device(p, v[0], v[1]);
         st8_device(p + 2, v[2], v[3]);
     } else {
         *reinterpret_cast<f32x4 *>(p) = v;
     }
 }
-__device__ __forceinline__ void st8_partial(float *p, float a, float b, bool coherent)
+template <RowStore HOW>
+__device__ __forceinline__ void st8_partial(float *p, float a, float b)
 {
-    if (coherent) st8_device(p, a, b);
-    else          *reinterpret_cast<float2 *>(p) = float2{a, b};
+    if constexpr (HOW != kRowsPlain) st8_device(p, a, b);
+    else                             *reinterpret_cast<float2 *>(p) = float2{a, b};
+}
+// body(integral constant): one branch around all stores of a task, whose LDS reads then travel together
+template <class Body>
+__device__ __forceinline__ void with_row_store(RowStore how, Body body)
+{
+    if (how == kRowsCoherent)     body(std::integral_constant<RowStore, kRowsCoherent>{});
+    else if (how == kRowsThrough) body(std::integral_constant<RowStore, kRowsThrough>{});
+    else                          body(std::integral_constant<RowStore, kRowsPlain>{});
 }
 
 // The lane index as a value the optimiser cannot trace back to the thread id.  Each task path derives
@@ -477,14 +514,13 @@ __device__ __forceinline__ void gather_q(const PacParams &P, const DevTask &t, i
 // vector-memory instruction takes a place in the CU's queue of instructions in flight, and a short task
 // has few to spare.  Staged, the task's rows (they are neighbours in the partial array) go out 1 KB of
 // consecutive memory per instruction: two instructions for four rows of 128 channels.
-template <int D>
+template <RowStore HOW, int D>
 __device__ __forceinline__ void store_partial_staged(const PacParams &P, const DevTask &t, int head, int rows,
                                                      int lane, const RowState<1, D> &st, char *stage)
 {
     static_assert(D <= 128, "staging area is sized for up to 128 channels");
     constexpr int PITCH = solo_stage_pitch(D), ROW = D * 4;
     const int l16 = lane & 15, grp = lane >> 4;
-    const bool coherent = P.arrive != nullptr;
     char *put = stage + l16 * PITCH + grp * 128;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -495,7 +531,7 @@ __device__ __forceinline__ void store_partial_staged(const PacParams &P, const D
         *reinterpret_cast<f32x4 *>(put + e * 32 + 16) = hi;
     }
     const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base;
-    if (grp == 0 && l16 < rows) st8_partial(P.part_ml + (prow + l16) * 2, st.m[0], st.l[0], coherent);
+    if (grp == 0 && l16 < rows) st8_partial<HOW>(P.part_ml + (prow + l16) * 2, st.m[0], st.l[0]);
     __builtin_amdgcn_wave_barrier();                    // LDS serves a wave's accesses in order: no wait needed
     float *po = P.part_o + prow * D;
     const int bytes = rows * ROW;
@@ -505,14 +541,14 @@ __device__ __forceinline__ void store_partial_staged(const PacParams &P, const D
         const int off = i * 1024 + lane * 16;
         if (off < bytes) {
             const f32x4 x = *reinterpret_cast<const f32x4 *>(stage + (off / ROW) * PITCH + off % ROW);
-            st16_partial(po + off / 4, x, coherent);
+            st16_partial<HOW>(po + off / 4, x);
         }
     }
     __builtin_amdgcn_wave_barrier();                    // the area is read before the wave's next task writes it
 }
 
 // Write one wave's rows of the partial result: unnormalised output, (reference, sum) per row.
-template <int NT, int D>
+template <RowStore HOW, int NT, int D>
 __device__ __forceinline__ void store_partial(const PacParams &P, const DevTask &t, int head, int row0, int rows,
                                               int l16, int grp, const RowState<NT, D> &st)
 {
@@ -529,10 +565,10 @@ __device__ __forceinline__ void store_partial(const PacParams &P, const DevTask 
                     if (D < 128 && grp * 32 + e * 8 >= D) continue;     // channels the head does not have
                     const f32x4 lo = {st.o[nt][8 * u + 0][e], st.o[nt][8 * u + 1][e], st.o[nt][8 * u + 2][e], st.o[nt][8 * u + 3][e]};
                     const f32x4 hi = {st.o[nt][8 * u + 4][e], st.o[nt][8 * u + 5][e], st.o[nt][8 * u + 6][e], st.o[nt][8 * u + 7][e]};
-                    st16_partial(po + u * 128 + e * 8, lo, P.arrive != nullptr);
-                    st16_partial(po + u * 128 + e * 8 + 4, hi, P.arrive != nullptr);
+                    st16_partial<HOW>(po + u * 128 + e * 8, lo);
+                    st16_partial<HOW>(po + u * 128 + e * 8 + 4, hi);
                 }
-            if (grp == 0) st8_partial(P.part_ml + prow * 2, st.m[nt], st.l[nt], P.arrive != nullptr);
+            if (grp == 0) st8_partial<HOW>(P.part_ml + prow * 2, st.m[nt], st.l[nt]);
         }
     }
 }
@@ -588,7 +624,7 @@ __device__ __forceinline__ float weight(float a, float m) { return a == m ? 1.f 
 // FINISH: the task's rows go out finished (store_finished).
 template <int DT, bool ONCE, int NT, int W, int D, bool FINISH = false>
 __device__ __forceinline__ void run_stream(const PacParams &P, const DevTask &t, int head, char *lds_raw, int wave,
-                           char *stage = nullptr)      // W = 1, up to 128 channels: the wave's staging area
+                                           char *stage = nullptr)   // W = 1, up to 128 channels: the wave's staging area
 {
     constexpr int KS = D / 32, CT = channel_tiles(D);
     const int lane = opaque_lane();
@@ -697,9 +733,13 @@ __device__ __forceinline__ void run_stream(const PacParams &P, const DevTask &t,
     if constexpr (FINISH) {
         if (wave == 0) store_finished<DT, D>(P, t, head, rows, l16, grp, st);
     } else if constexpr (W == 1 && NT == 1 && D <= 128) {
-        store_partial_staged<D>(P, t, head, rows, lane, st, stage);
+        if (P.arrive) store_partial_staged<kRowsCoherent, D>(P, t, head, rows, lane, st, stage);
+        else          store_partial_staged<kRowsPlain, D>(P, t, head, rows, lane, st, stage);
     } else {
-        if (wave == 0) store_partial<NT, D>(P, t, head, 0, rows, l16, grp, st);
+        if (wave == 0) {
+            if (P.arrive) store_partial<kRowsCoherent, NT, D>(P, t, head, 0, rows, l16, grp, st);
+            else          store_partial<kRowsPlain, NT, D>(P, t, head, 0, rows, l16, grp, st);
+        }
     }
 }
 
@@ -818,7 +858,7 @@ enum { kHelper = 0, kMatrixFirst = 1, kVectorFirst = 2 };
 // One wave's share of a dense task: task rows row0 .. row0+31 (none for a helper).
 template <int DT, int ROLE, int STRIDE>
 __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &t, int head, char *lds,
-                                             int wave, int row0, int rows)
+                                             int wave, int row0, int rows, RowStore how)
 {
     constexpr bool LIVE = ROLE != kHelper;
     static_assert(STRIDE == 1 || STRIDE == 2, "a row group is shared by one or two waves");
@@ -1239,18 +1279,20 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
                 const f32x4 x4 = {o[ct][4 * q], o[ct][4 * q + 1], o[ct][4 * q + 2], o[ct][4 * q + 3]};
                 *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(put + ct * 128 + q * 32)) = x4;
             }
-        const int row = row0 + l32;
-        if (row < rows && kg == 0) {
-            const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + row;
-            st8_partial(P.part_ml + prow * 2, m, l, P.arrive != nullptr);
-        }
         const uint32_t get = area + uint32_t(kg) * kStageRow + uint32_t(l32) * 16;
-        float *po = P.part_o + (int64_t(head) * P.part_rows + t.part_row_base + row0 + kg) * kHeadDim + l32 * 4;
+        const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + row0;
+        float *po = P.part_o + prow * kHeadDim;
+        with_row_store(how, [&](auto h) __attribute__((always_inline)) {
+            constexpr RowStore HOW = decltype(h)::value;
+            if (row0 + l32 < rows && kg == 0) st8_partial<HOW>(P.part_ml + (prow + l32) * 2, m, l);
+            const Rows out = rows_at(po, (rows - row0) * kHeadDim * 4);         // rows the task does not have are dropped
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const f32x4 x4 = *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(get + j * 2 * kStageRow));
-            if (row0 + 2 * j + kg < rows) st16_partial(po + j * 2 * kHeadDim, x4, P.arrive != nullptr);
-        }
+            for (int j = 0; j < 16; ++j) {
+                const f32x4 x4 = *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(get + j * 2 * kStageRow));
+                if constexpr (HOW != kRowsCoherent) st16_rows<HOW>(out, lane * 16 + j * 2 * kHeadDim * 4, x4);
+                else if (row0 + 2 * j + kg < rows) st16_partial<HOW>(po + (2 * j + kg) * kHeadDim + l32 * 4, x4);
+            }
+        });
     }
     __syncthreads();                        // the staging areas (and the hand-over area) are free for the next task
 }
@@ -1260,20 +1302,20 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
 // and take alternate blocks, again in opposite phases; short slices, for which the hand-over at the end
 // costs more than the overlap gains (about 1 us per task), keep one wave per row group.
 template <int DT>
-__device__ void run_dense32(const PacParams &P, const DevTask &t, int head, char *lds)
+__device__ __forceinline__ void run_dense32(const PacParams &P, const DevTask &t, int head, char *lds, RowStore how)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows = t.n_req * P.group;
     if (rows > kSplitBlocksMaxRows || t.kv_len < kSplitBlocksMinLen) {
         const int row0 = wave * 32;
-        if (row0 >= rows)  dense32_wave<DT, kHelper, 1>(P, t, head, lds, wave, 0, 0);
-        else if (wave & 4) dense32_wave<DT, kVectorFirst, 1>(P, t, head, lds, wave, row0, rows);
-        else               dense32_wave<DT, kMatrixFirst, 1>(P, t, head, lds, wave, row0, rows);
+        if (row0 >= rows)  dense32_wave<DT, kHelper, 1>(P, t, head, lds, wave, 0, 0, how);
+        else if (wave & 4) dense32_wave<DT, kVectorFirst, 1>(P, t, head, lds, wave, row0, rows, how);
+        else               dense32_wave<DT, kMatrixFirst, 1>(P, t, head, lds, wave, row0, rows, how);
     } else {
         const int row0 = (wave & 3) * 32;
-        if (row0 >= rows)  dense32_wave<DT, kHelper, 2>(P, t, head, lds, wave, 0, 0);
-        else if (wave & 4) dense32_wave<DT, kVectorFirst, 2>(P, t, head, lds, wave, row0, rows);
-        else               dense32_wave<DT, kMatrixFirst, 2>(P, t, head, lds, wave, row0, rows);
+        if (row0 >= rows)  dense32_wave<DT, kHelper, 2>(P, t, head, lds, wave, 0, 0, how);
+        else if (wave & 4) dense32_wave<DT, kVectorFirst, 2>(P, t, head, lds, wave, row0, rows, how);
+        else               dense32_wave<DT, kMatrixFirst, 2>(P, t, head, lds, wave, row0, rows, how);
     }
 }
 
@@ -1344,7 +1386,7 @@ __device__ __forceinline__ void dma16(uint32_t lds_addr, uint32_t voff, const ch
 // NT: row tiles of 16 per wave.  SHARE: waves that share a row group; they take turns with the blocks of
 // every interval and merge their states at the end.
 template <int DT, int D, int NT, int SHARE>
-__device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t, int head, char *lds)
+__device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t, int head, char *lds, RowStore how)
 {
     using T = TilePath<D>;
     constexpr int RB = T::kRowBytes, KS = D / 32, CT = T::CT;
@@ -1577,35 +1619,43 @@ __device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t
     if (live && phase == 0) {
         const int tile_rows = (t.flags >> kTaskTileShift) & 255, stride = ~t.single_req;
         const int last_tile = (rows - 1) / tile_rows, last_back = t.flags >> kTaskLastShift;
-        const bool coherent = P.arrive != nullptr;
+        float *po = P.part_o + (int64_t(head) * P.part_rows + t.part_row_base) * D;
+        float *pml = P.part_ml + (int64_t(head) * P.part_rows + t.part_row_base) * 2;
+        // an offset reaches 2^31 bytes: more slices of a node than any but a forced division has
+        if (how == kRowsThrough && int64_t(last_tile + 1) * stride * (D * 4) >= int64_t(1) << 31) how = kRowsPlain;
+        with_row_store(how, [&](auto h) __attribute__((always_inline)) {
+            constexpr RowStore HOW = decltype(h)::value;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int row = row0 + nt * 16 + l16;
-            if (row < rows) {
-                const int tile = row / tile_rows;
-                const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + int64_t(tile) * stride
-                                     + (row - tile * tile_rows) - (tile == last_tile ? last_back : 0);
-                float *po = P.part_o + prow * D + grp * 4;
+            for (int nt = 0; nt < NT; ++nt) {
+                const int row = row0 + nt * 16 + l16;
+                if (row < rows) {
+                    const int tile = row / tile_rows;
+                    const int64_t at = int64_t(tile) * stride + (row - tile * tile_rows) - (tile == last_tile ? last_back : 0);
 #pragma unroll
-                for (int dt = 0; dt < CT; ++dt) st16_partial(po + dt * 16, st.o[nt][dt], coherent);
-                if (grp == 0) st8_partial(P.part_ml + prow * 2, st.m[nt], st.l[nt], coherent);
+                    for (int dt = 0; dt < CT; ++dt) {
+                        const int64_t off = at * D + grp * 4 + dt * 16;
+                        if constexpr (HOW == kRowsThrough) st16_rows<HOW>(rows_at(po, -1), int(off) * 4, st.o[nt][dt]);
+                        else                               st16_partial<HOW>(po + off, st.o[nt][dt]);
+                    }
+                    if (grp == 0) st8_partial<HOW>(pml + at * 2, st.m[nt], st.l[nt]);
+                }
             }
-        }
+        });
     }
     __syncthreads();                        // every block has been read: the ring is free for the next task
 }
 
 template <int DT, int D>
-__device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, int head, char *lds)
+__device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, int head, char *lds, RowStore how)
 {
     const int rows = t.n_req * P.group;
     if constexpr (D == 64) {            // row groups of 32: up to two, four, eight
-        if (rows <= 64)       run_tile_of<DT, D, 2, 4>(P, t, head, lds);
-        else if (rows <= 128) run_tile_of<DT, D, 2, 2>(P, t, head, lds);
-        else                  run_tile_of<DT, D, 2, 1>(P, t, head, lds);
+        if (rows <= 64)       run_tile_of<DT, D, 2, 4>(P, t, head, lds, how);
+        else if (rows <= 128) run_tile_of<DT, D, 2, 2>(P, t, head, lds, how);
+        else                  run_tile_of<DT, D, 2, 1>(P, t, head, lds, how);
     } else {                            // a row group per wave, of 16 or of 32 rows
-        if (rows <= 64) run_tile_of<DT, D, 1, 1>(P, t, head, lds);
-        else            run_tile_of<DT, D, 2, 1>(P, t, head, lds);
+        if (rows <= 64) run_tile_of<DT, D, 1, 1>(P, t, head, lds, how);
+        else            run_tile_of<DT, D, 2, 1>(P, t, head, lds, how);
     }
 }
 
@@ -1863,14 +1913,28 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
         static_assert(merge_bytes(W, stream_tiles(D), D) + W * solo_stage_bytes(D) <= TilePath<D>::kRingBytes,
                       "staging areas fit the ring");
     char *stage = lds + merge_bytes(W, DENSE ? 1 : stream_tiles(D), D) + wave * solo_stage_bytes(D);
+    // How dense and tile tasks store their rows with tasks to follow, and as the last of the workgroup (in
+    // single-launch mode all alike).
+    // With tasks to follow: written through where the plan's rows are more than 1 MB per XCD (of 4 MB of L2,
+    // through which K and V stream).  Of 34 drawn plans those with 1.2 MB and more gain (a random forest with 3.5 MB 262 -> 242 us, one with 2.8 MB
+    // 102 -> 95), those with 0.2 .. 0.75 MB lose up to 4 % when their rows are written through.
+    // The last rows stay in L2 for the reduction, whose workgroups of KV head h run on XCD h % 8, like those that
+    // store the head's rows, if there are eight heads (64 requests of 4 rows below a 4096-token root, 32 layers:
+    // 833 us plain, 844 written through).  With fewer heads most rows are read on another XCD (plain / written through:
+    // a 4096-token root under 16 requests of 28 / 4 heads 16.3 / 15.9 us, 8192 under 64 of 32 / 4 29.9 / 28.5, a
+    // six-level tree with one KV head 39.2 / 38.4).
+    constexpr bool ARRIVES = FUSED && !one_kernel(FORM, D);             // P.arrive for certain
+    const bool many_rows = int64_t(P.part_rows) * P.h_kv * (D * 4) > int64_t(8) << 20;
+    const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : many_rows ? kRowsThrough : kRowsPlain;
+    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : (P.h_kv & 7) ? kRowsThrough : kRowsPlain;
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in
     // LDS: the latencies of a short task (descriptor, query rows, page ids, first blocks, merge of a
     // team) then overlap with the other tasks' instead of adding up.  In a slot's list the plan marks
     // such runs (they are neighbours there, the list being sorted by cost); an entry of the run-time
-    // queue with several tasks is one such run.
-    auto run_tasks = [&](const DevTask *recs, int t0, int t1, bool marked) __attribute__((always_inline)) {
+    // queue with several tasks is one such run.  `more`: other records may follow these.
+    auto run_tasks = [&](const DevTask *recs, int t0, int t1, bool marked, bool more) __attribute__((always_inline)) {
         int i = t0;
 #pragma unroll 1
         while (i < t1) {
@@ -1902,13 +1966,14 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
             } else {
                 bool tiles = false;             // sibling row tiles packed into one task
                 if constexpr (TILES) tiles = (t.flags & kTaskTiles) != 0;
+                const RowStore how = i + 1 < t1 || more ? early : late;
                 if (tiles) {
-                    if constexpr (TILES) run_tile<DT, D>(P, t, head, lds);
+                    if constexpr (TILES) run_tile<DT, D>(P, t, head, lds, how);
                 } else if (t.n_req * P.group <= 16) {
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 1, W, D, FINISH>(P, t, head, lds, wave);
                     else             run_stream<DT, false, 1, W, D, FINISH>(P, t, head, lds, wave);
                 }
-                else if constexpr (DENSE) run_dense32<DT>(P, t, head, lds);
+                else if constexpr (DENSE) run_dense32<DT>(P, t, head, lds, how);
                 else if constexpr (stream_tiles(D) == 2 && !FINISH) {   // 17 .. 32 rows of 64 channels: two row tiles
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head, lds, wave);
                     else             run_stream<DT, false, 2, W, D>(P, t, head, lds, wave);
@@ -1935,7 +2000,7 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     int e = slot;
 #pragma unroll 1
     while (e < limit) {
-        run_tasks(recs, off[e], off[e + 1], !queued);
+        run_tasks(recs, off[e], off[e + 1], !queued, fetching);
         if (!fetching) break;
         // taken when the workgroup is free, not ahead of time: an entry reserved early would wait for
         // the end of a long task while other workgroups idle

@@ -245,6 +245,26 @@ def test_samples_of_undivided_prompts(d, hq, hkv, length, samples, opts):
     assert np.array_equal(two.double().cpu().numpy(), got) and torch.equal(one.view(torch.int16), two.view(torch.int16))
 
 
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (128, 8, 2), (128, 8, 1), (64, 32, 8), (64, 8, 2), (256, 16, 8), (256, 8, 2)])
+@pytest.mark.parametrize("opts", [{"num_slots": 3}, {"num_slots": 64}, {"num_slots": 2, "schedule": 1}])
+def test_rows_of_early_and_last_tasks(d, hq, hkv, opts):
+    """Partial rows that a workgroup stores with tasks to follow, and its last ones (written through or left to the
+    reduction in L2): one and several tasks per slot of every shape, heads on XCDs of their own and not, the queue.
+    Three steps on one workspace, each with other queries: no reduction may see rows of the step before."""
+    C = _C()
+    f = concat_forests(two_level_forest(1100, [60 + 17 * i for i in range(20)]), unshared_forest([2300, 40, 700]))
+    w = make_workload(f"early-{d}-{hq}-{hkv}", f, HeadConfig(hq, hkv, d, DTYPE_BF16), seed=1200 + d, poison=True, layout="htd")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", split_align=256, **opts)
+    wd = w.to("cuda:0")
+    for step in range(3):
+        w.q[:] = torch.randn(w.q.shape, generator=torch.Generator().manual_seed(step)).to(w.q.dtype)
+        out = pa.decode(w.q.to("cuda:0"), wd.k_pool, wd.v_pool)
+        torch.cuda.synchronize()
+        ref, _ = A.decode_attention_workload(w)
+        assert np.max(np.abs(out.double().cpu().numpy() - ref)) <= TOL, f"step {step}"
+    pa.close()
+
+
 @pytest.mark.parametrize("max_rows", [8, 16, 32, 48, 64, 100, 128, 200, 256])
 def test_row_tiles(max_rows):
     """70 requests x group 4 = 280 rows under the root: stream and dense task shapes, row tiling."""

@@ -265,6 +265,17 @@ def test_rows_of_early_and_last_tasks(d, hq, hkv, opts):
     pa.close()
 
 
+@pytest.mark.parametrize("hq,hkv,requests", [(1, 1, 65537), (1, 1, 70001), (6, 3, 9), (5, 5, 3), (28, 4, 1), (12, 1, 7)])
+def test_reduction_grid(hq, hkv, requests):
+    """The reduction's workgroups by KV head: heads that do not divide eight, odd numbers of row units per head, and
+    more units than one grid dimension holds."""
+    f = Forest(np.array([-1]), np.array([300 if requests < 100 else 40]), np.zeros(requests, np.int32))
+    w = make_workload(f"grid-{hq}-{hkv}-{requests}", f, HeadConfig(hq, hkv, 128, DTYPE_BF16), seed=1300 + hq, poison=True)
+    sel = sorted({(r, h) for r in (0, 1, 2, requests // 2, min(65535, requests - 1), min(65536, requests - 1), requests - 1)
+                  for h in range(hq)} if requests >= 9 else {(r, h) for r in range(requests) for h in range(hq)})
+    check(w, sel=sel, split_align=32, num_slots=8)
+
+
 @pytest.mark.parametrize("max_rows", [8, 16, 32, 48, 64, 100, 128, 200, 256])
 def test_row_tiles(max_rows):
     """70 requests x group 4 = 280 rows under the root: stream and dense task shapes, row tiling."""

@@ -1920,18 +1920,10 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     char *stage = lds + merge_bytes(W, DENSE ? 1 : stream_tiles(D), D) + wave * solo_stage_bytes(D);
     // How dense and tile tasks store their rows with tasks to follow, and as the last of the workgroup (in
     // single-launch mode all alike).
-    // With tasks to follow: written through where the plan's rows are more than 1 MB per XCD (of 4 MB of L2,
-    // through which K and V stream).  Of 34 drawn plans those with 1.2 MB and more gain (a random forest with 3.5 MB 262 -> 242 us, one with 2.8 MB
-    // 102 -> 95), those with 0.2 .. 0.75 MB lose up to 4 % when their rows are written through.
-    // The last rows stay in L2 for the reduction, whose workgroups of KV head h run on XCD h % 8, like those that
-    // store the head's rows, if there are eight heads (64 requests of 4 rows below a 4096-token root, 32 layers:
-    // 833 us plain, 844 written through).  With fewer heads most rows are read on another XCD (plain / written through:
-    // a 4096-token root under 16 requests of 28 / 4 heads 16.3 / 15.9 us, 8192 under 64 of 32 / 4 29.9 / 28.5, a
-    // six-level tree with one KV head 39.2 / 38.4).
     constexpr bool ARRIVES = FUSED && !one_kernel(FORM, D);             // P.arrive for certain
-    const bool many_rows = int64_t(P.part_rows) * P.h_kv * (D * 4) > int64_t(8) << 20;
-    const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : many_rows ? kRowsThrough : kRowsPlain;
-    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : (P.h_kv & 7) ? kRowsThrough : kRowsPlain;
+    const int64_t part_bytes = int64_t(P.part_rows) * P.h_kv * (D * 4);
+    const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : early_rows_through(part_bytes) ? kRowsThrough : kRowsPlain;
+    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(part_bytes, P.h_kv) ? kRowsThrough : kRowsPlain;
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in

@@ -19,13 +19,13 @@ int image_plan(const codec_tree *tree, const codec_head_config *head, const code
     return refreshed_len ? codec::refresh_plan(plan, refreshed_len, tree->node_page_off, tree->page_ids) : 0;
 }
 
-// slot_recs, slot_off, num_slots, queue_off, queue_recs, num_entries, packs, single_parts, schedule, fused, makespan
+// slot_recs, slot_off, num_slots, queue_off, queue_recs, num_entries, packs, single_parts, schedule, fused, makespan, part_rows
 void image_layout(int64_t *v)
 {
     const codec::DevLayout &L = plan.layout;
     const int64_t x[] = {int64_t(L.slot_recs), int64_t(L.slot_off), L.num_slots, int64_t(L.queue_off), int64_t(L.queue_recs),
                          L.num_entries, int64_t(plan.packs.size()), codec::single_parts(plan), plan.schedule, plan.fused,
-                         plan.makespan};
+                         plan.makespan, plan.part_rows};
     std::memcpy(v, x, sizeof x);
 }
 
@@ -40,6 +40,12 @@ void image_packs(int64_t *packs, int32_t *slot_off, int32_t *slot_packs)
     if (plan.packs.empty()) return;
     std::memcpy(slot_off, plan.pack_slots.off.data(), plan.pack_slots.off.size() * 4);
     std::memcpy(slot_packs, plan.pack_slots.tasks.data(), plan.pack_slots.tasks.size() * 4);
+}
+
+// which rows the kernels write through: bit 0 those with tasks to follow, bit 1 a workgroup's last ones
+int image_rows_through(int64_t part_bytes, int32_t kv_heads)
+{
+    return (codec::early_rows_through(part_bytes) ? 1 : 0) | (codec::last_rows_through(part_bytes, kv_heads) ? 2 : 0);
 }
 
 const unsigned char *image_blob() { return plan.blob.data(); }

@@ -17,7 +17,7 @@ CSRC = os.path.join(ROOT, "paper_2505_17694_amd", "csrc")
 # DevTask of planner.hpp
 RECORD = np.dtype([(n, np.int32) for n in ("page_off", "kv_len", "q_off", "n_req", "part_row_base", "solo_run", "flags", "single_req")])
 LAYOUT = ("slot_recs", "slot_off", "num_slots", "queue_off", "queue_recs", "num_entries", "packs", "single_parts",
-          "schedule", "fused", "makespan")
+          "schedule", "fused", "makespan", "part_rows")
 
 
 @functools.lru_cache(maxsize=None)
@@ -29,7 +29,14 @@ def _probe():
         lib = ctypes.CDLL(so)
     lib.image_blob.restype = ctypes.c_void_p
     lib.image_bytes.restype = ctypes.c_int64
+    lib.image_rows_through.argtypes = [ctypes.c_int64, ctypes.c_int32]
     return lib
+
+
+def rows_through(part_bytes, kv_heads):
+    """(rows with tasks to follow, last rows): whether the two-launch kernels write them through to memory."""
+    bits = _probe().image_rows_through(part_bytes, kv_heads)
+    return bool(bits & 1), bool(bits & 2)
 
 
 def plan_image(f, head, num_slots=0, split_align=0, max_rows=0, share=1, fixed_slices=0, schedule=0, fused=0,

@@ -13,7 +13,7 @@ import paper_2505_17694_amd as C
 from oracle import planner as P
 from golden_tables import load_table2
 from helpers import DIVIDED_PACKS, DIVIDED_PACKS_OPTS, divided_packs_forest
-from plan_image import plan_image
+from plan_image import plan_image, rows_through
 from workloads import (two_level_forest, three_level_forest, random_forest, unshared_forest,
                        concat_forests, degenerate_forest, full_kary_forest, draft_tree_forest, draft_masked_forest, Forest,
                        HeadConfig, build_paged_kv)
@@ -680,3 +680,16 @@ def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts):
     records = im["slot_recs"]
     shifts = records["flags"][(records["flags"] & 4) != 0] >> 16
     assert (max(shifts) > 0) == uneven
+
+
+@pytest.mark.parametrize("kv_heads", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 36, 64])
+def test_which_rows_are_written_through(kv_heads):
+    """The rule by the plan's partial rows and KV heads: last rows only where eight does not divide the heads, and never
+    those of a small plan, which the reduction finds in L2 whichever XCD it runs on often enough."""
+    mb, aligned = 1 << 20, kv_heads % 8 == 0
+    for size in (0, mb // 16, mb, 3 * mb):
+        assert rows_through(size, kv_heads) == (False, False)
+    for size in (3 * mb + 1, 8 * mb):
+        assert rows_through(size, kv_heads) == (False, not aligned)
+    for size in (8 * mb + 1, 31 * mb, 2600 * mb):
+        assert rows_through(size, kv_heads) == (True, not aligned)

@@ -1921,9 +1921,9 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     // How dense and tile tasks store their rows with tasks to follow, and as the last of the workgroup (in
     // single-launch mode all alike).
     constexpr bool ARRIVES = FUSED && !one_kernel(FORM, D);             // P.arrive for certain
-    const int64_t part_bytes = int64_t(P.part_rows) * P.h_kv * (D * 4);
-    const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : early_rows_through(part_bytes) ? kRowsThrough : kRowsPlain;
-    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(part_bytes, P.h_kv) ? kRowsThrough : kRowsPlain;
+    const bool many_rows = early_rows_through(P.part_rows, P.h_kv, D);
+    const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : many_rows ? kRowsThrough : kRowsPlain;
+    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(P.part_rows, P.h_kv, D) ? kRowsThrough : kRowsPlain;
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in

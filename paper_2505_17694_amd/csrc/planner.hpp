@@ -66,20 +66,26 @@ constexpr int32_t kTaskLastMax = 32767;
 constexpr int32_t pack_max_rows(int32_t head_dim) { return head_dim == 64 ? 256 : 128; }
 
 // Which partial rows of dense and packed tasks are written through to memory at once, instead of staying in L2 until
-// the reduction reads them (`part_bytes`: all partial rows of the plan, fp32; why, and what else was measured:
-// RowStore in kernels.hip).  Time written through over plain, geometric mean and worst of drawn plans, both builds
+// the reduction reads them (MB: all partial rows of the plan, fp32; why, and what else was measured: RowStore in
+// kernels.hip).  Time written through over plain, geometric mean and worst of drawn plans, both builds
 // in turn on one card.
 // Rows with tasks to follow in their workgroup, by MB of rows (260 plans, 158 of them with 128 channels):
 //   128 channels:  3 .. 6 1.015 (1.049),  6 .. 8 1.002 (1.047),  8 .. 10 0.992 (1.046),  10 .. 14 0.973,  more 0.957
 //   256 channels:  3 .. 6 1.002 (1.034),  6 .. 8 0.987,  8 .. 10 0.998 (1.018),  10 .. 14 0.982,  more 0.989
 //    64 channels:  3 .. 8 0.996,  8 .. 10 0.989,  10 .. 14 0.986,  more 1.005 (1.019)
-constexpr bool early_rows_through(int64_t part_bytes) { return part_bytes > int64_t(8) << 20; }
+constexpr bool early_rows_through(int32_t part_rows, int32_t kv_heads, int32_t head_dim)
+{
+    return int64_t(part_rows) * kv_heads * (head_dim * 4) > int64_t(8) << 20;
+}
 // A workgroup's last rows, with a number of KV heads that eight does not divide.  (Workgroups of KV head h run on XCD
 // h % 8 if eight divides it, in the reduction too, which then finds the rows in that XCD's L2: they stay plain.)
 //   up to 3 MB: 55 plans 1.007 (1.031)
 //   more, up to seven heads:         128 channels 41 plans 0.986 (1.018), 256: 25 0.992 (1.014), 64: 24 0.994 (1.015)
 //   more, from nine heads (9 .. 36): 128 channels 45 plans 0.997 (1.014), 256: 39 0.995 (1.007), 64: 21 1.002 (1.017)
-constexpr bool last_rows_through(int64_t part_bytes, int32_t kv_heads) { return (kv_heads & 7) != 0 && part_bytes > int64_t(3) << 20; }
+constexpr bool last_rows_through(int32_t part_rows, int32_t kv_heads, int32_t head_dim)
+{
+    return (kv_heads & 7) && int64_t(part_rows) * kv_heads * (head_dim * 4) > int64_t(3) << 20;
+}
 
 // Per request, the reduction kernel reads one 64-byte line: the number of partial rows on the request's
 // path and, if there are at most kInlineParts of them, the rows themselves; longer lists are read

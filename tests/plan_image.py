@@ -29,13 +29,12 @@ def _probe():
         lib = ctypes.CDLL(so)
     lib.image_blob.restype = ctypes.c_void_p
     lib.image_bytes.restype = ctypes.c_int64
-    lib.image_rows_through.argtypes = [ctypes.c_int64, ctypes.c_int32]
     return lib
 
 
-def rows_through(part_bytes, kv_heads):
+def rows_through(part_rows, kv_heads, head_dim):
     """(rows with tasks to follow, last rows): whether the two-launch kernels write them through to memory."""
-    bits = _probe().image_rows_through(part_bytes, kv_heads)
+    bits = _probe().image_rows_through(part_rows, kv_heads, head_dim)
     return bool(bits & 1), bool(bits & 2)
 
 

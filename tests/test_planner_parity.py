@@ -682,14 +682,15 @@ def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts):
     assert (max(shifts) > 0) == uneven
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("kv_heads", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 36, 64])
-def test_which_rows_are_written_through(kv_heads):
+def test_which_rows_are_written_through(kv_heads, d):
     """The rule by the plan's partial rows and KV heads: last rows only where eight does not divide the heads, and never
-    those of a small plan, which the reduction finds in L2 whichever XCD it runs on often enough."""
-    mb, aligned = 1 << 20, kv_heads % 8 == 0
-    for size in (0, mb // 16, mb, 3 * mb):
-        assert rows_through(size, kv_heads) == (False, False)
-    for size in (3 * mb + 1, 8 * mb):
-        assert rows_through(size, kv_heads) == (False, not aligned)
-    for size in (8 * mb + 1, 31 * mb, 2600 * mb):
-        assert rows_through(size, kv_heads) == (True, not aligned)
+    those of a small plan."""
+    per_mb, aligned = (1 << 20) / (kv_heads * d * 4), kv_heads % 8 == 0
+    for rows in (0, 1, int(per_mb), int(3 * per_mb)):
+        assert rows_through(rows, kv_heads, d) == (False, False)
+    for rows in (int(3 * per_mb) + 1, int(8 * per_mb)):
+        assert rows_through(rows, kv_heads, d) == (False, not aligned)
+    for rows in (int(8 * per_mb) + 1, int(31 * per_mb), 2 ** 31 - 1):
+        assert rows_through(rows, kv_heads, d) == (True, not aligned)

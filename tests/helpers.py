@@ -2,7 +2,7 @@
 import numpy as np
 import torch
 
-from workloads import bits_to_float64, concat_forests, two_level_forest
+from workloads import Forest, bits_to_float64, concat_forests, two_level_forest
 
 
 def token_slot(w, node, t):
@@ -63,3 +63,34 @@ def divided_packs_forest(requests):
     for n in (97, 513, 1000):
         f = concat_forests(f, two_level_forest(n, [5 + n % 40] * requests))
     return f
+
+
+# Partial rows of dense (128 channels) and packed tasks, written through to memory or not: (channels, query heads, KV
+# heads, requests per node, node lengths, slices per node, rows with tasks to follow written through or not, last rows).
+# Every request ends at a node of many slices, so that wide tasks come first and last in a workgroup; 43 and 41 rows and
+# their multiples leave a smaller last tile.
+ROW_STORES = [
+    (128, 32, 8, 43, (1000, 700, 300, 97), 12, True, False), (128, 16, 4, 43, (1000, 700, 300, 97), 12, True, True),
+    (128, 12, 12, 43, (1000, 700, 300, 97), 12, True, True), (128, 8, 2, 43, (1000, 700, 300, 97), 12, False, True),
+    (128, 32, 8, 43, (1000, 700), 5, False, False), (128, 16, 4, 43, (1000, 700), 4, False, False),
+    (64, 32, 8, 43, (1000, 700, 300, 97), 12, True, False), (64, 16, 4, 43, (1000, 700, 300, 97), 30, True, True),
+    (64, 12, 12, 41, (1000, 1000, 700, 300, 97), 30, True, True), (64, 80, 20, 23, (1000, 700), 11, True, True),
+    (64, 8, 2, 43, (1000, 700, 300, 97), 16, False, True), (64, 32, 8, 43, (1000, 700), 11, False, False),
+    (64, 8, 2, 43, (1000, 700), 16, False, False),
+    (256, 16, 8, 43, (1000, 700, 300, 97), 8, True, False), (256, 8, 4, 43, (1000, 700, 300, 97), 8, True, True),
+    (256, 12, 12, 41, (1000, 700, 300), 8, True, True), (256, 32, 4, 43, (1000, 700), 4, True, True),
+    (256, 8, 2, 43, (1000, 700, 300, 97), 6, False, True),
+    (256, 16, 8, 43, (1000, 700), 5, False, False), (256, 8, 4, 43, (1000, 700), 4, False, False)]
+ROW_STORES_OPTS = [{"num_slots": 3}, {"num_slots": 2, "schedule": 1}]
+
+
+def row_stores_forest(requests, lens):
+    return Forest(np.full(len(lens), -1), np.array(lens), np.repeat(np.arange(len(lens)), requests))
+
+
+# 32 requests of eight heads on one KV head end at a node of this many slices of one block (64 channels)
+LONG_DIVISIONS = [32767, 32768]
+
+
+def long_division_forest(slices):
+    return Forest(np.array([-1]), np.array([32 * slices]), np.zeros(32, np.int64))

@@ -78,3 +78,23 @@ def plan_image(f, head, num_slots=0, split_align=0, max_rows=0, share=1, fixed_s
         at = out[recs]
         out[recs] = blob[at:at + RECORD.itemsize * int(out[offs][-1])].view(RECORD)
     return out
+
+
+def row_stores(f, head, **opts):
+    """How a plan in two launches stores the rows of its dense and packed tasks, walked as the kernel walks its lists:
+    bytes of partial rows, and per kind ("early": with tasks to follow in the workgroup, "last") the number of such
+    tasks and whether their rows are written through."""
+    im = plan_image(f, head, **opts)
+    assert not im["fused"] and not im["single_parts"]
+    group = head.num_q_heads // head.num_kv_heads
+    queued = im["schedule"] == 1
+    fetching = queued and im["num_entries"] > im["num_slots"]
+    recs, off = (im["queue_recs"], im["queue_off"]) if queued else (im["slot_recs"], im["slot_off"])
+    count = {"early": 0, "last": 0}
+    for a, b in zip(off, off[1:]):
+        for i in range(a, b):
+            dense = int(recs[i]["n_req"]) * group > 16 if head.head_dim == 128 else recs[i]["flags"] & 4
+            if dense:
+                count["early" if i + 1 < b or fetching else "last"] += 1
+    early, last = rows_through(im["part_rows"], head.num_kv_heads, head.head_dim)
+    return {"bytes": im["part_rows"] * head.num_kv_heads * head.head_dim * 4, "early": (count["early"], early), "last": (count["last"], last), "image": im}

@@ -11,7 +11,8 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import DIVIDED_PACKS, DIVIDED_PACKS_OPTS, divided_packs_forest
+from helpers import (DIVIDED_PACKS, DIVIDED_PACKS_OPTS, LONG_DIVISIONS, ROW_STORES, ROW_STORES_OPTS, divided_packs_forest,
+                     long_division_forest, row_stores_forest)
 from oracle import attention as A
 from workloads import (HeadConfig, Forest, make_workload, make_small_config, make_config,
                        two_level_forest, three_level_forest, unshared_forest, random_forest,
@@ -248,8 +249,8 @@ def test_samples_of_undivided_prompts(d, hq, hkv, length, samples, opts):
 @pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (128, 8, 2), (128, 8, 1), (64, 32, 8), (64, 8, 2), (256, 16, 8), (256, 8, 2)])
 @pytest.mark.parametrize("opts", [{"num_slots": 3}, {"num_slots": 64}, {"num_slots": 2, "schedule": 1}])
 def test_rows_of_early_and_last_tasks(d, hq, hkv, opts):
-    """Partial rows that a workgroup stores with tasks to follow, and its last ones (written through or left to the
-    reduction in L2): one and several tasks per slot of every shape, heads on XCDs of their own and not, the queue.
+    """Partial rows of small plans, which stay in L2 (test_row_stores_of_early_and_last_tasks has those that are written
+    through): one and several tasks per slot of every shape, heads on XCDs of their own and not, the queue.
     Three steps on one workspace, each with other queries: no reduction may see rows of the step before."""
     C = _C()
     f = concat_forests(two_level_forest(1100, [60 + 17 * i for i in range(20)]), unshared_forest([2300, 40, 700]))
@@ -263,6 +264,51 @@ def test_rows_of_early_and_last_tasks(d, hq, hkv, opts):
         ref, _ = A.decode_attention_workload(w)
         assert np.max(np.abs(out.double().cpu().numpy() - ref)) <= TOL, f"step {step}"
     pa.close()
+
+
+@pytest.mark.parametrize("d,hq,hkv,requests,lens,slices,early,last", ROW_STORES)
+@pytest.mark.parametrize("opts", ROW_STORES_OPTS)
+def test_row_stores_of_early_and_last_tasks(d, hq, hkv, requests, lens, slices, early, last, opts):
+    """Rows of dense and packed tasks with others to follow and as the last of their workgroup, written through to
+    memory or left in L2 (which case does what is asserted on the host, in the planner tests), packs with a smaller
+    last tile.  Three steps on one workspace, filled with NaN before the first, each with other queries: a reduction
+    that reads a row of the step before, or one that was stored elsewhere, shows."""
+    C = _C()
+    dtype = DTYPE_FP16 if "schedule" in opts else DTYPE_BF16
+    w = make_workload(f"stores-{d}-{hq}-{hkv}", row_stores_forest(requests, lens), HeadConfig(hq, hkv, d, dtype),
+                      seed=1400 + d + hkv, poison=True, layout="htd" if hkv % 8 else "thd")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", split_align=32, fixed_slices=slices, **opts)
+    pa.workspace.fill_(0xFF)
+    wd = w.to("cuda:0")
+    for step in range(3):
+        w.q[:] = torch.randn(w.q.shape, generator=torch.Generator().manual_seed(step)).to(w.q.dtype)
+        out = pa.decode(w.q.to("cuda:0"), wd.k_pool, wd.v_pool)
+        torch.cuda.synchronize()
+        ref, _ = A.decode_attention_workload(w)
+        err = np.abs(out.double().cpu().numpy() - ref)
+        assert np.all(err <= 2e-3 + 2.0 ** -7 * np.abs(ref)), f"step {step}: worst {np.nanmax(err):.3e}"
+    pa.close()
+
+
+@pytest.mark.parametrize("slices", LONG_DIVISIONS)
+def test_packs_whose_rows_lie_two_gigabytes_apart(slices):
+    """The rows of the eight tiles of a pack span 64 KB less than the 2^31 bytes that the written-through form reaches;
+    with one slice more they span 2^31 and stay plain.  The workspace is filled with NaN, so that a row stored
+    elsewhere shows; outputs are means over a million tokens, so the error is taken relative to them."""
+    C = _C()
+    w = make_workload(f"long-{slices}", long_division_forest(slices), HeadConfig(8, 1, 64, DTYPE_BF16), seed=1500, layout="htd")
+    wd = w.to("cuda:0")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", split_align=32, fixed_slices=slices)
+    pa.workspace.fill_(0xFF)
+    out = pa.decode(wd.q, wd.k_pool, wd.v_pool)
+    torch.cuda.synchronize()
+    pa.close()
+    got = out.double().cpu().numpy()
+    assert not np.any(np.isnan(got))
+    sel = [(r, h) for r in (0, 3, 4, 15, 28, 31) for h in (0, 7)]
+    ref, _ = A.decode_attention_workload(w, sel=sel)
+    off = np.linalg.norm(np.stack([got[r, h] for r, h in sel]) - ref) / np.linalg.norm(ref)
+    assert off <= 1e-2, off                         # probabilities and output rounded to bf16: 2.3e-3, four times that
 
 
 @pytest.mark.parametrize("hq,hkv,requests", [(1, 1, 65537), (1, 1, 70001), (6, 3, 9), (5, 5, 3), (28, 4, 1), (12, 1, 7)])

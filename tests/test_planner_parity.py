@@ -12,8 +12,9 @@ import pytest
 import paper_2505_17694_amd as C
 from oracle import planner as P
 from golden_tables import load_table2
-from helpers import DIVIDED_PACKS, DIVIDED_PACKS_OPTS, divided_packs_forest
-from plan_image import plan_image, rows_through
+from helpers import (DIVIDED_PACKS, DIVIDED_PACKS_OPTS, LONG_DIVISIONS, ROW_STORES, ROW_STORES_OPTS, divided_packs_forest,
+                     long_division_forest, row_stores_forest)
+from plan_image import plan_image, row_stores, rows_through
 from workloads import (two_level_forest, three_level_forest, random_forest, unshared_forest,
                        concat_forests, degenerate_forest, full_kary_forest, draft_tree_forest, draft_masked_forest, Forest,
                        HeadConfig, build_paged_kv)
@@ -694,3 +695,30 @@ def test_which_rows_are_written_through(kv_heads, d):
         assert rows_through(rows, kv_heads, d) == (False, not aligned)
     for rows in (int(8 * per_mb) + 1, int(31 * per_mb), 2 ** 31 - 1):
         assert rows_through(rows, kv_heads, d) == (True, not aligned)
+
+
+@pytest.mark.parametrize("d,hq,hkv,requests,lens,slices,early,last", ROW_STORES)
+@pytest.mark.parametrize("opts", ROW_STORES_OPTS)
+def test_row_stores_of_early_and_last_tasks(d, hq, hkv, requests, lens, slices, early, last, opts):
+    """The plans of the GPU parity test of the same name: dense or packed tasks with others to follow and as the last of
+    their workgroup (none under the queue), rows written through or not as the table says; packs with a smaller
+    last tile on several slices of a node."""
+    got = row_stores(row_stores_forest(requests, lens), HeadConfig(hq, hkv, d), split_align=32, fixed_slices=slices, **opts)
+    assert (got["early"][1], got["last"][1]) == (early, last), got["bytes"]
+    assert got["early"][0] >= 5 and got["last"][0] == (0 if "schedule" in opts else 3)
+    if d != 128:
+        records = got["image"]["queue_recs" if "schedule" in opts else "slot_recs"]
+        assert max(p["rows"] for p in got["image"]["packs"]) >= 41
+        assert max(records["flags"][(records["flags"] & 4) != 0] >> 16) > 0
+
+
+@pytest.mark.parametrize("slices", LONG_DIVISIONS)
+def test_packs_whose_rows_lie_two_gigabytes_apart(slices):
+    """The plans of the GPU parity test of the same name: packs of eight tiles, written through, on both sides of the
+    2^31 bytes that the kernel compares (tiles) x (rows from tile to tile) x (bytes of a row) with."""
+    got = row_stores(long_division_forest(slices), HeadConfig(8, 1, 64), split_align=32, fixed_slices=slices)
+    records = got["image"]["slot_recs"]
+    assert (records["flags"] & 4).all() and len(records) == slices and (records["n_req"] == 32).all()
+    assert got["early"][0] > 30000 and got["early"][1] and got["last"][1]
+    spans = {8 * int(~r) * 256 for r in records["single_req"]}
+    assert spans == {2 ** 31 - (65536 if slices == 32767 else 0)}

@@ -147,20 +147,23 @@ __device__ __forceinline__ float2 ld8_device(const float *p)
     return __builtin_bit_cast(float2, v);
 }
 // How the partial rows of a task are stored.
-//  kRowsPlain     read by a later launch; the lines stay in the L2 of the XCD, where the reduction finds them
-//  kRowsThrough   the same, written through at once (the `sc1` form): dense and tile tasks with K and V still to
-//                 read behind them
+//  kRowsPlain     read by a later launch; the lines stay in the L2 of the XCD until something pushes them out
+//  kRowsThrough   the same, written through at once (the `sc1` form): rows of dense and tile tasks in plans that
+//                 have many (early_rows_through, last_rows_through)
 //  kRowsCoherent  read by other workgroups of this launch (single-launch mode)
 // Lines that wait in L2 for their write-back are pushed out by the K and V that stream through it, a few at a
-// time, and HBM turns around between reads and writes for each: 2 KB stored for every 15 blocks of 16 KB
-// read take a stream of 256 workgroups from 6.74 to 5.82 TB/s, written through to 6.14; for every 31 blocks 6.36
-// and 6.56.  Rows written through are not in L2, though, when the reduction reads them: with all rows stored like
-// that a lone request goes 14.8 -> 16.6 us.  Stream tasks store 16 bytes of each of 16 lines per instruction, which
-// only L2 puts together: theirs stay plain (written through, two drawn plans with heads of 64 channels lost 4 and 6 %).
+// time, and HBM turns around between reads and writes for each.  Rows written through are not in L2, though, when
+// the reduction reads them.  Which of the two costs more depends on how many rows the plan has; both sides are
+// measured at the rules.  Stream tasks keep plain stores.  Rows of a wave that ran a task on its own, 1 KB of
+// consecutive memory per instruction: written through, 117 drawn plans of 64 and 128 channels take 1.008 of the
+// time, the worst 1.096.  Rows of a team, 16 bytes of each of up to 64 lines per instruction, which only L2 puts
+// together: 150 plans 1.023, the worst 1.155.
 enum RowStore { kRowsPlain, kRowsThrough, kRowsCoherent };
 // Rows behind a buffer descriptor (base the same for the wave, `bytes` long; stores behind its end are dropped):
 // the compiler has no other 16-byte store that is written through, and it keeps the distance that this target wants
-// between a store of this width and the next write to its data registers (inline assembly would not).
+// between a store of this width and the next write to its data registers (inline assembly would not).  Dense tasks
+// store plain rows like that as well, as no row then needs a branch: 92 drawn plans whose dense rows stay plain take
+// 0.993 of the time with pointers, the best 0.949, the worst 1.009.
 typedef __amdgpu_buffer_rsrc_t Rows;
 __device__ __forceinline__ Rows rows_at(float *base, int bytes)
 {
@@ -1621,7 +1624,9 @@ __device__ __forceinline__ void run_tile_of(const PacParams &P, const DevTask &t
         const int last_tile = (rows - 1) / tile_rows, last_back = t.flags >> kTaskLastShift;
         float *po = P.part_o + (int64_t(head) * P.part_rows + t.part_row_base) * D;
         float *pml = P.part_ml + (int64_t(head) * P.part_rows + t.part_row_base) * 2;
-        // an offset reaches 2^31 bytes: more slices of a node than any but a forced division has
+        // The descriptor spans the rows of all tiles, which lie apart, and drops none: rows that a tile does not have
+        // are left out by a branch.  An offset reaches 2^31 bytes: more slices of a node than any but a forced
+        // division has.
         if (how == kRowsThrough && int64_t(last_tile + 1) * stride * (D * 4) >= int64_t(1) << 31) how = kRowsPlain;
         with_row_store(how, [&](auto h) __attribute__((always_inline)) {
             constexpr RowStore HOW = decltype(h)::value;
@@ -1783,10 +1788,12 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
 }
 
 // blockIdx.x is the KV head.  Workgroups are dealt to the eight XCDs in turn, here and in the attention kernel, so
-// with eight heads the rows of a head are read through the L2 that holds them.  In order of requests, as before,
-// that was so only where the rows of a request fill eight workgroups.  us per step, before / now: a lone request of
+// with eight heads the rows of a head are read through the L2 that holds them.  In order of requests that is so only
+// where the rows of a request fill eight workgroups.  us per step, by request / by head: a lone request of
 // 8191 tokens with 64 / 8 heads 16.4 / 14.5, with 8 / 8 heads 15.5 / 13.7, with 28 / 4 14.9 / 14.5; a 4096-token root under
-// 16 requests with 64 / 8 heads 19.4 / 16.5, with 32 / 4 16.2 / 15.5; 32 / 8 heads of 128 channels, where it was so, unchanged.
+// 16 requests with 64 / 8 heads 19.4 / 16.5, with 32 / 4 16.2 / 15.5; 32 / 8 heads of 128 channels, where both are so, alike.
+// Drawn plans, time by head over by request: 193 with KV heads that eight divides 0.991 (0.858 .. 1.013), 7 with four
+// heads 0.988, 51 with one head, for which the order is the same, 1.002 (0.987 .. 1.020).
 template <int DT, int D, int RPW>
 __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergeParams P)
 {

@@ -149,7 +149,7 @@ __device__ __forceinline__ float2 ld8_device(const float *p)
 // How the partial rows of a task are stored.
 //  kRowsPlain     read by a later launch; the lines stay in the L2 of the XCD until something pushes them out
 //  kRowsThrough   the same, written through at once (the `sc1` form): rows of dense and tile tasks in plans that
-//                 have many (early_rows_through, last_rows_through)
+//                 have many (kEarlyThroughBytes, last_rows_through)
 //  kRowsCoherent  read by other workgroups of this launch (single-launch mode)
 // Lines that wait in L2 for their write-back are pushed out by the K and V that stream through it, a few at a
 // time, and HBM turns around between reads and writes for each.  Rows written through are not in L2, though, when
@@ -1928,9 +1928,9 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     // How dense and tile tasks store their rows with tasks to follow, and as the last of the workgroup (in
     // single-launch mode all alike).
     constexpr bool ARRIVES = FUSED && !one_kernel(FORM, D);             // P.arrive for certain
-    const bool many_rows = early_rows_through(P.part_rows, P.h_kv, D);
+    const bool many_rows = int64_t(P.part_rows) * P.h_kv * (D * 4) > kEarlyThroughBytes;
     const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : many_rows ? kRowsThrough : kRowsPlain;
-    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(P.part_rows, P.h_kv, D) ? kRowsThrough : kRowsPlain;
+    const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(P.h_kv) ? kRowsThrough : kRowsPlain;
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in

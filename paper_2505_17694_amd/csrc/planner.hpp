@@ -73,19 +73,19 @@ constexpr int32_t pack_max_rows(int32_t head_dim) { return head_dim == 64 ? 256 
 //   128 channels:  3 .. 6 1.015 (1.049),  6 .. 8 1.002 (1.047),  8 .. 10 0.992 (1.046),  10 .. 14 0.973,  more 0.957
 //   256 channels:  3 .. 6 1.002 (1.034),  6 .. 8 0.987,  8 .. 10 0.998 (1.018),  10 .. 14 0.982,  more 0.989
 //    64 channels:  3 .. 8 0.996,  8 .. 10 0.989,  10 .. 14 0.986,  more 1.005 (1.019)
-constexpr bool early_rows_through(int32_t part_rows, int32_t kv_heads, int32_t head_dim)
-{
-    return int64_t(part_rows) * kv_heads * (head_dim * 4) > int64_t(8) << 20;
-}
+// (A constant, not a function as below: with the comparison in a function the compiler allocates the tile path of 256
+// channels otherwise, 13 drawn plans 1.006 of the time.)
+constexpr int64_t kEarlyThroughBytes = int64_t(8) << 20;
 // A workgroup's last rows, with a number of KV heads that eight does not divide.  (Workgroups of KV head h run on XCD
 // h % 8 if eight divides it, in the reduction too, which then finds the rows in that XCD's L2: they stay plain.)
-//   up to 3 MB: 55 plans 1.007 (1.031)
-//   more, up to seven heads:         128 channels 41 plans 0.986 (1.018), 256: 25 0.992 (1.014), 64: 24 0.994 (1.015)
-//   more, from nine heads (9 .. 36): 128 channels 45 plans 0.997 (1.014), 256: 39 0.995 (1.007), 64: 21 1.002 (1.017)
-constexpr bool last_rows_through(int32_t part_rows, int32_t kv_heads, int32_t head_dim)
-{
-    return (kv_heads & 7) && int64_t(part_rows) * kv_heads * (head_dim * 4) > int64_t(3) << 20;
-}
+//   more than 3 MB, up to seven heads:         128 channels 82 plans 0.991 (1.025), 256: 34 0.992 (1.014), 64: 35 0.993 (1.015)
+//   more than 3 MB, from nine heads (9 .. 36): 128 channels 47 plans 0.997 (1.014), 256: 40 0.995 (1.007), 64: 22 1.002 (1.017)
+//   up to 3 MB: 119 plans 1.006 (1.049); but groups of more than 16 heads of 128 channels, all of whose tasks are dense,
+//   so that all rows are written through: 16 plans 0.979 (1.006)
+// The rule knows neither size nor group all the same: with them (several forms, evaluated here or on the host) the small
+// plans of smaller groups took 0.995 .. 1.002 of the time, and plans that the rule treats alike, of 128 channels and
+// up to 6 MB, 1.003 .. 1.007, by where the kernel's code then lay; two copies of one build differ by 0.0005.
+constexpr bool last_rows_through(int32_t kv_heads) { return (kv_heads & 7) != 0; }
 
 // Per request, the reduction kernel reads one 64-byte line: the number of partial rows on the request's
 // path and, if there are at most kInlineParts of them, the rows themselves; longer lists are read

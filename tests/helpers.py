@@ -72,15 +72,16 @@ def divided_packs_forest(requests):
 ROW_STORES = [
     (128, 32, 8, 43, (1000, 700, 300, 97), 12, True, False), (128, 16, 4, 43, (1000, 700, 300, 97), 12, True, True),
     (128, 12, 12, 43, (1000, 700, 300, 97), 12, True, True), (128, 8, 2, 43, (1000, 700, 300, 97), 12, False, True),
-    (128, 32, 8, 43, (1000, 700), 5, False, False), (128, 16, 4, 43, (1000, 700), 4, False, False),
+    (128, 32, 8, 43, (1000, 700), 5, False, False), (128, 16, 4, 43, (1000, 700), 4, False, True),
+    (128, 32, 1, 13, (1000, 700), 4, False, True),
     (64, 32, 8, 43, (1000, 700, 300, 97), 12, True, False), (64, 16, 4, 43, (1000, 700, 300, 97), 30, True, True),
     (64, 12, 12, 41, (1000, 1000, 700, 300, 97), 30, True, True), (64, 80, 20, 23, (1000, 700), 11, True, True),
     (64, 8, 2, 43, (1000, 700, 300, 97), 16, False, True), (64, 32, 8, 43, (1000, 700), 11, False, False),
-    (64, 8, 2, 43, (1000, 700), 16, False, False),
+    (64, 8, 2, 43, (1000, 700), 16, False, True),
     (256, 16, 8, 43, (1000, 700, 300, 97), 8, True, False), (256, 8, 4, 43, (1000, 700, 300, 97), 8, True, True),
     (256, 12, 12, 41, (1000, 700, 300), 8, True, True), (256, 32, 4, 43, (1000, 700), 4, True, True),
     (256, 8, 2, 43, (1000, 700, 300, 97), 6, False, True),
-    (256, 16, 8, 43, (1000, 700), 5, False, False), (256, 8, 4, 43, (1000, 700), 4, False, False)]
+    (256, 16, 8, 43, (1000, 700), 5, False, False), (256, 8, 4, 43, (1000, 700), 4, False, True)]
 ROW_STORES_OPTS = [{"num_slots": 3}, {"num_slots": 2, "schedule": 1}]
 
 

@@ -45,8 +45,8 @@ void image_packs(int64_t *packs, int32_t *slot_off, int32_t *slot_packs)
 // which rows the kernels write through: bit 0 those with tasks to follow, bit 1 a workgroup's last ones
 int image_rows_through(int32_t part_rows, int32_t kv_heads, int32_t head_dim)
 {
-    return (codec::early_rows_through(part_rows, kv_heads, head_dim) ? 1 : 0) |
-           (codec::last_rows_through(part_rows, kv_heads, head_dim) ? 2 : 0);
+    const bool early = int64_t(part_rows) * kv_heads * (head_dim * 4) > codec::kEarlyThroughBytes;
+    return (early ? 1 : 0) | (codec::last_rows_through(kv_heads) ? 2 : 0);
 }
 
 const unsigned char *image_blob() { return plan.blob.data(); }

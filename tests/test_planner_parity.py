@@ -686,15 +686,13 @@ def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts):
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("kv_heads", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 36, 64])
 def test_which_rows_are_written_through(kv_heads, d):
-    """The rule by the plan's partial rows and KV heads: last rows only where eight does not divide the heads, and never
-    those of a small plan."""
-    per_mb, aligned = (1 << 20) / (kv_heads * d * 4), kv_heads % 8 == 0
-    for rows in (0, 1, int(per_mb), int(3 * per_mb)):
-        assert rows_through(rows, kv_heads, d) == (False, False)
-    for rows in (int(3 * per_mb) + 1, int(8 * per_mb)):
-        assert rows_through(rows, kv_heads, d) == (False, not aligned)
+    """The rule by the plan's partial rows and KV heads: rows with tasks to follow beyond 8 MB, last rows where eight does
+    not divide the heads."""
+    per_mb = (1 << 20) / (kv_heads * d * 4)
+    for rows in (1, int(3 * per_mb), int(8 * per_mb)):
+        assert rows_through(rows, kv_heads, d) == (False, kv_heads % 8 != 0)
     for rows in (int(8 * per_mb) + 1, int(31 * per_mb), 2 ** 31 - 1):
-        assert rows_through(rows, kv_heads, d) == (True, not aligned)
+        assert rows_through(rows, kv_heads, d) == (True, kv_heads % 8 != 0)
 
 
 @pytest.mark.parametrize("d,hq,hkv,requests,lens,slices,early,last", ROW_STORES)

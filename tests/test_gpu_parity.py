@@ -224,6 +224,25 @@ def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts, dt
     check(w, **opts)
 
 
+@pytest.mark.parametrize("group,requests", [(5, 13), (8, 12), (1, 97), (8, 16), (3, 43), (8, 20), (8, 25), (15, 17), (8, 32)])
+@pytest.mark.parametrize("opts", [{"num_slots": 2}, {"num_slots": 2, "fused": 1}, {"num_slots": 3, "schedule": 1}])
+def test_dense_packs_of_64_channels(group, requests, opts):
+    """Packs of 65 .. 256 rows of 64 channels: the dense path's blocks of 64 tokens, edges of row groups of 32, of one
+    block, of the ring (512 tokens) and of the length from which two waves share a row group (1024, up to 128 rows)."""
+    C = _C()
+    rows = group * requests
+    lens = [1, 63, 64, 65, 447, 448, 449, 511, 512, 513, 1023, 1024, 1088, 1089, 1216, 1300]
+    f = Forest(np.full(len(lens), -1), np.array(lens), np.repeat(np.arange(len(lens)), requests))
+    w = make_workload(f"dense64-{group}-{requests}", f, HeadConfig(2 * group, 2, 64, DTYPE_FP16 if requests % 2 else DTYPE_BF16),
+                      seed=1600 + rows, poison=True, layout="htd" if requests % 4 else "thd")
+    opts = dict(opts, split_align=2048)
+    check(w, **opts)
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cpu", **opts)
+    widest = max(t["n_req"] * group for t in pa.export()["tasks"])
+    assert C.codec_plan_device_bytes(pa.plan) < _image_bytes_without_packs(pa.export(), w.paged, w.head) and widest <= 32 < rows
+    pa.close()
+
+
 @pytest.mark.parametrize("d,hq,hkv,length,samples", [(256, 16, 8, 256, 16), (256, 16, 8, 1024, 32), (256, 32, 8, 200, 16),
                                                      (64, 16, 8, 500, 32)])
 @pytest.mark.parametrize("opts", [{}, {"schedule": 1}, {"fused": 1}, {"share": 2, "schedule": 2, "fused": 2, "extensions": 3}])

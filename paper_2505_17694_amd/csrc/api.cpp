@@ -209,6 +209,8 @@ codec::MergeParams merge_params(const codec_plan_t *plan, const void *workspace,
     mp.req_part_off = reinterpret_cast<const int32_t *>(meta + L.req_part_off);
     mp.req_part = reinterpret_cast<const int32_t *>(meta + L.req_part);
     mp.req_inline = reinterpret_cast<const int32_t *>(meta + L.req_inline);
+    mp.req_line = reinterpret_cast<const int32_t *>(meta + L.req_line);
+    mp.split_waves = L.split_waves;
     mp.out = out;
     mp.num_requests = d.num_requests;
     mp.h_q = d.head.num_q_heads;

@@ -1784,9 +1784,10 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 }
 
 // Partial output reduction (Alg. 3), n-ary: one wave folds the partials of RPW consecutive query heads
-// of one request (hq .. hq + RPW - 1, all of one KV head) in list order.  Partials are taken eight or
-// fifteen at a time: their loads are issued together, then they are folded against their common maximum
-// (by associativity of the reduction this equals any binary bracketing).
+// of one request (hq .. hq + RPW - 1, all of one KV head) in list order.  Partials are taken in chunks, the first fifteen
+// of a list, then eight at a time: their loads are issued together, they are summed up against the maximum so far, and
+// the sum is added to what the chunks before came to (by associativity of the reduction this equals any binary
+// bracketing).  merge_split_kernel has the same chunks and the same rounding: the forms agree bit for bit.
 //
 // RPW = 1: each lane owns D / 64 channels of the one row.  RPW = 256 / D (the reduction kernel, when
 // the group size allows it): each lane owns four channels of one of the rows; the rows of consecutive
@@ -1796,10 +1797,11 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 // in flight whatever it moves.  For the same reason it loads only the partials that exist (inside the
 // attention kernel, single-launch mode, every slot of a round is loaded: rows behind the end of a list
 // read as row 0, which is valid memory, and the straight-line code keeps that kernel as it is).
+constexpr int kFoldChunk = 8;
 template <int DT, bool COHERENT, int D, int RPW = 1>
 __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, int wave_lane)
 {
-    constexpr int kChunk = 8;
+    constexpr int kChunk = kFoldChunk;
     constexpr int LPR = 64 / RPW;       // lanes per row
     constexpr int CPL = D / LPR;        // channels per lane: 1, 2 or 4
     static_assert(CPL == 1 || CPL == 2 || CPL == 4, "channels per lane");
@@ -1808,7 +1810,8 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
     const int head = hq / P.group, hj = hq - head * P.group;
     // The request's line: its number of partial rows and the first kInlineParts of them, read together
     // (no address waits for another read).  Lists of up to eight rows, and of up to kInlineParts, are
-    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.
+    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.  (Small
+    // launches with lists of 24 rows and more take merge_split_kernel.)
     const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
     const int total = line[0];
     int first[kInlineParts];
@@ -1818,7 +1821,7 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
     float M = -INFINITY, L = 0.f, acc[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-    auto fold = [&](const int *rows, int cnt, auto width) {
+    auto fold = [&](const int *rows, int cnt, auto width, auto later) {
         constexpr int N = decltype(width)::value;
         float2 ml[N];
         float o[N][CPL];
@@ -1865,24 +1868,27 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
 #pragma unroll
         for (int j = 0; j < N; ++j)
             if (j < cnt) mm = fmaxf(mm, ml[j].x);
-        const float wa = weight(M, mm);
-        L *= wa;
+        float l = 0.f, sum[CPL];
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= wa;
+        for (int c = 0; c < CPL; ++c) sum[c] = 0.f;
 #pragma unroll
         for (int j = 0; j < N; ++j)
             if (j < cnt) {
-                const float wb = weight(ml[j].x, mm);
-                L += ml[j].y * wb;
+                const float w = weight(ml[j].x, mm);
+                l = __builtin_fmaf(ml[j].y, w, l);
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] += o[j][c] * wb;
+                for (int c = 0; c < CPL; ++c) sum[c] = __builtin_fmaf(o[j][c], w, sum[c]);
             }
+        const float before = decltype(later)::value ? weight(M, mm) : 0.f;
+        L = decltype(later)::value ? __builtin_fmaf(L, before, l) : l;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] = decltype(later)::value ? __builtin_fmaf(acc[c], before, sum[c]) : sum[c];
         M = mm;
     };
     if (total <= kChunk) {
-        fold(first, total, std::integral_constant<int, kChunk>{});
+        fold(first, total, std::integral_constant<int, kChunk>{}, std::false_type{});
     } else {
-        fold(first, total < kInlineParts ? total : kInlineParts, std::integral_constant<int, kInlineParts>{});
+        fold(first, total < kInlineParts ? total : kInlineParts, std::integral_constant<int, kInlineParts>{}, std::false_type{});
         if (total > kInlineParts) {
             const int32_t *list = P.req_part + P.req_part_off[r];
 #pragma unroll 1
@@ -1891,7 +1897,7 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
                 int rows[kChunk];
 #pragma unroll
                 for (int j = 0; j < kChunk; ++j) rows[j] = list[base + (j < cnt ? j : 0)];
-                fold(rows, cnt, std::integral_constant<int, kChunk>{});
+                fold(rows, cnt, std::integral_constant<int, kChunk>{}, std::true_type{});
             }
         }
     }
@@ -1921,6 +1927,113 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
     if (unit >= P.num_requests * per_req) return;
     const int r = unit / per_req;
     merge_one<DT, false, D, RPW>(P, r, blockIdx.x * P.group + (unit - r * per_req) * RPW, threadIdx.x & 63);
+}
+
+// The same for plans with lists of 24 rows and more whose launch is small (split_waves), which is bound by its chain of
+// dependent reads: one wave makes four or five for a list of 32 (line, fifteen rows, CSR entries and eight rows, twice).
+// Here WAVES waves take a chunk each, wave 0 the first, after two dependent reads (line, rows), and their sums meet in LDS.
+// The references of all rows up to the end of its chunk, whose maximum a chunk's sum refers to, are read by every wave, a
+// row per lane.  us per step, one wave / split: a lone request of 8191 tokens, 32 / 8 heads, 32 partials 14.9 / 13.5;
+// one KV head, a two-level tree of three requests, 58 partials 21.6 / 13.4; 24 requests, 48 partials 31.6 / 27.2.  Measured
+// and dropped: the sums of the waves against references of their own (12.9, but the single launch, which has to round
+// alike, then took up to 16 % longer); the rows handed over through LDS as they are and folded there (14.4).
+template <int DT, int D, int RPW, int WAVES>
+__global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergeParams P)
+{
+    constexpr int LPR = 64 / RPW, CPL = D / LPR;
+    __shared__ float sums[WAVES - 1][CPL + 2][64];
+    const int per_req = P.group / RPW;
+    const int unit = blockIdx.z * gridDim.y + blockIdx.y;
+    if (unit >= P.num_requests * per_req) return;
+    const int r = unit / per_req;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave_lane = threadIdx.x & 63;
+    const int lane = wave_lane % LPR;
+    const int hj = (unit - r * per_req) * RPW + wave_lane / LPR;
+    const int32_t *line = P.req_line + int64_t(r) * split_line_words(WAVES);
+    const int total = line[0];
+    const int32_t *list = line + 1;
+    const int64_t head_base = int64_t(blockIdx.x) * P.part_rows + hj;
+    float M = -INFINITY, L = 0.f, acc[CPL] = {};        // the wave's chunk; wave 0: all chunks so far
+
+    // rows begin .. begin + cnt - 1 of the list, cnt at most N
+    auto fold = [&](int begin, int cnt, auto width) {
+        constexpr int N = decltype(width)::value;
+        float2 ml[N];
+        float o[N][CPL];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            if (j >= cnt) continue;                     // wave-uniform: no load for a partial that does not exist
+            const int64_t prow = head_base + list[begin + j];
+            ml[j] = *reinterpret_cast<const float2 *>(P.part_ml + prow * 2);
+            const float *src = P.part_o + prow * D + lane * CPL;
+            if constexpr (CPL == 4) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(src);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) o[j][c] = x[c];
+            } else {
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) o[j][c] = src[c];
+            }
+        }
+#pragma unroll 1
+        for (int j = lane; j < begin + cnt; j += LPR) M = fmaxf(M, P.part_ml[(head_base + list[j]) * 2]);
+#pragma unroll
+        for (int d = 1; d < LPR; d *= 2) M = fmaxf(M, __shfl_xor(M, d));
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j < cnt) {
+                const float w = weight(ml[j].x, M);
+                L = __builtin_fmaf(ml[j].y, w, L);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(o[j][c], w, acc[c]);
+            }
+    };
+    int base = kInlineParts;                            // first row of wave 1's chunk
+    if (wave == 0) fold(0, kInlineParts < total ? kInlineParts : total, std::integral_constant<int, kInlineParts>{});
+#pragma unroll 1
+    for (;;) {                                          // one round, but for lists of more than split_rows(WAVES)
+        if (wave > 0) {
+            const int begin = base + (wave - 1) * kFoldChunk, cnt = total - begin < kFoldChunk ? total - begin : kFoldChunk;
+            if (cnt > 0) {
+                M = -INFINITY;
+                L = 0.f;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+                fold(begin, cnt, std::integral_constant<int, kFoldChunk>{});
+                float (*put)[64] = sums[wave - 1];
+                put[CPL][wave_lane] = L;
+                put[CPL + 1][wave_lane] = M;
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) put[c][wave_lane] = acc[c];
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 0; w < WAVES - 1; ++w) {
+                if (base + w * kFoldChunk >= total) break;
+                const float m = sums[w][CPL + 1][wave_lane], before = weight(M, m);
+                L = __builtin_fmaf(L, before, sums[w][CPL][wave_lane]);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(acc[c], before, sums[w][c][wave_lane]);
+                M = m;
+            }
+        }
+        base += (WAVES - 1) * kFoldChunk;
+        if (base >= total) break;
+        list = P.req_part + P.req_part_off[r];
+        __syncthreads();                                // the sums of this round have been read
+    }
+    if (wave > 0) return;
+    const float inv = 1.f / L;
+    char *out = static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + blockIdx.x * P.group + hj) * D + lane * CPL) * 2;
+    if constexpr (CPL == 1) {
+        *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(acc[0] * inv, 0.f) & 0xFFFFu);
+    } else {
+#pragma unroll
+        for (int c = 0; c < CPL; c += 2)
+            *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(acc[c] * inv, acc[c + 1] * inv);
+    }
 }
 
 // ---- single-launch mode: the reduction inside the attention launch (Sec. 4.3, parallel reduction) ----
@@ -2276,10 +2389,20 @@ void launch_merge_of(const MergeParams &p, hipStream_t s)
     const bool wide = kWide > 1 && p.group % kWide == 0;
     const int units = p.num_requests * (p.group / (wide ? kWide : 1));     // per KV head
     constexpr unsigned kMaxY = 32768;
-    const unsigned groups = unsigned((units + kMergeWaves - 1) / kMergeWaves), y = groups < kMaxY ? groups : kMaxY;
-    const dim3 grid(unsigned(p.h_q / p.group), y, (groups + y - 1) / y), block(kMergeWaves * 64);
-    if (wide) hipLaunchKernelGGL((merge_kernel<DT, D, kWide>), grid, block, 0, s, p);
-    else      hipLaunchKernelGGL((merge_kernel<DT, D, 1>), grid, block, 0, s, p);
+    auto launch = [&](auto kernel, int units_of, int waves) {               // of a workgroup
+        const unsigned groups = unsigned((units + units_of - 1) / units_of), y = groups < kMaxY ? groups : kMaxY;
+        const dim3 grid(unsigned(p.h_q / p.group), y, (groups + y - 1) / y), block(waves * 64);
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, p);
+    };
+    auto split = [&](auto waves) {
+        constexpr int W = decltype(waves)::value;
+        if (wide) launch(merge_split_kernel<DT, D, kWide, W>, 1, W);
+        else      launch(merge_split_kernel<DT, D, 1, W>, 1, W);
+    };
+    if (p.split_waves == 4)      split(std::integral_constant<int, 4>{});
+    else if (p.split_waves == 8) split(std::integral_constant<int, 8>{});
+    else if (wide) launch(merge_kernel<DT, D, kWide>, kMergeWaves, kMergeWaves);
+    else           launch(merge_kernel<DT, D, 1>, kMergeWaves, kMergeWaves);
 }
 
 int launch_merge(const MergeParams &p, int dtype, int head_dim, void *stream)

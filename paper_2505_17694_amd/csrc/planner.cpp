@@ -310,6 +310,11 @@ void build_device_image(PlanData &p)
     L.req_part_off = place(p.req_part_off.size() * 4);
     L.req_part = place(p.req_part.size() * 4);
     L.req_inline = place(size_t(p.num_requests) * (kInlineParts + 1) * 4);
+    int32_t longest_list = 0;
+    for (int32_t r = 0; r < p.num_requests; ++r) longest_list = std::max(longest_list, p.req_part_off[r + 1] - p.req_part_off[r]);
+    L.split_waves = split_waves(longest_list, p.num_requests, p.head.num_q_heads, p.group, p.head.head_dim);
+    const int32_t line_words = L.split_waves ? split_line_words(L.split_waves) : 0;
+    L.req_line = place(size_t(p.num_requests) * line_words * 4);
     if (p.schedule == 2)        // by the entries and slots that run
         p.schedule = L.num_entries >= int64_t(packed ? kAutoQueueEntriesPerSlotPacked : kAutoQueueEntriesPerSlot) * L.num_slots ? 1 : 0;
     L.queue_off = place(queue_off.size() * 4);
@@ -399,6 +404,12 @@ void build_device_image(PlanData &p)
             const int32_t e0 = p.req_part_off[r], cnt = p.req_part_off[r + 1] - e0;
             line[0] = cnt;
             for (int32_t j = 0; j < kInlineParts; ++j) line[1 + j] = j < cnt ? p.req_part[e0 + j] : 0;
+        }
+        line = reinterpret_cast<int32_t *>(p.blob.data() + L.req_line);
+        for (int32_t r = 0; r < p.num_requests && line_words; ++r, line += line_words) {     // zero behind the end
+            const int32_t e0 = p.req_part_off[r], cnt = p.req_part_off[r + 1] - e0;
+            line[0] = cnt;
+            std::copy_n(p.req_part.begin() + e0, std::min(cnt, split_rows(L.split_waves)), line + 1);
         }
     }
     put(L.queue_off, queue_off);

@@ -92,16 +92,36 @@ constexpr bool last_rows_through(int32_t kv_heads) { return (kv_heads & 7) != 0;
 // from the CSR arrays.  One dependent read less than offset -> list -> partial rows.
 constexpr int32_t kInlineParts = 15;
 
+// Waves that share a list in the split form of the reduction (merge_split_kernel), the first fifteen rows and eight each
+// round; 0: one wave folds a list.  By the longest list and by the waves of the launch, as a wave whose part of a list is
+// empty still has to start.  Drawn plans, whole steps, time with the split form over time with one wave per list:
+// lists of 16 .. 23 rows (two waves) 73 plans 0.997 (0.915 .. 1.043), 24 .. 39 rows (four) 37 plans 0.965 (0.873 .. 1.016),
+// more (eight) 13 plans 0.88 (0.62 .. 0.98).  By waves, a variant with up to eight waves: 2048 .. 16383 217 plans 0.964
+// (0.593 .. 1.015), 16384 .. 32767 69 plans 0.997 (up to 1.030), 32768 .. 65535 59 plans 1.018 (up to 1.128), more 1.13
+// (up to 1.60).
+constexpr int32_t kSplitMinList = 24;
+constexpr int64_t kSplitMaxWaves = 16383;
+constexpr int32_t split_rows(int32_t waves) { return kInlineParts + 8 * (waves - 1); }     // of a list, that a round reads
+constexpr int32_t split_waves(int32_t longest_list, int32_t num_requests, int32_t h_q, int32_t group, int32_t head_dim)
+{
+    const int32_t waves = longest_list < kSplitMinList ? 0 : longest_list <= split_rows(4) ? 4 : 8;
+    const int32_t heads = 256 / head_dim > 1 && group % (256 / head_dim) == 0 ? 256 / head_dim : 1;  // rows of a wave
+    return int64_t(num_requests) * (h_q / heads) * waves <= kSplitMaxWaves ? waves : 0;
+}
+// Words of a request's line for the split form: its list's length and first rows.
+constexpr int32_t split_line_words(int32_t waves) { return (1 + split_rows(waves) + 15) / 16 * 16; }
+
 // Byte offsets of the arrays inside the device metadata blob.
 struct DevLayout {
     size_t slot_recs = 0, slot_off = 0, node_q = 0, page_ids = 0,
-           req_part_off = 0, req_part = 0, req_inline = 0, queue_off = 0, queue_recs = 0, counters = 0,
+           req_part_off = 0, req_part = 0, req_inline = 0, req_line = 0, queue_off = 0, queue_recs = 0, counters = 0,
            arrive = 0,      // [h_kv][num_requests] partial results arrived (single-launch mode), zero between launches
            nodeq_mask = 0,  // per entry of node_q: first word of that request's mask if the node ends the request, else -1
            mask_words = 0,
            total = 0;
     int32_t num_entries = 0;    // entries of the run-time queue as the kernels see it
     int32_t num_slots = 0;      // workgroups per KV head
+    int32_t split_waves = 0;    // split_waves() of the plan
 };
 
 // Lists of task indices with their offsets.

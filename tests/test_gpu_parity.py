@@ -670,6 +670,24 @@ def test_reduction_lists_of_every_length(slices):
     assert lens == ({2} if slices == 1 else {slices + 1, slices + 2}), lens
 
 
+@pytest.mark.parametrize("parts", [15, 16, 23, 24, 25, 39, 40, 71, 72, 127, 128, 195])
+@pytest.mark.parametrize("d,hq,hkv,requests", [(128, 32, 8, 2), (128, 7, 1, 3), (64, 16, 2, 3), (64, 3, 3, 5), (256, 10, 2, 2), (128, 8, 2, 600)])
+def test_split_reduction(parts, d, hq, hkv, requests):
+    """Lists around the edges of the split form (24 .. 39 and up to 71 rows by 4 and 8 waves, further rounds of 56 rows),
+    beside requests with one partial, in every width of a wave's rows; 600 requests with eight waves per list are more
+    than the form takes.  Two launches and one (which folds a list with one wave) agree bit for bit."""
+    C = _C()
+    f = concat_forests(Forest(np.array([-1]), np.array([32 * parts - 7]), np.zeros(requests, np.int64)), unshared_forest([19, 32]))
+    w = make_workload(f"split-{parts}-{d}", f, HeadConfig(hq, hkv, d, DTYPE_FP16 if parts % 2 and d > 64 else DTYPE_BF16),
+                      seed=1700 + parts + d, poison=True, layout="htd")
+    opts = {"num_slots": 5, "split_align": 32, "fixed_slices": parts}
+    sel = [(r, h) for r in sorted({0, 1, requests - 1, requests, requests + 1}) for h in range(hq)]
+    got, view = check(w, sel=sel if requests > 100 else None, **opts)
+    assert int(np.max(np.diff(view["req_part_off"]))) == parts
+    one, _ = run_gpu(w, 1, fused=1, **opts)
+    assert np.array_equal(one, got)
+
+
 def _queue_cases():
     short = [7, 40, 2048, 33, 2049, 64, 300, 5, 3000, 96, 17, 1000, 31, 640, 1, 129] * 3
     dense = two_level_forest(1, [43] * 17)

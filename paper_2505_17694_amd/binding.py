@@ -283,9 +283,8 @@ def codec_decode_attention(plan, q_ptr: int, k_ptr: int, v_ptr: int, num_pages: 
                            page_stride: int, token_stride: int, head_stride: int, out_ptr: int,
                            workspace_ptr: int, workspace_bytes: int, stream: int = 0) -> int:
     lay = codec_kv_layout(num_pages, page_stride, token_stride, head_stride)
-    return _lib.codec_decode_attention(plan, c_void_p(q_ptr), c_void_p(k_ptr), c_void_p(v_ptr),
-                                       byref(lay), c_void_p(out_ptr), c_void_p(workspace_ptr),
-                                       workspace_bytes, c_void_p(stream))
+    # integers as they are: the declared argument types convert them
+    return _lib.codec_decode_attention(plan, q_ptr, k_ptr, v_ptr, lay, out_ptr, workspace_ptr, workspace_bytes, stream)
 
 
 def codec_partial_attention(plan, q_ptr: int, k_ptr: int, v_ptr: int, num_pages: int,

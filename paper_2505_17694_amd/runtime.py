@@ -6,6 +6,11 @@ import torch
 from . import binding as B
 
 
+def _current_stream(device: torch.device) -> int:
+    """Handle of PyTorch's current stream on `device`, without the Stream object around it."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 class PlannedAttention:
     """Owns a codec plan plus its device metadata and workspace tensors.
 
@@ -73,6 +78,9 @@ class PlannedAttention:
         p, h = self.paged, self.head
         last = ((p.num_pages - 1) * p.page_stride + (h.page_size - 1) * p.token_stride
                 + (h.num_kv_heads - 1) * p.head_stride + h.head_dim)
+        # a contiguous tensor holds all its elements from its first one on
+        if pool.is_contiguous() and pool.numel() >= last and pool.element_size() == 2 and pool.device == self.device:
+            return
         have = pool.untyped_storage().nbytes() // pool.element_size() - pool.storage_offset()
         if pool.device != self.device or pool.element_size() != 2 or last > have:
             raise ValueError(f"{what}: {have} elements from the tensor's first one on {pool.device}, "
@@ -83,8 +91,7 @@ class PlannedAttention:
         h = self.head
         want = (self.num_requests, h.num_q_heads, h.head_dim)
         dtype = torch.float16 if h.dtype == B.CODEC_DTYPE_FP16 else torch.bfloat16
-        if (tuple(t.shape) != want or t.dtype != dtype or t.device != self.device
-                or not t.is_contiguous()):
+        if t.shape != want or t.dtype != dtype or t.device != self.device or not t.is_contiguous():
             raise ValueError(f"{what}: need a contiguous {dtype} tensor of shape {want} on {self.device}, "
                              f"got {t.dtype} {tuple(t.shape)} on {t.device}, contiguous={t.is_contiguous()}")
 
@@ -95,8 +102,9 @@ class PlannedAttention:
         self._check_rows(q, "q")
         if out is None:
             out = torch.empty_like(q)
-        self._check_rows(out, "out")
-        s = (stream or torch.cuda.current_stream(self.device)).cuda_stream
+        else:
+            self._check_rows(out, "out")
+        s = stream.cuda_stream if stream else _current_stream(self.device)
         p = self.paged
         st = B.codec_decode_attention(self.plan, q.data_ptr(), k_pool.data_ptr(), v_pool.data_ptr(),
                                       p.num_pages, p.page_stride, p.token_stride, p.head_stride,
@@ -110,7 +118,7 @@ class PlannedAttention:
         self._check_pool(k_pool, "k_pool")
         self._check_pool(v_pool, "v_pool")
         self._check_rows(q, "q")
-        s = (stream or torch.cuda.current_stream(self.device)).cuda_stream
+        s = stream.cuda_stream if stream else _current_stream(self.device)
         p = self.paged
         st = B.codec_partial_attention(self.plan, q.data_ptr(), k_pool.data_ptr(), v_pool.data_ptr(),
                                        p.num_pages, p.page_stride, p.token_stride, p.head_stride,
@@ -120,7 +128,7 @@ class PlannedAttention:
 
     def partial_reduction(self, out, stream=None) -> None:
         self._check_rows(out, "out")
-        s = (stream or torch.cuda.current_stream(self.device)).cuda_stream
+        s = stream.cuda_stream if stream else _current_stream(self.device)
         st = B.codec_partial_reduction(self.plan, self.workspace.data_ptr(), self.workspace.numel(),
                                        out.data_ptr(), s)
         if st != B.CODEC_OK:

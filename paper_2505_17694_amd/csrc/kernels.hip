@@ -1787,31 +1787,21 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 // of one request (hq .. hq + RPW - 1, all of one KV head) in list order.  Partials are taken in chunks, the first fifteen
 // of a list, then eight at a time: their loads are issued together, they are summed up against the maximum so far, and
 // the sum is added to what the chunks before came to (by associativity of the reduction this equals any binary
-// bracketing).  merge_split_kernel has the same chunks and the same rounding: the forms agree bit for bit.
+// bracketing).  All forms of the reduction have the same chunks and the same rounding: they agree bit for bit.
 //
-// RPW = 1: each lane owns D / 64 channels of the one row.  RPW = 256 / D (the reduction kernel, when
-// the group size allows it): each lane owns four channels of one of the rows; the rows of consecutive
-// heads are neighbours in the partial arrays and in the output, so every load of partial rows is one
-// full 1 KB instruction and a reduction costs half (a quarter for 64 channels) the memory instructions
-// per row.  The kernel is bound by those: each takes a place in the CU's queue of memory instructions
-// in flight whatever it moves.  For the same reason it loads only the partials that exist (inside the
-// attention kernel, single-launch mode, every slot of a round is loaded: rows behind the end of a list
-// read as row 0, which is valid memory, and the straight-line code keeps that kernel as it is).
+// merge_one is the form inside the attention kernel (single-launch mode): RPW = 1, each lane owns D / 64 channels of the
+// one row, and every slot of a round is loaded: rows behind the end of a list read as row 0, which is valid memory, and
+// the straight-line code keeps that kernel as it is.
 constexpr int kFoldChunk = 8;
-template <int DT, bool COHERENT, int D, int RPW = 1>
+template <int DT, int D>
 __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, int wave_lane)
 {
     constexpr int kChunk = kFoldChunk;
-    constexpr int LPR = 64 / RPW;       // lanes per row
-    constexpr int CPL = D / LPR;        // channels per lane: 1, 2 or 4
-    static_assert(CPL == 1 || CPL == 2 || CPL == 4, "channels per lane");
-    const int lane = wave_lane % LPR;   // the lane's place in its row
-    hq += wave_lane / LPR;              // the lane's row
+    constexpr int CPL = D / 64;         // channels per lane: 1, 2 or 4
     const int head = hq / P.group, hj = hq - head * P.group;
     // The request's line: its number of partial rows and the first kInlineParts of them, read together
     // (no address waits for another read).  Lists of up to eight rows, and of up to kInlineParts, are
-    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.  (Small
-    // launches with lists of 24 rows and more take merge_split_kernel.)
+    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.
     const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
     const int total = line[0];
     int first[kInlineParts];
@@ -1827,40 +1817,18 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
         float o[N][CPL];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            if constexpr (!COHERENT)        // the reduction kernel: no load for a partial that does not exist
-                if (j >= cnt) {             // (wave-uniform)
-                    ml[j] = float2{0.f, 0.f};
-#pragma unroll
-                    for (int c = 0; c < CPL; ++c) o[j][c] = 0.f;
-                    continue;
-                }
             const int64_t prow = head_base + rows[j];
-            const float *src = P.part_o + prow * D + lane * CPL;
-            if constexpr (COHERENT) {       // rows written by other workgroups of this launch
-                ml[j] = ld8_device(P.part_ml + prow * 2);
-                if constexpr (CPL == 1) {
-                    o[j][0] = __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const unsigned int *>(src),
-                                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                } else {
-#pragma unroll
-                    for (int c = 0; c < CPL; c += 2) {
-                        const float2 x = ld8_device(src + c);
-                        o[j][c] = x.x;
-                        o[j][c + 1] = x.y;
-                    }
-                }
+            const float *src = P.part_o + prow * D + wave_lane * CPL;
+            ml[j] = ld8_device(P.part_ml + prow * 2);       // rows written by other workgroups of this launch
+            if constexpr (CPL == 1) {
+                o[j][0] = __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const unsigned int *>(src),
+                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             } else {
-                ml[j] = *reinterpret_cast<const float2 *>(P.part_ml + prow * 2);
-                if constexpr (CPL == 1) {
-                    o[j][0] = *src;
-                } else if constexpr (CPL == 2) {
-                    const float2 x = *reinterpret_cast<const float2 *>(src);
-                    o[j][0] = x.x;
-                    o[j][1] = x.y;
-                } else {
-                    const f32x4 x = *reinterpret_cast<const f32x4 *>(src);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) o[j][c] = x[c];
+                for (int c = 0; c < CPL; c += 2) {
+                    const float2 x = ld8_device(src + c);
+                    o[j][c] = x.x;
+                    o[j][c + 1] = x.y;
                 }
             }
         }
@@ -1902,7 +1870,7 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
         }
     }
     const float inv = 1.f / L;
-    char *out = static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + hq) * D + lane * CPL) * 2;
+    char *out = static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + hq) * D + wave_lane * CPL) * 2;
     if constexpr (CPL == 1) {
         *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(acc[0] * inv, 0.f) & 0xFFFFu);
     } else {
@@ -1911,6 +1879,110 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
             *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(acc[c] * inv, acc[c + 1] * inv);
     }
 }
+
+// The reduction kernels.  A wave takes RPW = 256 / D consecutive query heads of a request where the rows of a KV head's
+// group divide that evenly (else RPW = 1, as above): each lane owns four channels of one of the rows; they are
+// neighbours in the partial arrays and in the output, so every load of partial rows is one full 1 KB instruction and a
+// reduction costs half (a quarter for 64 channels) the memory instructions per row.  Large launches are bound by those: each
+// takes a place in the CU's queue of memory instructions in flight whatever it moves.  For the same reason only the
+// partials that exist are loaded.  Small launches are bound by the chain of dependent reads and by the code between them:
+// merge_kernel has what is the same for the wave, the request's line and the addresses of its rows, read and worked out by
+// the scalar unit, and reads rows sixteen to 23 beside the first fifteen.  Time against a form with all of that in vector
+// registers and rows in rounds, whole steps of drawn plans: lists of up to eight rows, steps of 8 .. 16 us 0.986 (40
+// plans, the best 0.956), 16 .. 32 us 0.990; 16 .. 23 rows 0.979 and 0.986 (the best 0.932); larger steps 0.997 .. 1.000.
+
+// A chunk of a row's partials.
+template <int N, int CPL>
+struct Chunk {
+    float2 ml[N];
+    float o[N][CPL];
+
+    template <class Rows>
+    __device__ __forceinline__ void load(const MergeParams &P, const Rows &at, const int *rows, int cnt)
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            ml[j] = float2{0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) o[j][c] = 0.f;
+            if (j < cnt) at.load(P, rows[j], ml[j], o[j]);      // wave-uniform
+        }
+    }
+    __device__ __forceinline__ float top(float m, int cnt) const
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j < cnt) m = fmaxf(m, ml[j].x);
+        return m;
+    }
+    // against a reference.  (fmaf written out here and above: the compiler has no choice to make.)
+    __device__ __forceinline__ void sum_up(int cnt, float reference, float &l, float (&sum)[CPL]) const
+    {
+        l = 0.f;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) sum[c] = 0.f;
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (j < cnt) {
+                const float w = weight(ml[j].x, reference);
+                l = __builtin_fmaf(ml[j].y, w, l);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) sum[c] = __builtin_fmaf(o[j][c], w, sum[c]);
+            }
+    }
+};
+
+// The rows of a wave and the place of its lanes in them.
+template <int DT, int D, int RPW>
+struct WaveRows {
+    static constexpr int LPR = 64 / RPW;        // lanes per row
+    static constexpr int CPL = D / LPR;         // channels per lane
+    static_assert(CPL == 1 || CPL == 2 || CPL == 4, "channels per lane");
+    int lane, row;                              // the lane's place in its row, which is row `row` of the wave
+    uint32_t off_o, off_ml;                     // bytes behind the first of the wave's rows
+    int64_t head_base;                          // the first of the wave's rows lies at head_base + an entry of the list
+    char *out;
+
+    __device__ __forceinline__ WaveRows(const MergeParams &P, int head, int r, int hj)
+    {
+        const int wave_lane = threadIdx.x & 63;
+        lane = wave_lane % LPR;
+        row = wave_lane / LPR;
+        off_o = uint32_t(row * D + lane * CPL) * 4;
+        off_ml = uint32_t(row) * 8;
+        head_base = int64_t(head) * P.part_rows + hj;
+        out = static_cast<char *>(P.out) + (int64_t(r) * P.h_q + int64_t(head) * P.group + hj) * (D * 2) + off_o / 2;
+    }
+    __device__ __forceinline__ void load(const MergeParams &P, int entry, float2 &ml, float (&o)[CPL]) const
+    {
+        const int64_t prow = head_base + entry;
+        ml = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(P.part_ml + prow * 2) + off_ml);
+        const char *src = reinterpret_cast<const char *>(P.part_o + prow * D) + off_o;
+        if constexpr (CPL == 1) {
+            o[0] = *reinterpret_cast<const float *>(src);
+        } else if constexpr (CPL == 2) {
+            const float2 x = *reinterpret_cast<const float2 *>(src);
+            o[0] = x.x;
+            o[1] = x.y;
+        } else {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(src);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = x[c];
+        }
+    }
+    // normalised, rounded
+    __device__ __forceinline__ void store(float l, const float (&sum)[CPL]) const
+    {
+        const float inv = 1.f / l;
+        if constexpr (CPL == 1) {
+            *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(sum[0] * inv, 0.f) & 0xFFFFu);
+        } else {
+#pragma unroll
+            for (int c = 0; c < CPL; c += 2)
+                *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(sum[c] * inv, sum[c + 1] * inv);
+        }
+    }
+};
 
 // blockIdx.x is the KV head.  Workgroups are dealt to the eight XCDs in turn, here and in the attention kernel, so
 // with eight heads the rows of a head are read through the L2 that holds them.  In order of requests that is so only
@@ -1922,11 +1994,62 @@ __device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, i
 template <int DT, int D, int RPW>
 __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergeParams P)
 {
+    using W = WaveRows<DT, D, RPW>;
+    constexpr int CPL = W::CPL;
     const int per_req = P.group / RPW;          // the launch has checked that RPW divides the group size
-    const int unit = (blockIdx.z * gridDim.y + blockIdx.y) * kMergeWaves + (threadIdx.x >> 6);
+    const int unit = (blockIdx.z * gridDim.y + blockIdx.y) * kMergeWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (unit >= P.num_requests * per_req) return;
     const int r = unit / per_req;
-    merge_one<DT, false, D, RPW>(P, r, blockIdx.x * P.group + (unit - r * per_req) * RPW, threadIdx.x & 63);
+    const W at(P, blockIdx.x, r, (unit - r * per_req) * RPW);
+    // see merge_one; rows sixteen to 23 are read beside the first fifteen
+    const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
+    const int total = line[0], list_off = P.req_part_off[r];
+    int first[kInlineParts];
+#pragma unroll
+    for (int j = 0; j < kInlineParts; ++j) first[j] = line[1 + j];
+#pragma unroll
+    for (int j = 0; j < kInlineParts; ++j) asm volatile("" : : "s"(first[j]));  // the line is read whole, not its second half when it is wanted
+    asm volatile("" : : "s"(list_off));
+    float M, L, acc[CPL];
+    if (total <= kFoldChunk) {
+        Chunk<kFoldChunk, CPL> x;
+        x.load(P, at, first, total);
+        x.sum_up(total, x.top(-INFINITY, total), L, acc);
+    } else {
+        Chunk<kInlineParts, CPL> x;
+        const int cnt = total < kInlineParts ? total : kInlineParts;
+        x.load(P, at, first, cnt);
+        if (total <= kInlineParts) {
+            x.sum_up(cnt, x.top(-INFINITY, cnt), L, acc);
+        } else {
+            const int32_t *list = P.req_part + list_off;
+            int base = kInlineParts;
+            Chunk<kFoldChunk, CPL> y;
+            auto load_next = [&]() {
+                int rows[kFoldChunk];
+#pragma unroll
+                for (int j = 0; j < kFoldChunk; ++j) rows[j] = list[base + j];  // behind the list: what follows it in the metadata, unused
+                y.load(P, at, rows, total - base);
+            };
+            load_next();
+            M = x.top(-INFINITY, cnt);
+            x.sum_up(cnt, M, L, acc);
+#pragma unroll 1
+            for (;;) {
+                const float mm = y.top(M, total - base), before = weight(M, mm);
+                float l, sum[CPL];
+                y.sum_up(total - base, mm, l, sum);
+                L = __builtin_fmaf(L, before, l);
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(acc[c], before, sum[c]);
+                M = mm;
+                base += kFoldChunk;
+                if (base >= total) break;
+                load_next();
+            }
+        }
+    }
+    at.store(L, acc);
 }
 
 // The same for plans with lists of 24 rows and more whose launch is small (split_waves), which is bound by its chain of
@@ -2091,7 +2214,7 @@ __device__ __forceinline__ void task_delivered_by_workgroup(const PacParams &P, 
 #pragma unroll 1
         for (int i = wave; i < n; i += waves) {
             const int k = i / P.group;
-            merge_one<DT, true, D>(P.merge, ready[k], head * P.group + (i - k * P.group), threadIdx.x & 63);
+            merge_one<DT, D>(P.merge, ready[k], head * P.group + (i - k * P.group), threadIdx.x & 63);
         }
     }
     __syncthreads();                    // the list is done with before LDS is used again
@@ -2115,7 +2238,7 @@ __device__ __forceinline__ void task_delivered_by_wave(const PacParams &P, const
         ready &= ready - 1;
         const int r = __shfl(expected.x, src);
 #pragma unroll 1
-        for (int hj = 0; hj < P.group; ++hj) merge_one<DT, true, D>(P.merge, r, head * P.group + hj, lane);
+        for (int hj = 0; hj < P.group; ++hj) merge_one<DT, D>(P.merge, r, head * P.group + hj, lane);
     }
 }
 

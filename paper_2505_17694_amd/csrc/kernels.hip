@@ -2286,6 +2286,21 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     const bool many_rows = int64_t(P.part_rows) * P.h_kv * (D * 4) > kEarlyThroughBytes;
     const RowStore early = ARRIVES || P.arrive ? kRowsCoherent : many_rows ? kRowsThrough : kRowsPlain;
     const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(P.h_kv) ? kRowsThrough : kRowsPlain;
+    // The KV head for which the workgroup runs record i.  Where the heads of a token lie side by side ([token][head]
+    // pools), the rows of one head meet a subset of the memory channels, and not all heads as many: with a head
+    // of its own a workgroup of a slow head ends up to 20 % after the others.  Of plans whose rows go out finished the
+    // workgroups therefore take record i for the head i places on: every (record, head) is still run once, by the
+    // workgroups that run record i, and the slow heads are spread over all of them.  (Slices that other tasks read as
+    // well keep their head, whose L2 may hold them.)  Drawn plans of 100 .. 500 unshared contexts, time against fixed heads,
+    // [token][head] pools: 64 channels 8 plans 0.816 (0.756 .. 0.908), 128 channels and four or eight heads 30 plans 0.902
+    // (0.877 .. 0.961), 256 channels 11 plans 0.961; one head, or [head][token] pools, 142 plans 0.997 (0.985 .. 1.005).
+    // 256 contexts of 100 .. 4000 tokens, 28 / 4 heads 199.8 -> 185.5 us.
+    auto head_of = [&](const DevTask &t, int i) __attribute__((always_inline)) {
+        if constexpr (FINISH) {
+            if (t.flags & kTaskReadOnce) return int(uint32_t(head + i) % uint32_t(P.h_kv));
+        }
+        return head;
+    };
     // Runs the task records recs[t0 .. t1).  Tasks of more than 16 rows take the dense path (wide variant
     // only).  Tasks of at most 16 rows take the stream path, as a rule with all waves of the workgroup
     // as one team.  Runs of two or more short ones are handed out one wave each through a counter in
@@ -2312,8 +2327,9 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
 #pragma unroll 1
                 while (k < n) {
                     const DevTask mine = recs[i + k];
-                    if (mine.flags & kTaskReadOnce) run_stream<DT, true, 1, 1, D, FINISH>(P, mine, head, lds, 0, stage);
-                    else                run_stream<DT, false, 1, 1, D, FINISH>(P, mine, head, lds, 0, stage);
+                    const int own = head_of(mine, i + k);
+                    if (mine.flags & kTaskReadOnce) run_stream<DT, true, 1, 1, D, FINISH>(P, mine, own, lds, 0, stage);
+                    else                run_stream<DT, false, 1, 1, D, FINISH>(P, mine, own, lds, 0, stage);
                     if constexpr (FUSED)
                         if (P.arrive) task_delivered_by_wave<DT, D>(P, mine, head);
                     k = 0;
@@ -2329,8 +2345,9 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
                 if (tiles) {
                     if constexpr (TILES) run_tile<DT, D>(P, t, head, lds, how);
                 } else if (t.n_req * P.group <= 16) {
-                    if (t.flags & kTaskReadOnce) run_stream<DT, true, 1, W, D, FINISH>(P, t, head, lds, wave);
-                    else             run_stream<DT, false, 1, W, D, FINISH>(P, t, head, lds, wave);
+                    const int own = head_of(t, i);
+                    if (t.flags & kTaskReadOnce) run_stream<DT, true, 1, W, D, FINISH>(P, t, own, lds, wave);
+                    else             run_stream<DT, false, 1, W, D, FINISH>(P, t, own, lds, wave);
                 }
                 else if constexpr (DENSE) run_dense32<DT, D>(P, t, head, lds, how);
                 else if constexpr (stream_tiles(D) == 2 && !FINISH) {   // 17 .. 32 rows of 64 channels: two row tiles

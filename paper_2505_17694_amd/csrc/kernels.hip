@@ -2253,7 +2253,9 @@ extern __shared__ __attribute__((aligned(1024))) char dyn_lds[];
 // 161.5 -> 160.2; nothing on steps of 250 us and more.  Only the tile path of 256 channels was allocated worse without it (three-level
 // documents 289 -> 299 us), so its one kernel serves both modes (one_kernel).
 constexpr bool one_kernel(int form, int d) { return form == kFormWide && d == 256; }
-template <int DT, int FORM, int D, bool FUSED>
+// TURNS: stream tasks that alone read their slice go round the KV heads (head_of); two launches, up to 128 channels.  In a
+// kernel of its own: a choice at run time costs small plans, which do not make it, about 1 us.
+template <int DT, int FORM, int D, bool TURNS, bool FUSED>
 __global__ void __launch_bounds__(kernel_waves(FORM, D) * 64, D > 128 ? 1 : 2)
 pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in registers need a wave per SIMD
 {
@@ -2288,15 +2290,15 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
     const RowStore late = ARRIVES || P.arrive ? kRowsCoherent : last_rows_through(P.h_kv) ? kRowsThrough : kRowsPlain;
     // The KV head for which the workgroup runs record i.  Where the heads of a token lie side by side ([token][head]
     // pools), the rows of one head meet a subset of the memory channels, and not all heads as many: with a head
-    // of its own a workgroup of a slow head ends up to 20 % after the others.  Of plans whose rows go out finished the
-    // workgroups therefore take record i for the head i places on: every (record, head) is still run once, by the
+    // of its own a workgroup of a slow head ends up to 20 % after the others.  In plans whose rows go out finished the
+    // workgroups, and with TURNS those of larger plans in two launches, therefore take record i for the head i places on: every (record, head) is still run once, by the
     // workgroups that run record i, and the slow heads are spread over all of them.  (Slices that other tasks read as
     // well keep their head, whose L2 may hold them.)  Drawn plans of 100 .. 500 unshared contexts, time against fixed heads,
     // [token][head] pools: 64 channels 8 plans 0.816 (0.756 .. 0.908), 128 channels and four or eight heads 30 plans 0.902
     // (0.877 .. 0.961), 256 channels 11 plans 0.961; one head, or [head][token] pools, 142 plans 0.997 (0.985 .. 1.005).
     // 256 contexts of 100 .. 4000 tokens, 28 / 4 heads 199.8 -> 185.5 us.
     auto head_of = [&](const DevTask &t, int i) __attribute__((always_inline)) {
-        if constexpr (FINISH) {
+        if constexpr (FINISH || TURNS) {
             if (t.flags & kTaskReadOnce) return int(uint32_t(head + i) % uint32_t(P.h_kv));
         }
         return head;
@@ -2351,7 +2353,7 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
                 }
                 else if constexpr (DENSE) run_dense32<DT, D>(P, t, head, lds, how);
                 else if constexpr (stream_tiles(D) == 2 && !FINISH) {   // 17 .. 32 rows of 64 channels: two row tiles
-                    if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head, lds, wave);
+                    if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head_of(t, i), lds, wave);
                     else             run_stream<DT, false, 2, W, D>(P, t, head, lds, wave);
                 }
                 if constexpr (FUSED)
@@ -2460,7 +2462,11 @@ int prepare_kernels()
     struct Kernel { const void *kernel; int bytes; };
     auto wide = [](auto dt, auto d, auto fused) {
         constexpr int D = decltype(d)::value;
-        return Kernel{reinterpret_cast<const void *>(pac_kernel<decltype(dt)::value, kFormWide, D, decltype(fused)::value>), wide_lds_bytes<D>()};
+        return Kernel{reinterpret_cast<const void *>(pac_kernel<decltype(dt)::value, kFormWide, D, false, decltype(fused)::value>), wide_lds_bytes<D>()};
+    };
+    auto turns = [](auto dt, auto d) {
+        constexpr int D = decltype(d)::value;
+        return Kernel{reinterpret_cast<const void *>(pac_kernel<decltype(dt)::value, kFormWide, D, true, false>), wide_lds_bytes<D>()};
     };
     using f16 = std::integral_constant<int, CODEC_DTYPE_FP16>;
     using b16 = std::integral_constant<int, CODEC_DTYPE_BF16>;
@@ -2473,6 +2479,7 @@ int prepare_kernels()
         wide(f16{}, d128{}, no{}), wide(b16{}, d128{}, no{}), wide(f16{}, d128{}, yes{}), wide(b16{}, d128{}, yes{}),
         wide(f16{}, d64{}, no{}),  wide(b16{}, d64{}, no{}),  wide(f16{}, d64{}, yes{}),  wide(b16{}, d64{}, yes{}),
         wide(f16{}, d256{}, yes{}), wide(b16{}, d256{}, yes{}),
+        turns(f16{}, d64{}), turns(b16{}, d64{}), turns(f16{}, d128{}), turns(b16{}, d128{}),
     };
     for (const auto &k : kernels)
         if (hipError_t e = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes)) return int(e);
@@ -2481,20 +2488,24 @@ int prepare_kernels()
 }
 
 template <int DT, int D>
-void launch_pac_of(const PacParams &p, dim3 grid, bool wide, hipStream_t s)
+void launch_pac_of(const PacParams &p, dim3 grid, bool wide, bool turns, hipStream_t s)
 {
+    constexpr bool kTurns = D <= 128;
+
     const bool fused = p.arrive != nullptr;
     constexpr bool kOne = one_kernel(kFormWide, D);
     const dim3 block((wide ? kernel_waves(kFormWide, D) : kNarrowWaves) * 64);
     const size_t lds = wide ? wide_lds_bytes<D>() : 0;
-    if (!p.part_o)          hipLaunchKernelGGL((pac_kernel<DT, kFormFinish, D, false>), grid, block, lds, s, p);
-    else if (wide && fused) hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, true>), grid, block, lds, s, p);
-    else if (wide)          hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, kOne>), grid, block, lds, s, p);
-    else if (fused)         hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, true>), grid, block, lds, s, p);
-    else                    hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, false>), grid, block, lds, s, p);
+    if (!p.part_o)          hipLaunchKernelGGL((pac_kernel<DT, kFormFinish, D, false, false>), grid, block, lds, s, p);
+    else if (wide && fused) hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, false, true>), grid, block, lds, s, p);
+    else if (wide && turns) hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, kTurns, kOne>), grid, block, lds, s, p);
+    else if (wide)          hipLaunchKernelGGL((pac_kernel<DT, kFormWide, D, false, kOne>), grid, block, lds, s, p);
+    else if (fused)         hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, false, true>), grid, block, lds, s, p);
+    else if (turns)         hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, kTurns, false>), grid, block, lds, s, p);
+    else                    hipLaunchKernelGGL((pac_kernel<DT, kFormNarrow, D, false, false>), grid, block, lds, s, p);
 }
 
-int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, void *stream)
+int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, bool turns, void *stream)
 {
     if (head_dim != 64 && head_dim != 128 && head_dim != 256) return int(hipErrorInvalidValue);
     // all task shapes: dense tasks with 128 channels, packed row tiles with 64 and 256
@@ -2505,9 +2516,9 @@ int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int m
     const dim3 grid(unsigned(num_slots) * unsigned(p.h_kv));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool half = dtype == CODEC_DTYPE_FP16;
-    if (head_dim == 64)       half ? launch_pac_of<CODEC_DTYPE_FP16, 64>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 64>(p, grid, wide, s);
-    else if (head_dim == 128) half ? launch_pac_of<CODEC_DTYPE_FP16, 128>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 128>(p, grid, wide, s);
-    else                      half ? launch_pac_of<CODEC_DTYPE_FP16, 256>(p, grid, wide, s) : launch_pac_of<CODEC_DTYPE_BF16, 256>(p, grid, wide, s);
+    if (head_dim == 64)       half ? launch_pac_of<CODEC_DTYPE_FP16, 64>(p, grid, wide, turns, s) : launch_pac_of<CODEC_DTYPE_BF16, 64>(p, grid, wide, turns, s);
+    else if (head_dim == 128) half ? launch_pac_of<CODEC_DTYPE_FP16, 128>(p, grid, wide, turns, s) : launch_pac_of<CODEC_DTYPE_BF16, 128>(p, grid, wide, turns, s);
+    else                      half ? launch_pac_of<CODEC_DTYPE_FP16, 256>(p, grid, wide, false, s) : launch_pac_of<CODEC_DTYPE_BF16, 256>(p, grid, wide, false, s);
     return int(hipGetLastError());
 }
 

@@ -73,8 +73,9 @@ int launch_stream_read(const void *buf, uint64_t chunks, uint64_t mult, int once
 // Both return a hipError_t value (0 = success) without synchronising.
 // `max_rows_in_plan` selects the register-budget variant of the attention kernel.
 // `head_dim`: 64, 128 or 256 (plans for 64 and 256 hold tasks of at most 32 and 16 rows); `tiles`: the
-// device image packs sibling row tiles (64 and 256 channels only).
-int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, void *stream);
+// device image packs sibling row tiles (64 and 256 channels only); `turns`: stream tasks that alone read their slice go
+// round the KV heads (heads_in_turn; two launches only).
+int launch_pac(const PacParams &p, int dtype, int head_dim, int num_slots, int max_rows_in_plan, bool tiles, bool turns, void *stream);
 int launch_merge(const MergeParams &p, int dtype, int head_dim, void *stream);
 
 }  // namespace codec

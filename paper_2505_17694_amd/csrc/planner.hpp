@@ -87,6 +87,18 @@ constexpr int64_t kEarlyThroughBytes = int64_t(8) << 20;
 // up to 6 MB, 1.003 .. 1.007, by where the kernel's code then lay; two copies of one build differ by 0.0005.
 constexpr bool last_rows_through(int32_t kv_heads) { return (kv_heads & 7) != 0; }
 
+// Two-launch plans whose stream tasks go round the KV heads on [token][head] pools (head_of in kernels.hip): plans of
+// at least this estimated makespan and so many tasks per CU.  Rows of a head then lie in other L2s than the one of the XCD
+// that reduces it, and a workgroup with a single task gains nothing.  444 drawn plans of 64 and 128 channels, time against
+// fixed heads by tasks of all heads per CU: one 1.020, 1.4 .. 2.8 0.990 .. 1.011 (up to 1.043), 4 .. 8 0.96 .. 1.00, more
+// 0.81 .. 0.96.  By this rule 147 plans 0.956 (0.807 .. 1.024); what it leaves out 0.997.  256 channels gain nothing (1.00).
+constexpr int64_t kHeadsInTurnNs = 60000;
+constexpr int64_t kHeadsInTurnTasks = 3 * 256;
+constexpr bool heads_in_turn(int64_t tasks, int32_t kv_heads, int64_t makespan)
+{
+    return kv_heads > 1 && makespan >= kHeadsInTurnNs && tasks * kv_heads >= kHeadsInTurnTasks;
+}
+
 // Per request, the reduction kernel reads one 64-byte line: the number of partial rows on the request's
 // path and, if there are at most kInlineParts of them, the rows themselves; longer lists are read
 // from the CSR arrays.  One dependent read less than offset -> list -> partial rows.

@@ -688,6 +688,19 @@ def test_split_reduction(parts, d, hq, hkv, requests):
     assert np.array_equal(one, got)
 
 
+@pytest.mark.parametrize("d,hq,hkv,leaves", [(128, 32, 8, 110), (128, 28, 4, 200), (128, 9, 3, 280), (64, 16, 8, 110), (64, 12, 12, 90)])
+@pytest.mark.parametrize("opts", [{"num_slots": 1}, {"num_slots": 2}, {"num_slots": 3, "schedule": 1}])
+def test_stream_tasks_go_round_the_heads(d, hq, hkv, leaves, opts):
+    """[token][head] pools, plans long enough and with enough tasks for their stream tasks to go round the KV heads: every
+    task runs once for every head, from static lists and the queue, single-wave runs and whole workgroups, beside
+    dense or two-tile tasks that stay where they are."""
+    f = concat_forests(two_level_forest(300, [17 + 13 * (i % 9) for i in range(leaves)]), unshared_forest([2200, 33, 700]))
+    w = make_workload(f"turns-{d}-{hq}-{hkv}", f, HeadConfig(hq, hkv, d, DTYPE_BF16), seed=1900 + hq, poison=True, layout="thd")
+    sel = [(r, h) for r in range(0, len(f.req_node), 3) for h in range(0, hq, 2)] + [(leaves, hq - 1), (leaves + 2, 0)]
+    _, view = check(w, sel=sel, **opts)
+    assert view["makespan"] >= 60000 and len(view["tasks"]) * hkv >= 768 and view["fused"] == 0
+
+
 def _queue_cases():
     short = [7, 40, 2048, 33, 2049, 64, 300, 5, 3000, 96, 17, 1000, 31, 640, 1, 129] * 3
     dense = two_level_forest(1, [43] * 17)

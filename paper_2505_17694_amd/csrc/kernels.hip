@@ -1991,7 +1991,11 @@ struct WaveRows {
 // 16 requests with 64 / 8 heads 19.4 / 16.5, with 32 / 4 16.2 / 15.5; 32 / 8 heads of 128 channels, where both are so, alike.
 // Drawn plans, time by head over by request: 193 with KV heads that eight divides 0.991 (0.858 .. 1.013), 7 with four
 // heads 0.988, 51 with one head, for which the order is the same, 1.002 (0.987 .. 1.020).
-template <int DT, int D, int RPW>
+//
+// LONG: what of a list follows its first fifteen rows.  0: nothing, in no list of the plan.  1: rows sixteen to 23 are read
+// beside the first fifteen.  2: one after the other, for large launches, as 1 takes half as many registers again and the
+// waves of a CU are then fewer (1040 requests of 32 heads, lists of three rows, reduction alone 11.4 us, 13.1 with 1).
+template <int DT, int D, int RPW, int LONG>
 __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergeParams P)
 {
     using W = WaveRows<DT, D, RPW>;
@@ -2001,15 +2005,15 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
     if (unit >= P.num_requests * per_req) return;
     const int r = unit / per_req;
     const W at(P, blockIdx.x, r, (unit - r * per_req) * RPW);
-    // see merge_one; rows sixteen to 23 are read beside the first fifteen
+    // see merge_one
     const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
-    const int total = line[0], list_off = P.req_part_off[r];
+    const int total = line[0], list_off = LONG ? P.req_part_off[r] : 0;
     int first[kInlineParts];
 #pragma unroll
     for (int j = 0; j < kInlineParts; ++j) first[j] = line[1 + j];
 #pragma unroll
     for (int j = 0; j < kInlineParts; ++j) asm volatile("" : : "s"(first[j]));  // the line is read whole, not its second half when it is wanted
-    asm volatile("" : : "s"(list_off));
+    if constexpr (LONG != 0) asm volatile("" : : "s"(list_off));
     float M, L, acc[CPL];
     if (total <= kFoldChunk) {
         Chunk<kFoldChunk, CPL> x;
@@ -2019,7 +2023,7 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
         Chunk<kInlineParts, CPL> x;
         const int cnt = total < kInlineParts ? total : kInlineParts;
         x.load(P, at, first, cnt);
-        if (total <= kInlineParts) {
+        if (LONG == 0 || total <= kInlineParts) {
             x.sum_up(cnt, x.top(-INFINITY, cnt), L, acc);
         } else {
             const int32_t *list = P.req_part + list_off;
@@ -2031,9 +2035,10 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
                 for (int j = 0; j < kFoldChunk; ++j) rows[j] = list[base + j];  // behind the list: what follows it in the metadata, unused
                 y.load(P, at, rows, total - base);
             };
-            load_next();
+            if constexpr (LONG == 1) load_next();
             M = x.top(-INFINITY, cnt);
             x.sum_up(cnt, M, L, acc);
+            if constexpr (LONG == 2) load_next();
 #pragma unroll 1
             for (;;) {
                 const float mm = y.top(M, total - base), before = weight(M, mm);
@@ -2552,8 +2557,14 @@ void launch_merge_of(const MergeParams &p, hipStream_t s)
     };
     if (p.split_waves == 4)      split(std::integral_constant<int, 4>{});
     else if (p.split_waves == 8) split(std::integral_constant<int, 8>{});
-    else if (wide) launch(merge_kernel<DT, D, kWide>, kMergeWaves, kMergeWaves);
-    else           launch(merge_kernel<DT, D, 1>, kMergeWaves, kMergeWaves);
+    auto one = [&](auto form) {
+        constexpr int LONG = decltype(form)::value;
+        if (wide) launch(merge_kernel<DT, D, kWide, LONG>, kMergeWaves, kMergeWaves);
+        else      launch(merge_kernel<DT, D, 1, LONG>, kMergeWaves, kMergeWaves);
+    };
+    if (p.split_waves == 0)      one(std::integral_constant<int, 0>{});
+    else if (p.split_waves == 1) one(std::integral_constant<int, 1>{});
+    else if (p.split_waves == 2) one(std::integral_constant<int, 2>{});
 }
 
 int launch_merge(const MergeParams &p, int dtype, int head_dim, void *stream)

@@ -17,7 +17,7 @@ struct MergeParams {
     const int32_t *req_line;        // [B][split_line_words(split_waves)]: count, then the first split_rows(split_waves) rows
     void *out;                      // [B][h_q][head_dim], 16-bit
     int32_t num_requests, h_q, group, part_rows;
-    int32_t split_waves;            // 4 or 8 waves share a list; 0: one wave folds it, and there is no req_line
+    int32_t split_waves;            // 4 or 8 waves share a list; less: one wave folds it, and there is no req_line (split_waves())
 };
 
 struct PacParams {

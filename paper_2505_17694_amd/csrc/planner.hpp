@@ -105,7 +105,7 @@ constexpr bool heads_in_turn(int64_t tasks, int32_t kv_heads, int64_t makespan)
 constexpr int32_t kInlineParts = 15;
 
 // Waves that share a list in the split form of the reduction (merge_split_kernel), the first fifteen rows and eight each
-// round; 0: one wave folds a list.  By the longest list and by the waves of the launch, as a wave whose part of a list is
+// round; less than four: one wave folds a list, see LONG of merge_kernel.  By the longest list and by the waves of the launch, as a wave whose part of a list is
 // empty still has to start.  Drawn plans, whole steps, time with the split form over time with one wave per list:
 // lists of 16 .. 23 rows (two waves) 73 plans 0.997 (0.915 .. 1.043), 24 .. 39 rows (four) 37 plans 0.965 (0.873 .. 1.016),
 // more (eight) 13 plans 0.88 (0.62 .. 0.98).  By waves, a variant with up to eight waves: 2048 .. 16383 217 plans 0.964
@@ -116,9 +116,10 @@ constexpr int64_t kSplitMaxWaves = 16383;
 constexpr int32_t split_rows(int32_t waves) { return kInlineParts + 8 * (waves - 1); }     // of a list, that a round reads
 constexpr int32_t split_waves(int32_t longest_list, int32_t num_requests, int32_t h_q, int32_t group, int32_t head_dim)
 {
-    const int32_t waves = longest_list < kSplitMinList ? 0 : longest_list <= split_rows(4) ? 4 : 8;
+    if (longest_list <= kInlineParts) return 0;
+    const int32_t waves = longest_list < kSplitMinList ? 1 : longest_list <= split_rows(4) ? 4 : 8;
     const int32_t heads = 256 / head_dim > 1 && group % (256 / head_dim) == 0 ? 256 / head_dim : 1;  // rows of a wave
-    return int64_t(num_requests) * (h_q / heads) * waves <= kSplitMaxWaves ? waves : 0;
+    return int64_t(num_requests) * (h_q / heads) * waves <= kSplitMaxWaves ? waves : 2;
 }
 // Words of a request's line for the split form: its list's length and first rows.
 constexpr int32_t split_line_words(int32_t waves) { return (1 + split_rows(waves) + 15) / 16 * 16; }

@@ -31,8 +31,7 @@
 //    Long slices under at most 128 rows put two waves on each row group, on
 //    alternate blocks.
 //  * "tile" (64 and 256 channels): sibling row tiles of one slice packed into one
-//    task of up to 64 (128) rows; 16 x 16 x 32 tiles, blocks shared through LDS.
-//    Packs of more than 64 rows of 64 channels run as dense tasks.
+//    task of up to 256 (128) rows; 16 x 16 x 32 tiles, blocks shared through LDS.
 //
 // K and V slices that a single task reads, in plans that read little twice, are
 // loaded with the streaming (nontemporal) hint; the plan marks those tasks.
@@ -51,8 +50,8 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-constexpr int kHeadDim = 128;       // the head dimension whose plans have dense tasks; the paths and the reduction take the
-                                    // head dimension D (64, 128 or 256; the dense path 64 or 128) as a template parameter
+constexpr int kHeadDim = 128;       // the dense path; the stream path and the reduction take the head
+                                    // dimension D (64, 128 or 256) as a template parameter
 constexpr int kNarrowWaves = 4;     // stream-only kernel variant: 4 waves, two workgroups per CU
 constexpr int kWideWaves = 8;       // all task shapes: 8 waves (two per SIMD), one workgroup per CU
 // Forms of the attention kernel: stream tasks only; all task shapes (dense, or tile with 64 and 256 channels);
@@ -859,70 +858,12 @@ __device__ __forceinline__ void pin(int &x) { asm volatile("" : "+v"(x)); }
 // would hold a single computing wave and the other one would idle.
 enum { kHelper = 0, kMatrixFirst = 1, kVectorFirst = 2 };
 
-// Where the partial rows of a packed task lie: row tile k starts k * stride rows after the first, a smaller last tile
-// `last_back` rows earlier.
-struct PackedRows {
-    int tile_rows, stride, last_tile, last_back;
-    uint32_t inverse;
-    __device__ __forceinline__ PackedRows(const DevTask &t, int rows)
-    {
-        tile_rows = (t.flags >> kTaskTileShift) & 255;
-        stride = ~t.single_req;
-        inverse = 65536u / uint32_t(tile_rows) + 1;         // row * inverse >> 16 is row / tile_rows: rows and tile_rows are at most 256
-        last_tile = (rows - 1) / tile_rows;
-        last_back = t.flags >> kTaskLastShift;
-    }
-    // a descriptor at the first row reaches every row: offsets stay below 2^31 bytes (more slices of a node than any
-    // but a forced division has)
-    __device__ __forceinline__ bool reachable(int d) const { return int64_t(last_tile + 1) * stride * (d * 4) < int64_t(1) << 31; }
-    __device__ __forceinline__ int64_t place(int row) const
-    {
-        const int tile = int(uint32_t(row) * inverse >> 16);
-        return int64_t(tile) * stride + (row - tile * tile_rows) - (tile == last_tile ? last_back : 0);
-    }
-};
-
-// Whether the dense path looks for rows that have outgrown their reference in the block's sums of probabilities
-// (each is at most 2^kLag where the sum is) instead of in its scores, which saves the maxima: 64 channels, where vector
-// instructions are scarce, 128 rows on 4096 tokens 63.0 -> 59.4 us.  With 128 channels the longer
-// chain from the scores to the matrix instructions costs more: 256 rows on 4096 tokens 157 -> 169 us.
-template <int D> constexpr bool kCheckAfter = D == 64;
-constexpr float kLagSum = 256.f;            // 2^kLag
-
-// Sizes of the dense path.  A ring slot holds 8 KB of K and 8 KB of V: a block of 32 tokens of 128 channels or of 64
-// tokens of 64 channels, sixteen matrix instructions per wave either way.
-//
-// 64 channels: packed row tiles of more than 64 rows.  The vector work bounds them (a block has twice the
-// exponentials for the same matrix instructions), and what the path brings is that it runs beside the matrix
-// instructions of the SIMD's other wave; the tile path's waves do one after the other.  us per task, equal nodes that
-// fill the chip (64 / 8 heads), tile path / dense path: 128 rows on 512, 2048, 4096 tokens 15.5 / 12.8, 42.4 / 33.3,
-// 75.4 / 58.7; 256 rows 21.7 / 17.5, 64.8 / 47.8, 116 / 87.8.  64 rows 11.6 / 11.8, 28.3 / 29.8, 49.8 / 51.9 (two of
-// the four SIMDs have no row group): those stay in the tile path.  Drawn plans that pack: down to 0.80 of the time.
-template <int D>
-struct DensePath {
-    static_assert(D == 64 || D == 128, "a wave's share of a block is sixteen matrix instructions");
-    static constexpr int kRowBytes = D * 2;
-    static constexpr int kTokens = 8192 / kRowBytes;        // tokens of a block
-    static constexpr int kTiles = kTokens / 32;             // token tiles of the scores
-    static constexpr int kSteps = D / 16;                   // k-steps of the scores
-    static constexpr int kCT = D / 32;                      // channel tiles of the accumulation
-    static constexpr int kVT = kTokens / 16;                // k-steps of the accumulation
-    static constexpr int kTokensPerWave = kTokens / 8;      // what a wave copies of a block
-    // 16-byte column g of a row lies in slot g ^ key_swizzle (value_swizzle): a K read takes one column of 16
-    // tokens, which then fill the 256 bytes of banks; a transposing V read takes, per 32 lanes, 64 bytes of each of four
-    // tokens, which then lie in four different quarters of them.
-    static constexpr __device__ int key_swizzle(int token) { return D == 128 ? token & 15 : (token >> 1) & 7; }
-    static constexpr __device__ int value_swizzle(int token) { return D == 128 ? (token & 3) << 2 : ((token >> 1) & 1) << 2; }
-};
-
 // One wave's share of a dense task: task rows row0 .. row0+31 (none for a helper).
-template <int DT, int D, int ROLE, int STRIDE>
+template <int DT, int ROLE, int STRIDE>
 __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &t, int head, char *lds,
                                              int wave, int row0, int rows, RowStore how)
 {
-    using X = DensePath<D>;
     constexpr bool LIVE = ROLE != kHelper;
-    constexpr int KS = X::kSteps, CT = X::kCT, VT = X::kVT, NJ = X::kTiles, RB = X::kRowBytes, BT = X::kTokens;
     static_assert(STRIDE == 1 || STRIDE == 2, "a row group is shared by one or two waves");
     // slots in use: an interval of two blocks wants a deeper ring to keep as many bytes in flight
     constexpr int RING = STRIDE == 2 ? kRing : 8;
@@ -933,29 +874,31 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     const int l32 = lane & 31, kg = lane >> 5;
     const int l16 = lane & 15, grp = lane >> 4;
 
-    u32x4 qb[KS];           // B operand of the scores: row l32, channels 16*ks + 8*kg .. +7
-    f32x16 o[CT];           // O^T: row l32, channel 32*ct + 8*(r/4) + 4*kg + r%4
+    u32x4 qb[8];            // B operand of the scores: row l32, channels 16*ks + 8*kg .. +7
+    f32x16 o[4];            // O^T: row l32, channel 32*ct + 8*(r/4) + 4*kg + r%4
     float m = -INFINITY;    // reference, log2 units, integer-valued (same in the two lanes of a row)
     float l4[4] = {0.f, 0.f, 0.f, 0.f};     // this lane's share of the row sum, in four partial sums
     if constexpr (LIVE) {
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
     }
     const SliceCtx c = make_ctx(P, t, head);
 
-    // Asynchronous copies.  Wave w moves kTokensPerWave consecutive tokens of every block, 1 KB of K and 1 KB of V;
-    // a lane writes its 16-byte slot of an LDS row, fetching the column that the swizzle keeps there.
+    // Asynchronous copies.  Wave w moves tokens 4w .. 4w+3 of every block, 1 KB of K and 1 KB of V;
+    // lane (grp, l16) writes the 16-byte slot l16 of LDS row 4w + grp.  A K row keeps its 16-byte
+    // column g in slot g ^ (token & 15), a V row in slot g ^ 4*(token & 3): the swizzles that make
+    // the operand reads below free of bank conflicts (a transposing V read takes, per 32 lanes, 4 rows
+    // x 64 bytes: the four rows must land in four different quarters of the 256 bytes of banks).
     const uint32_t lds_base = uint32_t(uintptr_t(lds));
-    const int row_w = D == kHeadDim ? grp : lane >> 3, col_w = D == kHeadDim ? l16 : lane & 7;
-    const int tok_w = wave * X::kTokensPerWave + row_w;
-    const uint32_t voff_k = uint32_t(row_w) * c.token_bytes + uint32_t((col_w ^ X::key_swizzle(tok_w)) << 4);
-    const uint32_t voff_v = uint32_t(row_w) * c.token_bytes + uint32_t((col_w ^ X::value_swizzle(tok_w)) << 4);
-    // the wave's tokens past the end of the slice are redirected to token 0 (their rows are masked
+    const int tok_w = wave * 4 + grp;
+    const uint32_t voff_k = uint32_t(grp) * c.token_bytes + uint32_t((l16 ^ (tok_w & 15)) << 4);
+    const uint32_t voff_v = uint32_t(grp) * c.token_bytes + uint32_t((l16 ^ ((tok_w & 3) << 2)) << 4);
+    // a group of four tokens past the end of the slice is redirected to token 0 (its rows are masked
     // later) so that no address leaves the slice's pages
     auto first_token = [&](int bb) {
-        const int tok0 = bb * BT + wave * X::kTokensPerWave;
+        const int tok0 = bb * 32 + wave * 4;
         return tok0 >= c.kv_len ? 0 : tok0;
     };
     auto page_issue = [&](int bb) { return uniform_load(c.pages, first_token(bb) >> c.page_shift); };
@@ -966,95 +909,83 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     };
 
     // Operand reads.
-    // K (A operand of the scores): lane (l32, kg) reads column 2*ks + kg of token row l32 of a token tile; with the
+    // K (A operand of the scores): lane (l32, kg) reads column 2*ks + kg of token row l32; with the
     // swizzle its address is the ks = 0 address with (ks << 5) XORed in.
     // V (A operand of the accumulation, channel tile ct, k-step t): ds_read_b64_tr_b16 hands lane i of a
     // 16-lane group column i of the 4 x 16 tile whose row k the group's lanes 4k .. 4k+3 address 8 bytes
     // apiece.  Lane group (kg, ch) = (lane/32, lane/16 % 2), lane (k, q) in it, addresses token
     // 16*t + 8*h + 4*kg + k, channels 32*ct + 16*ch + 4*q .. +3: two reads (h = 0, 1) give the lane its
     // channel 32*ct + lane%32 for the 8 tokens of its k-group.  ct is XORed into the address like ks.
-    const uint32_t ka_lane = uint32_t(l32 * RB + ((kg ^ X::key_swizzle(l32)) << 4));
+    const uint32_t ka_lane = uint32_t(l32 * 256 + ((kg ^ (l32 & 15)) << 4));
     const int vk = l16 >> 2, vq = l16 & 3, vch = grp & 1;
     const int vrow = 4 * kg + vk;
     const uint32_t va_lane =
-        uint32_t(8192 + vrow * RB + (((2 * vch + (vq >> 1)) ^ X::value_swizzle(vrow)) << 4) + 8 * (vq & 1));
-    // The eight matrix instructions of either product, i = 0 .. 7: scores of token tile i % NJ, k-step i / NJ;
-    // accumulation of channel tile i % CT, k-step i / CT.
-    u32x4 kr[8];            // K operands of one block
-    u32x4 vr[8];            // V operands of one block
-    static_assert(NJ * KS == 8 && CT * VT == 8, "");
+        uint32_t(8192 + vrow * 256 + ((((2 * vch + (vq >> 1)) ^ ((vrow & 3) << 2)) & 15) << 4) + 8 * (vq & 1));
+    u32x4 kr[8];            // K operands of one block, by k-step
+    u32x4 vr[4][2];         // V operands of one block, by channel tile and k-step
     auto key_base = [&](int bb) { return lds_base + uint32_t(bb % RING) * kBlockBytes + ka_lane; };
     auto value_base = [&](int bb) { return lds_base + uint32_t(bb % RING) * kBlockBytes + va_lane; };
-    auto load_key = [&](uint32_t base, int i) {
-        kr[i] = *reinterpret_cast<const u32x4 __attribute__((address_space(3))) *>(uintptr_t((base ^ uint32_t((i / NJ) << 5)) + (i % NJ) * 32 * RB));
+    auto load_key = [&](uint32_t base, int ks) {                        // K operand of k-step ks
+        kr[ks] = *reinterpret_cast<const u32x4 __attribute__((address_space(3))) *>(uintptr_t(base ^ uint32_t(ks << 5)));
     };
     typedef __attribute__((ext_vector_type(4))) short s16x4;
     typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
-    auto load_value = [&](uint32_t base, int i) {
+    auto load_value = [&](uint32_t base, int ct, int tt) {              // V operand of channel tile ct, k-step tt
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const uint32_t addr = (base ^ uint32_t((i % CT) << 6)) + (i / CT) * 16 * RB + h * 8 * RB;
+            const uint32_t addr = (base ^ uint32_t(ct << 6)) + tt * 4096 + h * 2048;
             const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_s16x4_ptr>(uintptr_t(addr)));
             const uint2 w = __builtin_bit_cast(uint2, x);
-            vr[i][2 * h] = w.x;
-            vr[i][2 * h + 1] = w.y;
+            vr[ct][tt][2 * h] = w.x;
+            vr[ct][tt][2 * h + 1] = w.y;
         }
     };
     auto load_keys = [&](int bb) {
         const uint32_t base = key_base(bb);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) load_key(base, i);
+        for (int ks = 0; ks < 8; ++ks) load_key(base, ks);
     };
     auto load_values = [&](int bb) {
         const uint32_t base = value_base(bb);
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-            for (int tt = 0; tt < VT; ++tt) load_value(base, tt * CT + ct);
+            for (int tt = 0; tt < 2; ++tt) load_value(base, ct, tt);
     };
     // tokens past `valid` count as zero in V (the slot may hold anything there, NaN patterns included)
     // and as -inf in the scores
     auto mask_values = [&](int valid) {
 #pragma unroll
-        for (int tt = 0; tt < VT; ++tt)
+        for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 const int tok = 16 * tt + 8 * (d >> 1) + 4 * kg + 2 * (d & 1);  // low half; high half tok+1
                 const unsigned int keep = (tok < valid ? 0x0000FFFFu : 0u) | (tok + 1 < valid ? 0xFFFF0000u : 0u);
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) vr[tt * CT + ct][d] &= keep;
+                for (int ct = 0; ct < 4; ++ct) vr[ct][tt][d] &= keep;
             }
+    };
+    auto mask_scores32 = [&](f32x16 &s, int valid) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const bool dead = 8 * (r >> 2) + 4 * kg + (r & 3) >= valid;
+            s[r] = dead ? -INFINITY : s[r];
+        }
     };
 
-    f32x16 s[NJ];           // scores of token tile j: row l32, token 32*j + 8*(r/4) + 4*kg + r%4
-    u32x4 p[VT];            // probabilities, B operand: k-step t holds registers 8*(t%2) .. +7 of the scores of tile t/2
-    auto mask_scores32 = [&](int valid) {
-        // 64 channels: against `valid` less the lane's first token, one register; the lane's 32 token indices, which
-        // the compiler otherwise keeps across the loop, spill (16 fit with 128 channels, whose loop is a few
-        // instructions shorter that way)
-        const int first = D == kHeadDim ? 4 * kg : 0, left = D == kHeadDim ? valid : valid - 4 * kg;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const bool dead = 32 * j + 8 * (r >> 2) + first + (r & 3) >= left;
-                s[j][r] = dead ? -INFINITY : s[j][r];
-            }
-    };
+    f32x16 s;               // scores: row l32, token 8*(r/4) + 4*kg + r%4
+    u32x4 p[2];             // probabilities, B operand: k-step t holds registers 8t .. 8t+7 of the scores
     auto scores32 = [&]() {
-        f32x16 acc[NJ];
+        f32x16 acc;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i % NJ] = mfma32<DT>(kr[i], qb[i / NJ], acc[i % NJ]);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) s[j] = acc[j];
+        for (int i = 0; i < 8; ++i) acc = mfma32<DT>(kr[i], qb[i], acc);
+        s = acc;
     };
     auto accumulate32 = [&]() {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) o[i % CT] = mfma32<DT>(vr[i], p[i / CT], o[i % CT]);
+        for (int i = 0; i < 8; ++i) o[i & 3] = mfma32<DT>(vr[i & 3][i >> 2], p[i >> 2], o[i & 3]);
     };
     // The matrix half of a FULL step: O^T += V^T P^T of the block in vr and the scores of the block in
     // kr; the two alternate so that no instruction waits for the one before it.  With one wave per row
@@ -1066,17 +997,15 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         // the wave in its matrix half goes first when both waves of the SIMD have an instruction ready:
         // measured, the other order starves the matrix instructions (1150 against 1010 clk per half)
         __builtin_amdgcn_s_setprio(3);
-        f32x16 acc[NJ];
+        f32x16 acc;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            o[i % CT] = mfma32<DT>(vr[i], p[i / CT], o[i % CT]);
-            acc[i % NJ] = mfma32<DT>(kr[i], qb[i / NJ], acc[i % NJ]);
+            o[i & 3] = mfma32<DT>(vr[i & 3][i >> 2], p[i >> 2], o[i & 3]);
+            acc = mfma32<DT>(kr[i], qb[i], acc);
             if constexpr (STRIDE == 1) {
-                load_value(vbase, i);
+                load_value(vbase, i & 3, i >> 2);
                 load_key(kbase, i);
             }
             if (i == 0) after_first_pair();
@@ -1088,67 +1017,41 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
             load_values(vb);
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) s[j] = acc[j];
+        s = acc;
     };
-    // The vector work of a block.  lane_maximum(): over the lane's scores, log2 units.  raise(): the reference moves
-    // up to the row maximum and everything accumulated against the old one is rescaled.
-    // probabilities(t): P = exp2(scale * S - m) for k-step t in B-operand layout, added up in sum[].
-    auto lane_maximum = [&]() {
-        float a = s[0][0];
+    // The vector work of a block, in three pieces.  reference(): the lane's maximum over its 16 scores;
+    // when a row has outgrown its reference by more than the lag, the reference moves up to the
+    // (rounded-up) row maximum and everything accumulated against the old one is rescaled.
+    // probabilities(t): P = exp2(scale * S - m) for k-step t in B-operand layout, and the lane's share
+    // of the row sum.
+    auto reference = [&]() {
+        float a = __builtin_fmaxf(__builtin_fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
-        for (int r = 1; r + 1 < 16 * NJ; r += 2)
-            a = __builtin_fmaxf(__builtin_fmaxf(a, s[r / 16][r % 16]), s[(r + 1) / 16][(r + 1) % 16]);
-        return __builtin_fmaxf(a, s[NJ - 1][15]) * P.scale_log2e;
+        for (int r = 3; r + 1 < 16; r += 2) a = __builtin_fmaxf(__builtin_fmaxf(a, s[r]), s[r + 1]);
+        const float lm = __builtin_fmaxf(a, s[15]) * P.scale_log2e;
+        if (__any(lm > m + kLag)) {
+            const float mx = fmaxf(lm, __shfl_xor(lm, 32));
+            const float m_new = __builtin_ceilf(fmaxf(m, mx));
+            const float alpha = fast_exp2(m - m_new);                   // 0 on the first block (m = -inf)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) l4[d] *= alpha;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
+            m = m_new;
+        }
     };
-    auto raise = [&](float lm) {
-        const float mx = fmaxf(lm, __shfl_xor(lm, 32));
-        // 64 channels: the row maximum itself, whose probability is then 1 and exact in 16 bits (contexts of a few
-        // dozen tokens: largest error against 64 bits 2.9e-3, rounded up 3.6e-3)
-        const float m_new = D == kHeadDim ? __builtin_ceilf(fmaxf(m, mx)) : fmaxf(m, mx);
-        const float alpha = fast_exp2(m - m_new);                   // 0 on the first block (m = -inf)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) l4[d] *= alpha;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[ct][r] *= alpha;
-        m = m_new;
-    };
-    auto probabilities32 = [&](int tt, float (&sum)[4]) {
+    auto probabilities32 = [&](int tt) {
         float e[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = fast_exp2(__builtin_fmaf(s[tt / 2][8 * (tt % 2) + i], P.scale_log2e, -m));
+        for (int i = 0; i < 8; ++i) e[i] = fast_exp2(__builtin_fmaf(s[8 * tt + i], P.scale_log2e, -m));
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
             p[tt][d] = pack2<DT>(e[2 * d], e[2 * d + 1]);
-            sum[d] = add_pair<DT>(p[tt][d], sum[d]);
+            l4[d] = add_pair<DT>(p[tt][d], l4[d]);
         }
         pin(p[tt]);
-    };
-    auto softmax_half = [&](auto after) {
-        if constexpr (!decltype(after)::value) {
-            const float lm = lane_maximum();
-            if (__any(lm > m + kLag)) raise(lm);
-#pragma unroll
-            for (int tt = 0; tt < VT; ++tt) probabilities32(tt, l4);
-        } else {
-            float sum[4], total;
-            auto all = [&]() {
-#pragma unroll
-                for (int d = 0; d < 4; ++d) sum[d] = 0.f;
-#pragma unroll
-                for (int tt = 0; tt < VT; ++tt) probabilities32(tt, sum);
-                total = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-            };
-            all();
-            if (__any(!(total <= kLagSum))) {
-                raise(lane_maximum());              // written out again: a loop of two passes takes 10 % longer
-                all();
-            }
-#pragma unroll
-            for (int d = 0; d < 4; ++d) l4[d] += sum[d];
-        }
     };
 
     // Common to all roles.  All but S = STRIDE blocks of the ring are requested up front; interval j
@@ -1163,7 +1066,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     // issues 2 loads per block and loads complete in order, so a block has landed once at most 2 * (blocks
     // issued after it) loads are outstanding; near the end of the slice, where fewer blocks follow, the
     // wait is for everything.
-    const int nblk = (t.kv_len + BT - 1) >> (D == kHeadDim ? 5 : 6);
+    const int nblk = (t.kv_len + 31) >> 5;
     const int nint = (nblk + STRIDE - 1) / STRIDE - 1;                  // the same for every wave
     // Start of the task.  What the first matrix instruction waits for is a chain of dependent reads:
     // page ids and the rows' requests, then the first blocks and the query rows.  The two reads of a
@@ -1190,7 +1093,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
             int req = t.single_req >= 0 ? t.single_req : P.node_q[t.q_off + qi];
             pin(req);                           // the wait for it stands here, ahead of the copies
             qp = static_cast<const char *>(P.q)
-                 + (int64_t(req) * P.h_q + int64_t(head) * P.group + hj) * RB + kg * 16;
+                 + (int64_t(req) * P.h_q + int64_t(head) * P.group + hj) * (kHeadDim * 2) + kg * 16;
         }
 #pragma unroll
         for (int d = 0; d < 4; ++d) pg_late[d] = pg[EARLY + d];
@@ -1201,7 +1104,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         const uint32_t parked = park + uint32_t(lane) * 16;
         if constexpr (LIVE) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) dma16_rows(park + ks * 1024, qp + ks * 32);
+            for (int ks = 0; ks < 8; ++ks) dma16_rows(park + ks * 1024, qp + ks * 32);
         }
 #pragma unroll
         for (int d = 2 * STRIDE; d < EARLY; ++d)
@@ -1213,7 +1116,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         if constexpr (LIVE) {
             typedef const u32x4 __attribute__((address_space(3))) *lds_u32x4_ptr;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+            for (int ks = 0; ks < 8; ++ks) {
                 const u32x4 x = *reinterpret_cast<lds_u32x4_ptr>(uintptr_t(parked + ks * 1024));   // the piece this lane sent
                 qb[ks] = live ? x : u32x4{0u, 0u, 0u, 0u};
             }
@@ -1255,7 +1158,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
     };
     using yes = std::true_type;
     using no = std::false_type;
-    auto short_block = [&](int b) { return c.kv_len - b * BT; };        // valid tokens if below BT
+    auto short_block = [&](int b) { return c.kv_len - b * 32; };        // valid tokens if below 32
     auto more_follow = [&](int j) { return STRIDE * j + RING - LAG + STRIDE - 1 < nblk; };
 
     if constexpr (LIVE) {
@@ -1268,10 +1171,11 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         // one's matrix work beside the other's vector work.
         constexpr bool VFIRST = ROLE == kVectorFirst;
         const int nmine = nblk > first ? (nblk - first + STRIDE - 1) / STRIDE : 0;
-        auto vector_half_of = [&](int b, auto more) {                   // more: b is not the slice's last block
-            if constexpr (!decltype(more)::value)
-                if (short_block(b) < BT) mask_scores32(short_block(b));
-            softmax_half(std::bool_constant<kCheckAfter<D> && decltype(more)::value>{});   // not at the ends of a slice: shorter code
+        auto vector_half_of = [&](int b) {
+            if (short_block(b) < 32) mask_scores32(s, short_block(b));
+            reference();
+            probabilities32(0);
+            probabilities32(1);
         };
         // With one wave per row group the copies of the interval are requested from inside the matrix
         // half: their address arithmetic issues while the matrix unit works, instead of ahead of it.
@@ -1287,12 +1191,12 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
             if constexpr (!REQUEST_INSIDE) request_blocks(k, more);
             if (STRIDE == 1 || k + 1 < nmine) {                         // else: the other wave's last block only
                 if constexpr (VFIRST) {
-                    vector_half_of(blk(k), more);
+                    vector_half_of(blk(k));
                     __builtin_amdgcn_sched_barrier(0);
                     matrix_half_and_loads(k, more);
                 } else {
                     matrix_half_and_loads(k, more);
-                    vector_half_of(blk(k + 1), more);
+                    vector_half_of(blk(k + 1));
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -1305,7 +1209,7 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
             load_values(blk(0));
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!VFIRST) {
-                vector_half_of(blk(0), no{});
+                vector_half_of(blk(0));
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1316,8 +1220,8 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         for (; k < nint; ++k) interval(k, no{});
         if (STRIDE == 1 || nmine > 0) {
             const int last = blk(nmine - 1);
-            if constexpr (VFIRST) vector_half_of(last, no{});
-            if (short_block(last) < BT) mask_values(short_block(last));
+            if constexpr (VFIRST) vector_half_of(last);
+            if (short_block(last) < 32) mask_values(short_block(last));
             accumulate32();
         }
     } else {
@@ -1330,28 +1234,27 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
 
     __syncthreads();                        // every block has been read: the ring is free
     float l = (l4[0] + l4[1]) + (l4[2] + l4[3]);
-    constexpr int kState = (CT * 16 + 2) * 64;      // floats of a wave's state
     if constexpr (STRIDE == 2) {
-        // The odd-block wave hands its state to the even-block wave of its row group: accumulator
+        // The odd-block wave hands its state to the even-block wave of its row group: 64 accumulator
         // registers, reference and sum share per lane, register-major so that a wave's store or load
         // covers consecutive words.
-        float *x = reinterpret_cast<float *>(lds) + (wave & 3) * kState + lane;
+        float *x = reinterpret_cast<float *>(lds) + (wave & 3) * (66 * 64) + lane;
         if constexpr (ROLE == kVectorFirst) {
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+            for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) x[(ct * 16 + r) * 64] = o[ct][r];
-            x[CT * 16 * 64] = m;
-            x[(CT * 16 + 1) * 64] = l;
+            x[64 * 64] = m;
+            x[65 * 64] = l;
         }
         __syncthreads();
         if constexpr (ROLE == kMatrixFirst) {
-            const float m2 = x[CT * 16 * 64], l2 = x[(CT * 16 + 1) * 64];
+            const float m2 = x[64 * 64], l2 = x[65 * 64];
             const float m_new = fmaxf(m, m2);
             const float a1 = weight(m, m_new), a2 = weight(m2, m_new);
             l = l * a1 + l2 * a2;
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+            for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[ct][r] = o[ct][r] * a1 + x[(ct * 16 + r) * 64] * a2;
             m = m_new;
@@ -1360,12 +1263,12 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
 
     // The partial rows go out through LDS: in registers a lane holds 16-byte pieces of one row, and a
     // store instruction of the wave would touch 32 rows with 32 bytes each (measured: 3.1 us to issue
-    // the 128 KB of a 256-row task of 128 channels, the address unit taking one such piece about every two cycles).
-    // Each wave writes its 32 rows into an area of its own (16 bytes between rows: 16 lanes
-    // then cover all banks) and reads them back row by row: a store instruction covers two (four) whole rows,
+    // the 128 KB of a 256-row task, the address unit taking one such piece about every two cycles).
+    // Each wave writes its 32 x 128 floats into an area of its own (rows 528 bytes apart: 16 lanes
+    // then cover all banks) and reads them back row by row: a store instruction covers two whole rows,
     // 1 KB of consecutive memory.  With two waves per row group the area is the one the hand-over
     // above has just used, and only its own wave touches it from here on.
-    constexpr int kStageRow = D * 4 + 16, kStageWave = kState * 4;
+    constexpr int kStageRow = 528, kStageWave = 66 * 64 * 4;
     static_assert(32 * kStageRow <= kStageWave && 8 * kStageWave <= kRingBytes, "staging areas fit the ring");
     if constexpr (ROLE == kMatrixFirst || (STRIDE == 1 && LIVE)) {
         l += __shfl_xor(l, 32);
@@ -1373,49 +1276,26 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
         const uint32_t area = lds_base + uint32_t(STRIDE == 2 ? (wave & 3) : wave) * kStageWave;
         const uint32_t put = area + uint32_t(l32) * kStageRow + uint32_t(kg) * 16;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const f32x4 x4 = {o[ct][4 * q], o[ct][4 * q + 1], o[ct][4 * q + 2], o[ct][4 * q + 3]};
                 *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(put + ct * 128 + q * 32)) = x4;
             }
-        constexpr int RPI = 256 / D;                    // rows of a store instruction, D / 4 lanes each
-        const int row_o = D == kHeadDim ? kg : grp, col_o = D == kHeadDim ? l32 : l16;
-        const uint32_t get = area + uint32_t(row_o) * kStageRow + uint32_t(col_o) * 16;
-        if constexpr (D == kHeadDim) {
-            const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + row0;
-            float *po = P.part_o + prow * D;
-            with_row_store(how, [&](auto h) __attribute__((always_inline)) {
-                constexpr RowStore HOW = decltype(h)::value;
-                if (row0 + l32 < rows && kg == 0) st8_partial<HOW>(P.part_ml + (prow + l32) * 2, m, l);
-                const Rows out = rows_at(po, (rows - row0) * D * 4);            // rows the task does not have are dropped
+        const uint32_t get = area + uint32_t(kg) * kStageRow + uint32_t(l32) * 16;
+        const int64_t prow = int64_t(head) * P.part_rows + t.part_row_base + row0;
+        float *po = P.part_o + prow * kHeadDim;
+        with_row_store(how, [&](auto h) __attribute__((always_inline)) {
+            constexpr RowStore HOW = decltype(h)::value;
+            if (row0 + l32 < rows && kg == 0) st8_partial<HOW>(P.part_ml + (prow + l32) * 2, m, l);
+            const Rows out = rows_at(po, (rows - row0) * kHeadDim * 4);         // rows the task does not have are dropped
 #pragma unroll
-                for (int j = 0; j < 32 / RPI; ++j) {
-                    const f32x4 x4 = *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(get + j * RPI * kStageRow));
-                    if constexpr (HOW != kRowsCoherent) st16_rows<HOW>(out, lane * 16 + j * RPI * D * 4, x4);
-                    else if (row0 + 2 * j + kg < rows) st16_partial<HOW>(po + (2 * j + kg) * D + l32 * 4, x4);
-                }
-            });
-        } else {
-            // packed row tiles: their rows lie apart
-            const PackedRows at(t, rows);
-            float *po = P.part_o + (int64_t(head) * P.part_rows + t.part_row_base) * D;
-            float *pml = P.part_ml + (int64_t(head) * P.part_rows + t.part_row_base) * 2;
-            if (how == kRowsThrough && !at.reachable(D)) how = kRowsPlain;
-            with_row_store(how, [&](auto h) __attribute__((always_inline)) {
-                constexpr RowStore HOW = decltype(h)::value;
-                if (row0 + l32 < rows && kg == 0) st8_partial<HOW>(pml + at.place(row0 + l32) * 2, m, l);
-#pragma unroll
-                for (int j = 0; j < 32 / RPI; ++j) {
-                    const f32x4 x4 = *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(get + j * RPI * kStageRow));
-                    const int row = row0 + j * RPI + row_o;
-                    if (row >= rows) continue;
-                    const int64_t off = at.place(row) * D + col_o * 4;
-                    if constexpr (HOW == kRowsThrough) st16_rows<HOW>(rows_at(po, -1), int(off) * 4, x4);
-                    else                               st16_partial<HOW>(po + off, x4);
-                }
-            });
-        }
+            for (int j = 0; j < 16; ++j) {
+                const f32x4 x4 = *reinterpret_cast<lds_f32x4_ptr>(uintptr_t(get + j * 2 * kStageRow));
+                if constexpr (HOW != kRowsCoherent) st16_rows<HOW>(out, lane * 16 + j * 2 * kHeadDim * 4, x4);
+                else if (row0 + 2 * j + kg < rows) st16_partial<HOW>(po + (2 * j + kg) * kHeadDim + l32 * 4, x4);
+            }
+        });
     }
     __syncthreads();                        // the staging areas (and the hand-over area) are free for the next task
 }
@@ -1424,25 +1304,25 @@ __device__ __forceinline__ void dense32_wave(const PacParams &P, const DevTask &
 // waves 0 .. 3 and run in the opposite phase.  Up to 128 rows: waves w and w+4 share rows 32w .. 32w+31
 // and take alternate blocks, again in opposite phases; short slices, for which the hand-over at the end
 // costs more than the overlap gains (about 1 us per task), keep one wave per row group.
-template <int DT, int D>
+template <int DT>
 __device__ __forceinline__ void run_dense32(const PacParams &P, const DevTask &t, int head, char *lds, RowStore how)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rows = t.n_req * P.group;
     if (rows > kSplitBlocksMaxRows || t.kv_len < kSplitBlocksMinLen) {
         const int row0 = wave * 32;
-        if (row0 >= rows)  dense32_wave<DT, D, kHelper, 1>(P, t, head, lds, wave, 0, 0, how);
-        else if (wave & 4) dense32_wave<DT, D, kVectorFirst, 1>(P, t, head, lds, wave, row0, rows, how);
-        else               dense32_wave<DT, D, kMatrixFirst, 1>(P, t, head, lds, wave, row0, rows, how);
+        if (row0 >= rows)  dense32_wave<DT, kHelper, 1>(P, t, head, lds, wave, 0, 0, how);
+        else if (wave & 4) dense32_wave<DT, kVectorFirst, 1>(P, t, head, lds, wave, row0, rows, how);
+        else               dense32_wave<DT, kMatrixFirst, 1>(P, t, head, lds, wave, row0, rows, how);
     } else {
         const int row0 = (wave & 3) * 32;
-        if (row0 >= rows)  dense32_wave<DT, D, kHelper, 2>(P, t, head, lds, wave, 0, 0, how);
-        else if (wave & 4) dense32_wave<DT, D, kVectorFirst, 2>(P, t, head, lds, wave, row0, rows, how);
-        else               dense32_wave<DT, D, kMatrixFirst, 2>(P, t, head, lds, wave, row0, rows, how);
+        if (row0 >= rows)  dense32_wave<DT, kHelper, 2>(P, t, head, lds, wave, 0, 0, how);
+        else if (wave & 4) dense32_wave<DT, kVectorFirst, 2>(P, t, head, lds, wave, row0, rows, how);
+        else               dense32_wave<DT, kMatrixFirst, 2>(P, t, head, lds, wave, row0, rows, how);
     }
 }
 
-// ---- tile path: 17 .. 64 rows of 64 channels, 17 .. 128 rows of 256 -------------------------------------
+// ---- tile path: 17 .. 256 rows of 64 channels, 17 .. 128 rows of 256 ------------------------------------
 //
 // With 64 and 256 channels the plan tiles query sets 32 (16) rows at a time.  Sibling row tiles of one KV
 // slice run here as ONE task (the device image packs them, DevTask): the slice then travels HBM -> LDS once
@@ -1775,8 +1655,9 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 {
     const int rows = t.n_req * P.group;
     if constexpr (D == 64) {            // row groups of 32: up to two, four, eight
-        if (rows <= 64) run_tile_of<DT, D, 2, 4>(P, t, head, lds, how);
-        else            run_dense32<DT, D>(P, t, head, lds, how);
+        if (rows <= 64)       run_tile_of<DT, D, 2, 4>(P, t, head, lds, how);
+        else if (rows <= 128) run_tile_of<DT, D, 2, 2>(P, t, head, lds, how);
+        else                  run_tile_of<DT, D, 2, 1>(P, t, head, lds, how);
     } else {                            // a row group per wave, of 16 or of 32 rows
         if (rows <= 64) run_tile_of<DT, D, 1, 1>(P, t, head, lds, how);
         else            run_tile_of<DT, D, 2, 1>(P, t, head, lds, how);
@@ -2266,7 +2147,7 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
 {
     PacParams P = params;
     if constexpr (!FUSED) P.arrive = nullptr;
-    // kFormWide: the dense path (128 channels, eight waves) or packed row tiles (64 and 256 channels)
+    // kFormWide: the dense path (128 channels, eight waves) or the tile path (64 and 256 channels)
     constexpr bool WIDE = FORM == kFormWide, DENSE = WIDE && D == kHeadDim, TILES = WIDE && D != kHeadDim;
     constexpr bool FINISH = FORM == kFormFinish;
     constexpr int W = kernel_waves(FORM, D);
@@ -2356,7 +2237,7 @@ pac_kernel(const PacParams params)     // 256 channels: two blocks of K and V in
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 1, W, D, FINISH>(P, t, own, lds, wave);
                     else             run_stream<DT, false, 1, W, D, FINISH>(P, t, own, lds, wave);
                 }
-                else if constexpr (DENSE) run_dense32<DT, D>(P, t, head, lds, how);
+                else if constexpr (DENSE) run_dense32<DT>(P, t, head, lds, how);
                 else if constexpr (stream_tiles(D) == 2 && !FINISH) {   // 17 .. 32 rows of 64 channels: two row tiles
                     if (t.flags & kTaskReadOnce) run_stream<DT, true, 2, W, D>(P, t, head_of(t, i), lds, wave);
                     else             run_stream<DT, false, 2, W, D>(P, t, head, lds, wave);
@@ -2429,7 +2310,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 template <int D>
 constexpr int wide_lds_bytes()
 {
-    if constexpr (D <= kHeadDim) return kRingBytes;
+    if constexpr (D == kHeadDim) return kRingBytes;
     else                         return TilePath<D>::kRingBytes;
 }
 

@@ -142,8 +142,6 @@ TaskLists queue_entries(int32_t num_tasks, int32_t num_slots, Cost cost, Short i
 //   64 channels, two workgroups per CU:  16 rows 10.1 / 41.9 / 87.3,  32 rows 15.5 / 50.3 / 95.2
 //   64 channels, one, packed:            64 rows 11.6 / 28.4 / 50.9, 128 rows 14.5 / 39.6 / 70.6, 256 rows 20.3 / 61.3 / 110
 //   256 channels (one per CU):           16 rows 22.4 / 82.3 / 174,   64 rows 30.0 / 96.7 / 176,  128 rows 42.6 / 122 / 220
-// (Since packs of more than 64 rows of 64 channels run in the dense path, 128 and 256 rows take 12.8 / 33.3 / 58.7 and
-// 17.5 / 47.8 / 87.8; the prices, by which plans are packed, are as fitted before.)
 // (without packs the same nodes of 64 / 128 rows took 23.4 / 71.7 / 129 and 45.3 / 123 / 222 with 64 channels,
 // two per CU, and 95 / 335 / 709 and 173 / 614 / 1311 with 256).
 int64_t task_cost(const PlanData &p, int32_t rows, int32_t len, bool packed)

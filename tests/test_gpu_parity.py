@@ -12,7 +12,7 @@ import pytest
 import torch
 
 from helpers import (DIVIDED_PACKS, DIVIDED_PACKS_OPTS, LONG_DIVISIONS, ROW_STORES, ROW_STORES_OPTS, divided_packs_forest,
-                     long_division_forest, row_stores_forest)
+                     long_division_forest, pool_row, q_float64, request_context, row_stores_forest, set_token, token_slot)
 from oracle import attention as A
 from workloads import (HeadConfig, Forest, make_workload, make_small_config, make_config,
                        two_level_forest, three_level_forest, unshared_forest, random_forest,
@@ -227,8 +227,8 @@ def test_divided_nodes_are_packed(d, hq, hkv, requests, widest, uneven, opts, dt
 @pytest.mark.parametrize("group,requests", [(5, 13), (8, 12), (1, 97), (8, 16), (3, 43), (8, 20), (8, 25), (15, 17), (8, 32)])
 @pytest.mark.parametrize("opts", [{"num_slots": 2}, {"num_slots": 2, "fused": 1}, {"num_slots": 3, "schedule": 1}])
 def test_dense_packs_of_64_channels(group, requests, opts):
-    """Packs of 65 .. 256 rows of 64 channels: the dense path's blocks of 64 tokens, edges of row groups of 32, of one
-    block, of the ring (512 tokens) and of the length from which two waves share a row group (1024, up to 128 rows)."""
+    """Packs of 65 .. 256 rows of 64 channels: edges of row groups of 32, of one and two blocks, of an interval of the ring
+    (128 tokens), of the ring (512 tokens), two waves per row group (up to 128 rows) and one."""
     C = _C()
     rows = group * requests
     lens = [1, 63, 64, 65, 447, 448, 449, 511, 512, 513, 1023, 1024, 1088, 1089, 1216, 1300]
@@ -241,6 +241,148 @@ def test_dense_packs_of_64_channels(group, requests, opts):
     widest = max(t["n_req"] * group for t in pa.export()["tasks"])
     assert C.codec_plan_device_bytes(pa.plan) < _image_bytes_without_packs(pa.export(), w.paged, w.head) and widest <= 32 < rows
     pa.close()
+
+
+def _is_packed(w, **opts):
+    C = _C()
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cpu", **opts)
+    packed = C.codec_plan_device_bytes(pa.plan) < _image_bytes_without_packs(pa.export(), w.paged, w.head)
+    pa.close()
+    return packed
+
+
+def _packs_workload(name, d, group, requests, lens, dtype, q_scale=1.0):
+    """Nodes that end `requests` requests each, whose row tiles are packed (128 channels: dense tasks) on two slots."""
+    f = Forest(np.full(len(lens), -1), np.array(lens), np.repeat(np.arange(len(lens)), requests))
+    w = make_workload(name, f, HeadConfig(2 * group, 2, d, dtype), seed=2000 + d + requests, q_scale=q_scale,
+                      layout="htd" if requests % 8 else "thd")
+    opts = {"num_slots": 2, "split_align": 2048}
+    assert _is_packed(w, **opts) == (d != 128)
+    return w, opts
+
+
+def _contexts_of_nodes(w):
+    """K and V of request r and one KV head; requests that end at one node share them."""
+    known = {}
+
+    def get(r, kvh):
+        key = int(w.forest.req_node[r]), kvh
+        if key not in known:
+            known[key] = request_context(w, r, kvh)
+        return known[key]
+    return get
+
+
+@pytest.mark.parametrize("group,requests", [(8, 12), (8, 16)])
+@pytest.mark.parametrize("dtype", [DTYPE_BF16, DTYPE_FP16])
+def test_precision_of_packs_of_short_slices(group, requests, dtype):
+    """What the rounding of the probabilities to 16 bits costs in the partial rows (fp32) of packs of 96 and 128 rows of 64
+    channels on up to 64 tokens, where the largest probability of a row dominates: no more than with a reference per
+    32 tokens, against whose maximum that probability is 1 and exact.  One reference for 64 tokens has errors 1.11 .. 1.14
+    times as large on these lengths.  The bound is the error of that arithmetic itself, in 64 bits but for the rounding
+    (measured: 0.9999 .. 1.0000 of it), and 4 % for scores that differ in their last bits."""
+    C = _C()
+    w, opts = _packs_workload(f"precision-{group}-{requests}", 64, group, requests, [33, 40, 48, 64] * 4, dtype, q_scale=2.0)
+    wd = w.to("cuda:0")
+    pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", **opts)
+    view = pa.export()
+    pa.partial_attention(wd.q, wd.k_pool, wd.v_pool)
+    torch.cuda.synchronize()
+    n, h = view["part_rows"], w.head.num_kv_heads
+    ws = pa.workspace.view(torch.float32).cpu().double()
+    rows, stats = ws[:h * n * 64].view(h, n, 64), ws[h * n * 64:][:h * n * 2].view(h, n, 2)
+    pa.close()
+    context = _contexts_of_nodes(w)
+    sq = {"run": 0.0, "bound": 0.0}
+    for r in range(w.forest.num_requests):
+        base = view["req_part"][view["req_part_off"][r]]
+        assert view["req_part_off"][r + 1] == view["req_part_off"][r] + 1
+        for kvh in range(h):
+            K, V = (torch.from_numpy(x) for x in context(r, kvh))
+            s = w.q[r, kvh * group:(kvh + 1) * group].double() @ K.T * (w.head.scale / np.log(2.0))
+            p = torch.exp2(s)
+            exact = p @ V / p.sum(1, keepdim=True)
+            o, l = torch.zeros_like(exact), torch.zeros(group, 1, dtype=torch.float64)
+            for b in range(0, s.shape[1], 32):
+                m = s[:, b:b + 32].amax(1, keepdim=True)
+                p = torch.exp2(s[:, b:b + 32] - m).to(w.q.dtype).double()
+                o, l = o + p @ V[b:b + 32] * torch.exp2(m), l + p.sum(1, keepdim=True) * torch.exp2(m)
+            got = rows[kvh, base:base + group] / stats[kvh, base:base + group, 1:]
+            sq["run"] += float(((got - exact) ** 2).sum())
+            sq["bound"] += float(((o / l - exact) ** 2).sum())
+    off = (sq["run"] / sq["bound"]) ** 0.5
+    print(f"[case] {w.name} {dtype}: {off:.4f} of the error with a reference per 32 tokens", flush=True)
+    assert off <= 1.04, off
+
+
+@pytest.mark.parametrize("d,group,requests", [(64, 8, 8), (64, 8, 12), (64, 8, 16), (64, 8, 32), (256, 8, 8), (256, 8, 16)])
+@pytest.mark.parametrize("opts2", [{}, {"fused": 1}])
+def test_rows_that_see_nothing_at_first_in_packs(d, group, requests, opts2):
+    """Tokens whose keys hold -inf score -inf for every row of a pack and weigh nothing: the first of a slice (part of a
+    block, one, several, all but one token), and those of a whole node above the requests' own."""
+    first = [1, 31, 32, 64, 65, 128, 300, 599]
+    w, opts = _packs_workload(f"unseen-{d}-{requests}", d, group, requests, [600] * len(first), DTYPE_BF16)
+    f = concat_forests(w.forest, two_level_forest(97, [40] * requests))
+    w = make_workload(f"unseen-{d}-{requests}", f, w.head, seed=2100 + d, layout="htd")
+    w.q[:, :, 0] = w.q[:, :, 0].abs() + 0.5
+    row = torch.zeros(d)
+    row[0] = -float("inf")
+    for node, n in list(enumerate(first)) + [(len(first), 97)]:
+        for t in range(n):
+            for kvh in range(2):
+                set_token(w, node, t, kvh, k_row=row)
+    assert _is_packed(w, **opts, **opts2)
+    got, _ = run_gpu(w, **opts, **opts2)
+    context = _contexts_of_nodes(w)
+    assert not np.any(np.isnan(got))
+    for r in range(w.forest.num_requests):
+        for kvh in range(2):
+            K, V = context(r, kvh)
+            seen = np.isfinite(K[:, 0])
+            s = q_float64(w)[r, kvh * group:(kvh + 1) * group] @ K[seen].T * w.head.scale
+            p = np.exp(s - s.max(1, keepdims=True))
+            ref = p @ V[seen] / p.sum(1, keepdims=True)
+            err = np.abs(got[r, kvh * group:(kvh + 1) * group] - ref)
+            assert np.all(err <= 2e-3 + 2.0 ** -7 * np.abs(ref)), (r, kvh, err.max())
+
+
+@pytest.mark.parametrize("d,group,requests", [(64, 8, 8), (64, 8, 12), (64, 8, 16), (64, 8, 32), (128, 8, 12), (128, 8, 32),
+                                              (256, 8, 8), (256, 8, 16)])
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("dtype", [DTYPE_BF16, DTYPE_FP16])
+def test_references_that_are_outgrown_in_packs(d, group, requests, rising, dtype):
+    """Scores that outgrow a row's reference again and again after the first block, one wave and several per row group:
+    queries of eight times the usual size (outgrown by chance), and scores that rise by 8 (11.5 binary orders) from one 32
+    tokens to the next.  Few tokens then have all the weight, and roundings do not average out: each probability is off
+    by at most the unit roundoff u of its type, which moves the output by at most u times the mean distance of V from
+    it, and the output is rounded once more.  Beside that, scores of up to 460 binary orders are off by up to 2.7e-5 of
+    one in fp32, and fp16 has no probabilities below 2^-24 (1300 tokens: 1e-4)."""
+    w, opts = _packs_workload(f"outgrown-{d}-{requests}-{rising}", d, group, requests, [63, 64, 65, 200, 513, 1024, 1300], dtype,
+                              q_scale=1.0 if rising else 8.0)
+    if rising:
+        w.q[:, :, 0] = 8.0
+        for node, n in enumerate(w.forest.node_len):
+            for t in range(int(n)):
+                page, slot = token_slot(w, node, t)
+                for kvh in range(2):
+                    pool_row(w.k_pool, w, page, slot, kvh)[0] = (t // 32) / w.head.scale
+    got, _ = run_gpu(w, **opts)
+    assert not np.any(np.isnan(got))
+    context = _contexts_of_nodes(w)
+    u = 2.0 ** -8 if dtype == DTYPE_BF16 else 2.0 ** -11             # 8 and 11 significant bits, to nearest
+    for r in range(w.forest.num_requests):
+        if r % requests not in (0, 3, requests // 2, requests - 1):
+            continue
+        for kvh in range(2):
+            K, V = context(r, kvh)
+            s = q_float64(w)[r, kvh * group:(kvh + 1) * group] @ K.T * w.head.scale
+            p = np.exp(s - s.max(1, keepdims=True))
+            p /= p.sum(1, keepdims=True)
+            ref = p @ V
+            spread = np.stack([p[i] @ np.abs(V - ref[i]) for i in range(group)])
+            bound = u * (spread + np.abs(ref)) * 1.01 + 3e-4
+            err = np.abs(got[r, kvh * group:(kvh + 1) * group] - ref)
+            assert np.all(err <= bound), (r, kvh, float((err - bound).max()), float(err.max()))
 
 
 @pytest.mark.parametrize("d,hq,hkv,length,samples", [(256, 16, 8, 256, 16), (256, 16, 8, 1024, 32), (256, 32, 8, 200, 16),

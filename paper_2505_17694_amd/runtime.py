@@ -78,9 +78,6 @@ class PlannedAttention:
         p, h = self.paged, self.head
         last = ((p.num_pages - 1) * p.page_stride + (h.page_size - 1) * p.token_stride
                 + (h.num_kv_heads - 1) * p.head_stride + h.head_dim)
-        # a contiguous tensor holds all its elements from its first one on
-        if pool.is_contiguous() and pool.numel() >= last and pool.element_size() == 2 and pool.device == self.device:
-            return
         have = pool.untyped_storage().nbytes() // pool.element_size() - pool.storage_offset()
         if pool.device != self.device or pool.element_size() != 2 or last > have:
             raise ValueError(f"{what}: {have} elements from the tensor's first one on {pool.device}, "

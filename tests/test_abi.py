@@ -144,6 +144,23 @@ def test_runtime_refuses_pools_smaller_than_the_strides_reach():
     pa.close()
 
 
+def test_runtime_refuses_pools_whose_storage_was_shrunk():
+    """A tensor keeps its shape, strides and element count when its storage is given back (as sharded weights do between
+    steps): the memory behind it is what counts."""
+    from workloads import make_workload
+    for layout in ("htd", "thd"):
+        w = make_workload("shrunk", two_level_forest(100, [20, 30]), HeadConfig(8, 2, 128, DTYPE_BF16), seed=3, layout=layout)
+        pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cpu")
+        pa._check_pool(w.k_pool, "k_pool")
+        whole = w.k_pool.untyped_storage().nbytes()
+        for left in (0, whole - 2):
+            w.k_pool.untyped_storage().resize_(left)
+            assert w.k_pool.is_contiguous() and w.k_pool.numel() * 2 == whole
+            with pytest.raises(ValueError, match="k_pool"):
+                pa.decode(w.q, w.k_pool, w.v_pool)
+        pa.close()
+
+
 def test_entry_points_added_for_measurement_and_for_callers_without_a_workspace_check_their_arguments():
     """Argument errors that are caught before any HIP call."""
     assert C.codec_static_scratch_bytes() == 64 << 20

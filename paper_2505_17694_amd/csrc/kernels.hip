@@ -1942,7 +1942,7 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
 // dependent reads: one wave makes four or five for a list of 32 (line, fifteen rows, CSR entries and eight rows, twice).
 // Here WAVES waves take a chunk each, wave 0 the first, after two dependent reads (line, rows), and their sums meet in LDS.
 // The references of all rows up to the end of its chunk, whose maximum a chunk's sum refers to, are read by every wave, a
-// row per lane.  us per step, one wave / split: a lone request of 8191 tokens, 32 / 8 heads, 32 partials 14.9 / 13.5;
+// row per lane and each once.  us per step, one wave / split: a lone request of 8191 tokens, 32 / 8 heads, 32 partials 14.9 / 13.5;
 // one KV head, a two-level tree of three requests, 58 partials 21.6 / 13.4; 24 requests, 48 partials 31.6 / 27.2.  Measured
 // and dropped: the sums of the waves against references of their own (12.9, but the single launch, which has to round
 // alike, then took up to 16 % longer); the rows handed over through LDS as they are and folded there (14.4).
@@ -1962,7 +1962,9 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
     const int total = line[0];
     const int32_t *list = line + 1;
     const int64_t head_base = int64_t(blockIdx.x) * P.part_rows + hj;
-    float M = -INFINITY, L = 0.f, acc[CPL] = {};        // the wave's chunk; wave 0: all chunks so far
+    float M, L = 0.f, acc[CPL] = {};                    // the wave's chunk; wave 0: all chunks so far
+    float top = -INFINITY;                              // maximum of the references of rows 0 .. seen - 1
+    int seen = 0;
 
     // rows begin .. begin + cnt - 1 of the list, cnt at most N
     auto fold = [&](int begin, int cnt, auto width) {
@@ -1985,9 +1987,11 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
             }
         }
 #pragma unroll 1
-        for (int j = lane; j < begin + cnt; j += LPR) M = fmaxf(M, P.part_ml[(head_base + list[j]) * 2]);
+        for (int j = seen + lane; j < begin + cnt; j += LPR) top = fmaxf(top, P.part_ml[(head_base + list[j]) * 2]);
 #pragma unroll
-        for (int d = 1; d < LPR; d *= 2) M = fmaxf(M, __shfl_xor(M, d));
+        for (int d = 1; d < LPR; d *= 2) top = fmaxf(top, __shfl_xor(top, d));
+        seen = begin + cnt;
+        M = top;
 #pragma unroll
         for (int j = 0; j < N; ++j)
             if (j < cnt) {
@@ -2004,7 +2008,6 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
         if (wave > 0) {
             const int begin = base + (wave - 1) * kFoldChunk, cnt = total - begin < kFoldChunk ? total - begin : kFoldChunk;
             if (cnt > 0) {
-                M = -INFINITY;
                 L = 0.f;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) acc[c] = 0.f;

@@ -830,6 +830,39 @@ def test_split_reduction(parts, d, hq, hkv, requests):
     assert np.array_equal(one, got)
 
 
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 16, 2), (64, 3, 3)])
+def test_split_reduction_of_very_long_lists(d, hq, hkv):
+    """Many rounds of the split form: right, and four times the rows take at most six times as long (a wave that reads the
+    references of the whole list so far in every round takes ten to twelve times as long)."""
+    C = _C()
+    us = {}
+    for parts in (1024, 4096):
+        w = make_workload(f"long-{parts}-{d}", unshared_forest([32 * parts]), HeadConfig(hq, hkv, d, DTYPE_BF16), seed=1800 + d,
+                          layout="htd")
+        opts = {"num_slots": 5, "split_align": 32, "fixed_slices": parts}
+        got, view = check(w, sel=[(0, 0), (0, hq - 1)], **opts)
+        assert int(view["req_part_off"][-1]) == parts
+        wd = w.to("cuda:0")
+        pa = C.PlannedAttention(w.forest, w.paged, w.head, device="cuda:0", **opts)
+        out = torch.empty_like(wd.q)
+        pa.partial_attention(wd.q, wd.k_pool, wd.v_pool)
+        pa.partial_reduction(out)
+        times = []
+        for _ in range(5):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(10):
+                pa.partial_reduction(out)
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end) * 100)
+        pa.close()
+        assert np.array_equal(out.double().cpu().numpy(), got)
+        us[parts] = min(times)
+    print(f"[case] {d} channels, {hq}/{hkv} heads: us by rows {us}", flush=True)
+    assert us[4096] <= 6 * us[1024], us
+
+
 @pytest.mark.parametrize("d,hq,hkv,leaves", [(128, 32, 8, 110), (128, 28, 4, 200), (128, 9, 3, 280), (64, 16, 8, 110), (64, 12, 12, 90)])
 @pytest.mark.parametrize("opts", [{"num_slots": 1}, {"num_slots": 2}, {"num_slots": 3, "schedule": 1}])
 def test_stream_tasks_go_round_the_heads(d, hq, hkv, leaves, opts):

@@ -1949,57 +1949,37 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
 template <int DT, int D, int RPW, int WAVES>
 __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergeParams P)
 {
-    constexpr int LPR = 64 / RPW, CPL = D / LPR;
+    using W = WaveRows<DT, D, RPW>;
+    constexpr int CPL = W::CPL;
     __shared__ float sums[WAVES - 1][CPL + 2][64];
     const int per_req = P.group / RPW;
     const int unit = blockIdx.z * gridDim.y + blockIdx.y;
     if (unit >= P.num_requests * per_req) return;
     const int r = unit / per_req;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave_lane = threadIdx.x & 63;
-    const int lane = wave_lane % LPR;
-    const int hj = (unit - r * per_req) * RPW + wave_lane / LPR;
+    const W at(P, blockIdx.x, r, (unit - r * per_req) * RPW);
     const int32_t *line = P.req_line + int64_t(r) * split_line_words(WAVES);
     const int total = line[0];
     const int32_t *list = line + 1;
-    const int64_t head_base = int64_t(blockIdx.x) * P.part_rows + hj;
-    float M, L = 0.f, acc[CPL] = {};                    // the wave's chunk; wave 0: all chunks so far
+    float M, L, acc[CPL];                               // the wave's chunk; wave 0: all chunks so far
     float top = -INFINITY;                              // maximum of the references of rows 0 .. seen - 1
     int seen = 0;
 
     // rows begin .. begin + cnt - 1 of the list, cnt at most N
     auto fold = [&](int begin, int cnt, auto width) {
         constexpr int N = decltype(width)::value;
-        float2 ml[N];
-        float o[N][CPL];
+        int rows[N];
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            if (j >= cnt) continue;                     // wave-uniform: no load for a partial that does not exist
-            const int64_t prow = head_base + list[begin + j];
-            ml[j] = *reinterpret_cast<const float2 *>(P.part_ml + prow * 2);
-            const float *src = P.part_o + prow * D + lane * CPL;
-            if constexpr (CPL == 4) {
-                const f32x4 x = *reinterpret_cast<const f32x4 *>(src);
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) o[j][c] = x[c];
-            } else {
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) o[j][c] = src[c];
-            }
-        }
+        for (int j = 0; j < N; ++j) rows[j] = list[begin + j];      // behind the list: see merge_kernel
+        Chunk<N, CPL> x;
+        x.load(P, at, rows, cnt);
 #pragma unroll 1
-        for (int j = seen + lane; j < begin + cnt; j += LPR) top = fmaxf(top, P.part_ml[(head_base + list[j]) * 2]);
+        for (int j = seen + at.lane; j < begin + cnt; j += W::LPR) top = fmaxf(top, P.part_ml[(at.head_base + at.row + list[j]) * 2]);
 #pragma unroll
-        for (int d = 1; d < LPR; d *= 2) top = fmaxf(top, __shfl_xor(top, d));
+        for (int d = 1; d < W::LPR; d *= 2) top = fmaxf(top, __shfl_xor(top, d));
         seen = begin + cnt;
         M = top;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j < cnt) {
-                const float w = weight(ml[j].x, M);
-                L = __builtin_fmaf(ml[j].y, w, L);
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(o[j][c], w, acc[c]);
-            }
+        x.sum_up(cnt, M, L, acc);
     };
     int base = kInlineParts;                            // first row of wave 1's chunk
     if (wave == 0) fold(0, kInlineParts < total ? kInlineParts : total, std::integral_constant<int, kInlineParts>{});
@@ -2008,9 +1988,6 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
         if (wave > 0) {
             const int begin = base + (wave - 1) * kFoldChunk, cnt = total - begin < kFoldChunk ? total - begin : kFoldChunk;
             if (cnt > 0) {
-                L = 0.f;
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
                 fold(begin, cnt, std::integral_constant<int, kFoldChunk>{});
                 float (*put)[64] = sums[wave - 1];
                 put[CPL][wave_lane] = L;
@@ -2036,16 +2013,7 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
         list = P.req_part + P.req_part_off[r];
         __syncthreads();                                // the sums of this round have been read
     }
-    if (wave > 0) return;
-    const float inv = 1.f / L;
-    char *out = static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + blockIdx.x * P.group + hj) * D + lane * CPL) * 2;
-    if constexpr (CPL == 1) {
-        *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(acc[0] * inv, 0.f) & 0xFFFFu);
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; c += 2)
-            *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(acc[c] * inv, acc[c + 1] * inv);
-    }
+    if (wave == 0) at.store(L, acc);
 }
 
 // ---- single-launch mode: the reduction inside the attention launch (Sec. 4.3, parallel reduction) ----

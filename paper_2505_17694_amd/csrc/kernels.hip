@@ -2390,7 +2390,7 @@ int launch_stream_read(const void *buf, uint64_t chunks, uint64_t mult, int once
 }
 
 template <int DT, int D>
-void launch_merge_of(const MergeParams &p, hipStream_t s)
+int launch_merge_of(const MergeParams &p, hipStream_t s)
 {
     // a wave reduces 256 / D rows at a time where the rows of a KV head's group divide that evenly
     constexpr int kWide = 256 / D;
@@ -2407,27 +2407,30 @@ void launch_merge_of(const MergeParams &p, hipStream_t s)
         if (wide) launch(merge_split_kernel<DT, D, kWide, W>, 1, W);
         else      launch(merge_split_kernel<DT, D, 1, W>, 1, W);
     };
-    if (p.split_waves == 4)      split(std::integral_constant<int, 4>{});
-    else if (p.split_waves == 8) split(std::integral_constant<int, 8>{});
     auto one = [&](auto form) {
         constexpr int LONG = decltype(form)::value;
         if (wide) launch(merge_kernel<DT, D, kWide, LONG>, kMergeWaves, kMergeWaves);
         else      launch(merge_kernel<DT, D, 1, LONG>, kMergeWaves, kMergeWaves);
     };
-    if (p.split_waves == 0)      one(std::integral_constant<int, 0>{});
-    else if (p.split_waves == 1) one(std::integral_constant<int, 1>{});
-    else if (p.split_waves == 2) one(std::integral_constant<int, 2>{});
+    switch (p.split_waves) {
+    case 0: one(std::integral_constant<int, 0>{}); break;
+    case 1: one(std::integral_constant<int, 1>{}); break;
+    case 2: one(std::integral_constant<int, 2>{}); break;
+    case 4: split(std::integral_constant<int, 4>{}); break;
+    case 8: split(std::integral_constant<int, 8>{}); break;
+    default: return int(hipErrorInvalidValue);
+    }
+    return int(hipGetLastError());
 }
 
 int launch_merge(const MergeParams &p, int dtype, int head_dim, void *stream)
 {
-    if (head_dim != 64 && head_dim != 128 && head_dim != 256) return int(hipErrorInvalidValue);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool half = dtype == CODEC_DTYPE_FP16;
-    if (head_dim == 64)       half ? launch_merge_of<CODEC_DTYPE_FP16, 64>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 64>(p, s);
-    else if (head_dim == 128) half ? launch_merge_of<CODEC_DTYPE_FP16, 128>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 128>(p, s);
-    else                      half ? launch_merge_of<CODEC_DTYPE_FP16, 256>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 256>(p, s);
-    return int(hipGetLastError());
+    if (head_dim == 64)  return half ? launch_merge_of<CODEC_DTYPE_FP16, 64>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 64>(p, s);
+    if (head_dim == 128) return half ? launch_merge_of<CODEC_DTYPE_FP16, 128>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 128>(p, s);
+    if (head_dim == 256) return half ? launch_merge_of<CODEC_DTYPE_FP16, 256>(p, s) : launch_merge_of<CODEC_DTYPE_BF16, 256>(p, s);
+    return int(hipErrorInvalidValue);
 }
 
 }  // namespace codec

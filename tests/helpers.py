@@ -2,7 +2,7 @@
 import numpy as np
 import torch
 
-from workloads import Forest, bits_to_float64, concat_forests, two_level_forest
+from workloads import Forest, bits_to_float64, concat_forests, two_level_forest, unshared_forest, DTYPE_BF16, DTYPE_FP16
 
 
 def token_slot(w, node, t):
@@ -95,3 +95,27 @@ LONG_DIVISIONS = [32767, 32768]
 
 def long_division_forest(slices):
     return Forest(np.array([-1]), np.array([32 * slices]), np.zeros(32, np.int64))
+
+
+# Stream tasks that go round the KV heads in two launches ([token][head] pools): (channels, query heads, KV heads, data
+# type, nodes, requests per node, requests below a shared node, form of the attention kernel: 0 stream tasks only, 1 all
+# task shapes).  Contexts of up to 2300 tokens are cut in two: teams of waves and single-wave runs; 24 rows of 64 channels
+# are two row tiles; the shared node brings dense tasks (128 channels) or, with 64, packed row tiles.  GOING_ROUND: all
+# beside a shared node, in the form for all task shapes.
+ROTATING = [(128, 32, 8, DTYPE_BF16, 60, 1, 0, 0), (128, 32, 8, DTYPE_FP16, 60, 1, 0, 0), (128, 28, 4, DTYPE_FP16, 120, 1, 0, 0),
+            (128, 9, 3, DTYPE_BF16, 140, 2, 0, 0), (64, 16, 8, DTYPE_BF16, 60, 1, 0, 0), (64, 16, 8, DTYPE_FP16, 60, 1, 0, 0),
+            (64, 64, 8, DTYPE_FP16, 60, 3, 0, 0), (64, 32, 4, DTYPE_BF16, 110, 3, 0, 0),
+            (128, 32, 8, DTYPE_FP16, 60, 1, 40, 1), (64, 64, 8, DTYPE_FP16, 30, 1, 64, 1), (64, 64, 8, DTYPE_BF16, 30, 1, 64, 1)]
+GOING_ROUND = [(128, 32, 8, 110), (128, 28, 4, 200), (128, 9, 3, 280), (64, 16, 8, 110), (64, 12, 12, 90)]
+GOING_ROUND_OPTS = [{"num_slots": 1}, {"num_slots": 2}, {"num_slots": 3, "schedule": 1}]
+ROTATING_OPTS = [{"num_slots": 2, "fixed_slices": 2}, {"num_slots": 3, "fixed_slices": 2, "schedule": 1}]
+
+
+def going_round_forest(leaves):
+    return concat_forests(two_level_forest(300, [17 + 13 * (i % 9) for i in range(leaves)]), unshared_forest([2200, 33, 700]))
+
+
+def rotating_forest(nodes, requests, below):
+    lens = [17 + (389 * i) % 2290 for i in range(nodes)]
+    f = Forest(np.full(nodes, -1), np.array(lens), np.repeat(np.arange(nodes), requests))
+    return concat_forests(f, two_level_forest(700, [33 + 17 * (i % 5) for i in range(below)])) if below else f

@@ -11,8 +11,9 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import (DIVIDED_PACKS, DIVIDED_PACKS_OPTS, LONG_DIVISIONS, ROW_STORES, ROW_STORES_OPTS, divided_packs_forest,
-                     long_division_forest, pool_row, q_float64, request_context, row_stores_forest, set_token, token_slot)
+from helpers import (DIVIDED_PACKS, DIVIDED_PACKS_OPTS, GOING_ROUND, GOING_ROUND_OPTS, LONG_DIVISIONS, ROTATING, ROTATING_OPTS,
+                     ROW_STORES, ROW_STORES_OPTS, divided_packs_forest, going_round_forest, long_division_forest, pool_row,
+                     q_float64, request_context, rotating_forest, row_stores_forest, set_token, token_slot)
 from oracle import attention as A
 from workloads import (HeadConfig, Forest, make_workload, make_small_config, make_config,
                        two_level_forest, three_level_forest, unshared_forest, random_forest,
@@ -863,17 +864,31 @@ def test_split_reduction_of_very_long_lists(d, hq, hkv):
     assert us[4096] <= 6 * us[1024], us
 
 
-@pytest.mark.parametrize("d,hq,hkv,leaves", [(128, 32, 8, 110), (128, 28, 4, 200), (128, 9, 3, 280), (64, 16, 8, 110), (64, 12, 12, 90)])
-@pytest.mark.parametrize("opts", [{"num_slots": 1}, {"num_slots": 2}, {"num_slots": 3, "schedule": 1}])
+@pytest.mark.parametrize("d,hq,hkv,leaves", GOING_ROUND)
+@pytest.mark.parametrize("opts", GOING_ROUND_OPTS)
 def test_stream_tasks_go_round_the_heads(d, hq, hkv, leaves, opts):
     """[token][head] pools, plans long enough and with enough tasks for their stream tasks to go round the KV heads: every
     task runs once for every head, from static lists and the queue, single-wave runs and whole workgroups, beside
-    dense or two-tile tasks that stay where they are."""
-    f = concat_forests(two_level_forest(300, [17 + 13 * (i % 9) for i in range(leaves)]), unshared_forest([2200, 33, 700]))
+    dense or two-tile tasks that stay where they are (which kernels run is asserted on the host, in the tests of the
+    kernels' choice)."""
+    f = going_round_forest(leaves)
     w = make_workload(f"turns-{d}-{hq}-{hkv}", f, HeadConfig(hq, hkv, d, DTYPE_BF16), seed=1900 + hq, poison=True, layout="thd")
     sel = [(r, h) for r in range(0, len(f.req_node), 3) for h in range(0, hq, 2)] + [(leaves, hq - 1), (leaves + 2, 0)]
     _, view = check(w, sel=sel, **opts)
     assert view["makespan"] >= 60000 and len(view["tasks"]) * hkv >= 768 and view["fused"] == 0
+
+
+@pytest.mark.parametrize("d,hq,hkv,dtype,nodes,requests,below,form", ROTATING)
+@pytest.mark.parametrize("opts", ROTATING_OPTS)
+def test_rotating_kernels(d, hq, hkv, dtype, nodes, requests, below, form, opts):
+    """The kernels whose stream tasks go round the KV heads, of both forms and data types (that these plans run them, and
+    which of their tasks go round, is asserted on the host, in the tests of the kernels' choice)."""
+    f = rotating_forest(nodes, requests, below)
+    w = make_workload(f"rotating-{d}-{hq}-{hkv}-{form}", f, HeadConfig(hq, hkv, d, dtype), seed=2200 + d + hq, poison=True, layout="thd")
+    sel = [(r, h) for r in range(0, f.num_requests, 3) for h in range(0, hq, 2)] + [(f.num_requests - 1, hq - 1), (1, 0)]
+    _, view = check(w, sel=sel, **opts)
+    rows = max(t["n_req"] for t in view["tasks"]) * (hq // hkv)
+    assert rows > 16 if form or requests > 2 else rows <= 16
 
 
 def _queue_cases():

@@ -2,8 +2,10 @@
 import numpy as np
 import pytest
 
+from helpers import GOING_ROUND, GOING_ROUND_OPTS, ROTATING, ROTATING_OPTS, going_round_forest, rotating_forest
 from kernel_choice import case, launches, reduction_status
-from workloads import Forest, HeadConfig, build_paged_kv, DTYPE_BF16, DTYPE_FP16
+from plan_image import plan_image
+from workloads import Forest, HeadConfig, build_paged_kv, unshared_forest, DTYPE_BF16, DTYPE_FP16
 
 
 def _case(f, head, layout="htd", **opts):
@@ -44,3 +46,61 @@ def test_reduction_form_by_the_longest_list_and_the_launch(d, hq, hkv, wide):
                               fixed_slices=n, num_slots=4))
             want.append(("merge_split_kernel" if form >= 4 else "merge_kernel", (DTYPE_FP16, d, wide, form)))
     assert [got["reduction"][0][:2] for got in launches(many)] == want
+
+
+@pytest.mark.parametrize("opts", ROTATING_OPTS)
+def test_rotating_kernels(opts):
+    """The plans of the GPU parity test of the same name run the kernels whose stream tasks go round the KV heads, and most
+    of their tasks do (those that alone read their slice, in a plan that reads little twice).  Heads that lie apart
+    ([head][token] pools), one launch and 256 channels stay with the others; so do one KV head and short plans (below)."""
+    cases, want = [], []
+    for d, hq, hkv, dtype, nodes, requests, below, form in ROTATING:
+        f, head = rotating_forest(nodes, requests, below), HeadConfig(hq, hkv, d, dtype)
+        im = plan_image(f, head, **opts)
+        recs = im["queue_recs" if im["schedule"] == 1 else "slot_recs"]
+        assert (recs["flags"] & 1).mean() > 0.5 and (len(im["packs"]) > 0) == (d == 64 and form == 1)
+        assert (form == 1 and d == 128) == (int(recs["n_req"].max()) * (hq // hkv) > (16 if d == 128 else 512))
+        for layout, extra, args in (("thd", {}, (dtype, form, d, 1, 0)), ("htd", {}, (dtype, form, d, 0, 0)),
+                                    ("thd", {"fused": 1}, (dtype, form, d, 0, 1))):
+            cases.append(_case(f, head, layout, **opts, **extra))
+            want.append(args)
+    wide = HeadConfig(16, 8, 256, DTYPE_BF16)
+    cases.append(_case(rotating_forest(120, 1, 0), wide, "thd", **opts))
+    want.append((DTYPE_BF16, 0, 256, 0, 0))
+    for got, args in zip(launches(cases), want):
+        assert got["tasks"] * 8 >= 768 and got["makespan"] >= 60000
+        assert got["decode"][0][:2] == ("pac_kernel", args)
+        two = args[:-1] + (0,)
+        assert got["attention"][0][:2] == ("pac_kernel", two if not args[-1] else args[:3] + (1, 0))
+
+
+@pytest.mark.parametrize("opts", GOING_ROUND_OPTS)
+def test_stream_tasks_go_round_the_heads(opts):
+    """The same for the plans of that GPU parity test."""
+    cases = []
+    for d, hq, hkv, leaves in GOING_ROUND:
+        f, head = going_round_forest(leaves), HeadConfig(hq, hkv, d, DTYPE_BF16)
+        im = plan_image(f, head, **opts)
+        assert (im["queue_recs" if im["schedule"] == 1 else "slot_recs"]["flags"] & 1).mean() > 0.5
+        cases.append(_case(f, head, "thd", **opts))
+    forms = [got["decode"][0][:2] for got in launches(cases)]
+    assert [(k, a[0], *a[2:]) for k, a in forms] == [("pac_kernel", DTYPE_BF16, d, 1, 0) for d, _, _, _ in GOING_ROUND]
+    assert {a[1] for _, a in forms} == {1}
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_plans_whose_tasks_do_not_go_round(d):
+    """By the plan's estimated time, its tasks of all heads and its KV heads: 60 us, 768, more than one."""
+    head = HeadConfig(32, 8, d)
+    f = unshared_forest([700] * 96)
+    cases = [_case(f, head, "thd", num_slots=4, fixed_slices=n) for n in (1, 2)]
+    cases += [_case(unshared_forest([700] * n), head, "thd", num_slots=2, fixed_slices=2) for n in (47, 48)]
+    cases += [_case(f, head, "thd", num_slots=64, fixed_slices=2),
+              _case(unshared_forest([700] * 400), HeadConfig(4, 1, d), "thd", num_slots=1, fixed_slices=2)]
+    seen = launches(cases)
+    forms = [got["attention"][0][1] for got in seen]
+    assert [(c["tasks"] * k, a[3]) for c, a, k in zip(seen, forms, (8, 8, 8, 8, 8, 1))] == [
+        (768, 1), (1536, 1), (752, 0), (768, 1), (1536, 0), (800, 0)]
+    assert [c["makespan"] >= 60000 for c in seen] == [True, True, True, True, False, True]
+    # finished rows: a kernel of its own (its tasks go round in any case), and nothing to reduce
+    assert [a[:2] for a in (seen[0]["decode"][0],)] == [("pac_kernel", (DTYPE_BF16, 2, d, 0, 0))] and len(seen[0]["decode"]) == 1

@@ -283,7 +283,7 @@ int partial_attention(const codec_plan_t *plan, const void *q, const void *k_pag
         else pp.arrive = reinterpret_cast<int32_t *>(const_cast<char *>(meta) + L.arrive);
     }
     const bool turns = !fused_out && layout->head_stride < layout->token_stride &&
-                       codec::heads_in_turn(int64_t(d.tasks.size()), d.head.num_kv_heads, d.makespan);
+                       codec::heads_in_turn(int64_t(d.tasks.size()), d.head.num_kv_heads, d.makespan, L.turning_tokens, L.tokens_read);
     if (int e = codec::launch_pac(pp, d.head.dtype, d.head.head_dim, L.num_slots, plan->max_task_rows, !d.packs.empty(), turns, stream))
         return hip_failure("partial attention launch", e);
     return CODEC_OK;

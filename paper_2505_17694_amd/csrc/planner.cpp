@@ -346,6 +346,12 @@ void build_device_image(PlanData &p)
     }
     for (int32_t len : p.node_len) tokens_held += len;
     const bool streaming_plan = 4 * tokens_read <= 5 * tokens_held;
+    auto read_once = [&](const DeviceTask &d) { return streaming_plan && readers[p.tasks[d.first].node] == 1; };
+    const int32_t stream_rows = p.head.head_dim == 128 ? kSoloMaxRows : max_task_rows(p.head.head_dim);
+    L.tokens_read = tokens_read;
+    L.turning_tokens = 0;
+    for (const DeviceTask &d : dev)
+        if (read_once(d) && d.tiles == 1 && d.rows <= stream_rows) L.turning_tokens += p.tasks[d.first].kv_len;
     auto record = [&](int32_t i) {
         const DeviceTask &d = dev[i];
         const codec_task &t = p.tasks[d.first];
@@ -356,7 +362,7 @@ void build_device_image(PlanData &p)
         r.n_req = d.rows / p.group;
         r.part_row_base = t.part_row_base;
         r.solo_run = 0;
-        r.flags = streaming_plan && readers[t.node] == 1 ? kTaskReadOnce : 0;
+        r.flags = read_once(d) ? kTaskReadOnce : 0;
         if (masks)
             for (int32_t e = t.q_off; e < t.q_off + t.n_req; ++e)
                 if (nodeq_mask[e] >= 0) r.flags |= kTaskMasked;

@@ -88,15 +88,19 @@ constexpr int64_t kEarlyThroughBytes = int64_t(8) << 20;
 constexpr bool last_rows_through(int32_t kv_heads) { return (kv_heads & 7) != 0; }
 
 // Two-launch plans whose stream tasks go round the KV heads on [token][head] pools (head_of in kernels.hip): plans of
-// at least this estimated makespan and so many tasks per CU.  Rows of a head then lie in other L2s than the one of the XCD
-// that reduces it, and a workgroup with a single task gains nothing.  444 drawn plans of 64 and 128 channels, time against
-// fixed heads by tasks of all heads per CU: one 1.020, 1.4 .. 2.8 0.990 .. 1.011 (up to 1.043), 4 .. 8 0.96 .. 1.00, more
-// 0.81 .. 0.96.  By this rule 147 plans 0.956 (0.807 .. 1.024); what it leaves out 0.997.  256 channels gain nothing (1.00).
+// at least this estimated makespan and so many tasks per CU, in which tasks that go round read at least this much of all
+// tokens that tasks read.  Rows of a head then lie in other L2s than the one of the XCD that reduces it, and a workgroup
+// with a single task gains nothing: by tasks of all heads per CU, 444 drawn plans of 64 and 128 channels, time against
+// fixed heads, one 1.020, 1.4 .. 2.8 0.990 .. 1.011 (up to 1.043), 4 .. 8 0.96 .. 1.00, more 0.81 .. 0.96.  Where nothing goes
+// round (plans that read their slices several times) the kernels are only longer: of 717 drawn plans by the first two
+// lines, 242 without such tasks 1.007 (up to 1.025), eight up to a tenth of the tokens 0.993 (up to 1.037), eleven up to a
+// quarter 0.958, 456 beyond 0.931.  The 467 plans by this rule 0.931 (0.797 .. 1.022).  256 channels gain nothing (1.00).
 constexpr int64_t kHeadsInTurnNs = 60000;
 constexpr int64_t kHeadsInTurnTasks = 3 * 256;
-constexpr bool heads_in_turn(int64_t tasks, int32_t kv_heads, int64_t makespan)
+constexpr int64_t kHeadsInTurnShare = 10;       // a tenth of the tokens
+constexpr bool heads_in_turn(int64_t tasks, int32_t kv_heads, int64_t makespan, int64_t turning_tokens, int64_t tokens)
 {
-    return kv_heads > 1 && makespan >= kHeadsInTurnNs && tasks * kv_heads >= kHeadsInTurnTasks;
+    return kv_heads > 1 && makespan >= kHeadsInTurnNs && tasks * kv_heads >= kHeadsInTurnTasks && turning_tokens * kHeadsInTurnShare >= tokens;
 }
 
 // Per request, the reduction kernel reads one 64-byte line: the number of partial rows on the request's
@@ -135,6 +139,8 @@ struct DevLayout {
     int32_t num_entries = 0;    // entries of the run-time queue as the kernels see it
     int32_t num_slots = 0;      // workgroups per KV head
     int32_t split_waves = 0;    // split_waves() of the plan
+    int64_t tokens_read = 0;    // by all tasks
+    int64_t turning_tokens = 0; // of those, by stream tasks that alone read their slice: they may go round the heads
 };
 
 // Lists of task indices with their offsets.

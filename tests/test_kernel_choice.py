@@ -5,7 +5,8 @@ import pytest
 from helpers import GOING_ROUND, GOING_ROUND_OPTS, ROTATING, ROTATING_OPTS, going_round_forest, rotating_forest
 from kernel_choice import case, launches, reduction_status
 from plan_image import plan_image
-from workloads import Forest, HeadConfig, build_paged_kv, unshared_forest, DTYPE_BF16, DTYPE_FP16
+from workloads import (Forest, HeadConfig, build_paged_kv, concat_forests, draft_masked_forest, two_level_forest, unshared_forest,
+                       DTYPE_BF16, DTYPE_FP16)
 
 
 def _case(f, head, layout="htd", **opts):
@@ -104,3 +105,25 @@ def test_plans_whose_tasks_do_not_go_round(d):
     assert [c["makespan"] >= 60000 for c in seen] == [True, True, True, True, False, True]
     # finished rows: a kernel of its own (its tasks go round in any case), and nothing to reduce
     assert [a[:2] for a in (seen[0]["decode"][0],)] == [("pac_kernel", (DTYPE_BF16, 2, d, 0, 0))] and len(seen[0]["decode"]) == 1
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(64, 32, 8), (128, 32, 8)])
+def test_plans_with_little_that_goes_round(d, hq, hkv):
+    """Long plans with many tasks of which none goes round the heads (they read their slices several times: drafted tokens,
+    flat plans of shared prefixes), or that read less than a tenth of the tokens, stay with the kernels that have no such
+    tasks; from a tenth on they do not."""
+    head = HeadConfig(hq, hkv, d)
+    drafted = draft_masked_forest(900, [1800 + 100 * i for i in range(16)], 48, seed=3)
+    flat = two_level_forest(2000, [100] * 100)
+    # shared slices of 33 .. 256 rows (dense tasks, packed row tiles) beside contexts of one request
+    shared = Forest(np.full(40, -1), np.full(40, 1500), np.repeat(np.arange(40), 16 if d == 128 else 24))
+    few, many = (concat_forests(shared, unshared_forest([n] * 80)) for n in (60, 100))
+    plans = [(drafted, dict(num_slots=4), 0), (flat, dict(num_slots=4, share=0), 0), (few, dict(num_slots=2), 0),
+             (many, dict(num_slots=2), 1)]
+    for (f, opts, turns), got in zip(plans, launches([_case(f, head, "thd", **opts) for f, opts, _ in plans])):
+        recs = plan_image(f, head, **opts)["slot_recs"]
+        rotating = (recs["flags"] & 1 == 1) & (recs["flags"] & 4 == 0) & (recs["n_req"] * (hq // hkv) <= (16 if d == 128 else 32))
+        share = recs["kv_len"][rotating].sum() / recs["kv_len"].sum()
+        assert got["makespan"] >= 60000 and got["tasks"] * hkv >= 768
+        assert got["decode"][0][1][3] == turns == int(share >= 0.1), (share, got["decode"])
+        assert share == 0 if f is drafted or f is flat else 0.05 < share < 0.15

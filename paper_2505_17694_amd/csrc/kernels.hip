@@ -1670,107 +1670,7 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 // the sum is added to what the chunks before came to (by associativity of the reduction this equals any binary
 // bracketing).  All forms of the reduction have the same chunks and the same rounding: they agree bit for bit.
 //
-// merge_one is the form inside the attention kernel (single-launch mode): RPW = 1, each lane owns D / 64 channels of the
-// one row, and every slot of a round is loaded: rows behind the end of a list read as row 0, which is valid memory, and
-// the straight-line code keeps that kernel as it is.
 constexpr int kFoldChunk = 8;
-template <int DT, int D>
-__device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, int wave_lane)
-{
-    constexpr int kChunk = kFoldChunk;
-    constexpr int CPL = D / 64;         // channels per lane: 1, 2 or 4
-    const int head = hq / P.group, hj = hq - head * P.group;
-    // The request's line: its number of partial rows and the first kInlineParts of them, read together
-    // (no address waits for another read).  Lists of up to eight rows, and of up to kInlineParts, are
-    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.
-    const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
-    const int total = line[0];
-    int first[kInlineParts];
-#pragma unroll
-    for (int j = 0; j < kInlineParts; ++j) first[j] = line[1 + j];  // zero behind the end: a valid row
-    const int64_t head_base = int64_t(head) * P.part_rows + hj;
-    float M = -INFINITY, L = 0.f, acc[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-    auto fold = [&](const int *rows, int cnt, auto width, auto later) {
-        constexpr int N = decltype(width)::value;
-        float2 ml[N];
-        float o[N][CPL];
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const int64_t prow = head_base + rows[j];
-            const float *src = P.part_o + prow * D + wave_lane * CPL;
-            ml[j] = ld8_device(P.part_ml + prow * 2);       // rows written by other workgroups of this launch
-            if constexpr (CPL == 1) {
-                o[j][0] = __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const unsigned int *>(src),
-                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            } else {
-#pragma unroll
-                for (int c = 0; c < CPL; c += 2) {
-                    const float2 x = ld8_device(src + c);
-                    o[j][c] = x.x;
-                    o[j][c + 1] = x.y;
-                }
-            }
-        }
-        float mm = M;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j < cnt) mm = fmaxf(mm, ml[j].x);
-        float l = 0.f, sum[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) sum[c] = 0.f;
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j < cnt) {
-                const float w = weight(ml[j].x, mm);
-                l = __builtin_fmaf(ml[j].y, w, l);
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) sum[c] = __builtin_fmaf(o[j][c], w, sum[c]);
-            }
-        const float before = decltype(later)::value ? weight(M, mm) : 0.f;
-        L = decltype(later)::value ? __builtin_fmaf(L, before, l) : l;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = decltype(later)::value ? __builtin_fmaf(acc[c], before, sum[c]) : sum[c];
-        M = mm;
-    };
-    if (total <= kChunk) {
-        fold(first, total, std::integral_constant<int, kChunk>{}, std::false_type{});
-    } else {
-        fold(first, total < kInlineParts ? total : kInlineParts, std::integral_constant<int, kInlineParts>{}, std::false_type{});
-        if (total > kInlineParts) {
-            const int32_t *list = P.req_part + P.req_part_off[r];
-#pragma unroll 1
-            for (int base = kInlineParts; base < total; base += kChunk) {
-                const int cnt = total - base < kChunk ? total - base : kChunk;
-                int rows[kChunk];
-#pragma unroll
-                for (int j = 0; j < kChunk; ++j) rows[j] = list[base + (j < cnt ? j : 0)];
-                fold(rows, cnt, std::integral_constant<int, kChunk>{}, std::true_type{});
-            }
-        }
-    }
-    const float inv = 1.f / L;
-    char *out = static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + hq) * D + wave_lane * CPL) * 2;
-    if constexpr (CPL == 1) {
-        *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(acc[0] * inv, 0.f) & 0xFFFFu);
-    } else {
-#pragma unroll
-        for (int c = 0; c < CPL; c += 2)
-            *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(acc[c] * inv, acc[c + 1] * inv);
-    }
-}
-
-// The reduction kernels.  A wave takes RPW = 256 / D consecutive query heads of a request where the rows of a KV head's
-// group divide that evenly (else RPW = 1, as above): each lane owns four channels of one of the rows; they are
-// neighbours in the partial arrays and in the output, so every load of partial rows is one full 1 KB instruction and a
-// reduction costs half (a quarter for 64 channels) the memory instructions per row.  Large launches are bound by those: each
-// takes a place in the CU's queue of memory instructions in flight whatever it moves.  For the same reason only the
-// partials that exist are loaded.  Small launches are bound by the chain of dependent reads and by the code between them:
-// merge_kernel has what is the same for the wave, the request's line and the addresses of its rows, read and worked out by
-// the scalar unit, and reads rows sixteen to 23 beside the first fifteen.  Time against a form with all of that in vector
-// registers and rows in rounds, whole steps of drawn plans: lists of up to eight rows, steps of 8 .. 16 us 0.986 (40
-// plans, the best 0.956), 16 .. 32 us 0.990; 16 .. 23 rows 0.979 and 0.986 (the best 0.932); larger steps 0.997 .. 1.000.
 
 // A chunk of a row's partials.
 template <int N, int CPL>
@@ -1778,6 +1678,7 @@ struct Chunk {
     float2 ml[N];
     float o[N][CPL];
 
+    // those that exist
     template <class Rows>
     __device__ __forceinline__ void load(const MergeParams &P, const Rows &at, const int *rows, int cnt)
     {
@@ -1789,6 +1690,13 @@ struct Chunk {
             if (j < cnt) at.load(P, rows[j], ml[j], o[j]);      // wave-uniform
         }
     }
+    // every slot
+    template <class Rows>
+    __device__ __forceinline__ void load_all(const MergeParams &P, const Rows &at, const int *rows)
+    {
+#pragma unroll
+        for (int j = 0; j < N; ++j) at.load(P, rows[j], ml[j], o[j]);
+    }
     __device__ __forceinline__ float top(float m, int cnt) const
     {
 #pragma unroll
@@ -1796,7 +1704,7 @@ struct Chunk {
             if (j < cnt) m = fmaxf(m, ml[j].x);
         return m;
     }
-    // against a reference.  (fmaf written out here and above: the compiler has no choice to make.)
+    // against a reference.  (fmaf written out here and in add_chunk: the compiler has no choice to make.)
     __device__ __forceinline__ void sum_up(int cnt, float reference, float &l, float (&sum)[CPL]) const
     {
         l = 0.f;
@@ -1812,6 +1720,116 @@ struct Chunk {
             }
     }
 };
+
+// What the chunks before came to, l and sum against m, and a chunk's sums against mm, the maximum so far.
+template <int CPL>
+__device__ __forceinline__ void add_chunk(float m, float &l, float (&sum)[CPL], float mm, float chunk_l, const float (&chunk_sum)[CPL])
+{
+    const float before = weight(m, mm);
+    l = __builtin_fmaf(l, before, chunk_l);
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) sum[c] = __builtin_fmaf(sum[c], before, chunk_sum[c]);
+}
+
+// A lane's channels of a finished row: normalised, rounded.
+template <int DT, int CPL>
+__device__ __forceinline__ void store_finished(char *out, float l, const float (&sum)[CPL])
+{
+    const float inv = 1.f / l;
+    if constexpr (CPL == 1) {
+        *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(sum[0] * inv, 0.f) & 0xFFFFu);
+    } else {
+#pragma unroll
+        for (int c = 0; c < CPL; c += 2)
+            *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(sum[c] * inv, sum[c + 1] * inv);
+    }
+}
+
+// The form inside the attention kernel (single-launch mode): one row per wave, each lane owns D / 64 channels of it, and
+// every slot of a round is loaded: rows behind the end of a list read as row 0, which is valid memory, and the
+// straight-line code keeps that kernel as it is.
+template <int D>
+struct DeliveredRows {
+    static constexpr int CPL = D / 64;          // channels per lane: 1, 2 or 4
+    int64_t head_base;
+    int lane;
+
+    // rows written by other workgroups of this launch
+    __device__ __forceinline__ void load(const MergeParams &P, int entry, float2 &ml, float (&o)[CPL]) const
+    {
+        const int64_t prow = head_base + entry;
+        const float *src = P.part_o + prow * D + lane * CPL;
+        ml = ld8_device(P.part_ml + prow * 2);
+        if constexpr (CPL == 1) {
+            o[0] = __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const unsigned int *>(src),
+                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        } else {
+#pragma unroll
+            for (int c = 0; c < CPL; c += 2) {
+                const float2 x = ld8_device(src + c);
+                o[c] = x.x;
+                o[c + 1] = x.y;
+            }
+        }
+    }
+};
+
+template <int DT, int D>
+__device__ __forceinline__ void merge_one(const MergeParams &P, int r, int hq, int wave_lane)
+{
+    constexpr int CPL = DeliveredRows<D>::CPL;
+    const int head = hq / P.group, hj = hq - head * P.group;
+    // The request's line: its number of partial rows and the first kInlineParts of them, read together
+    // (no address waits for another read).  Lists of up to eight rows, and of up to kInlineParts, are
+    // folded in one round of loads; what lies beyond comes from the CSR arrays, eight rows a round.
+    const int32_t *line = P.req_inline + int64_t(r) * (kInlineParts + 1);
+    const int total = line[0];
+    int first[kInlineParts];
+#pragma unroll
+    for (int j = 0; j < kInlineParts; ++j) first[j] = line[1 + j];  // zero behind the end: a valid row
+    const DeliveredRows<D> at{int64_t(head) * P.part_rows + hj, wave_lane};
+    float M, L, acc[CPL];
+    if (total <= kFoldChunk) {
+        Chunk<kFoldChunk, CPL> x;
+        x.load_all(P, at, first);
+        x.sum_up(total, x.top(-INFINITY, total), L, acc);
+    } else {
+        Chunk<kInlineParts, CPL> x;
+        const int cnt = total < kInlineParts ? total : kInlineParts;
+        x.load_all(P, at, first);
+        M = x.top(-INFINITY, cnt);
+        x.sum_up(cnt, M, L, acc);
+        if (total > kInlineParts) {
+            const int32_t *list = P.req_part + P.req_part_off[r];
+#pragma unroll 1
+            for (int base = kInlineParts; base < total; base += kFoldChunk) {
+                const int cnt = total - base < kFoldChunk ? total - base : kFoldChunk;
+                int rows[kFoldChunk];
+#pragma unroll
+                for (int j = 0; j < kFoldChunk; ++j) rows[j] = list[base + (j < cnt ? j : 0)];
+                Chunk<kFoldChunk, CPL> y;
+                y.load_all(P, at, rows);
+                const float mm = y.top(M, cnt);
+                float l, sum[CPL];
+                y.sum_up(cnt, mm, l, sum);
+                add_chunk(M, L, acc, mm, l, sum);
+                M = mm;
+            }
+        }
+    }
+    store_finished<DT>(static_cast<char *>(P.out) + ((int64_t(r) * P.h_q + hq) * D + wave_lane * CPL) * 2, L, acc);
+}
+
+// The reduction kernels.  A wave takes RPW = 256 / D consecutive query heads of a request where the rows of a KV head's
+// group divide that evenly (else RPW = 1, as above): each lane owns four channels of one of the rows; they are
+// neighbours in the partial arrays and in the output, so every load of partial rows is one full 1 KB instruction and a
+// reduction costs half (a quarter for 64 channels) the memory instructions per row.  Large launches are bound by those: each
+// takes a place in the CU's queue of memory instructions in flight whatever it moves.  For the same reason only the
+// partials that exist are loaded.  Small launches are bound by the chain of dependent reads and by the code between them:
+// merge_kernel has what is the same for the wave, the request's line and the addresses of its rows, read and worked out by
+// the scalar unit, and reads rows sixteen to 23 beside the first fifteen.  Time against a form with all of that in vector
+// registers and rows in rounds, whole steps of drawn plans: lists of up to eight rows, steps of 8 .. 16 us 0.986 (40
+// plans, the best 0.956), 16 .. 32 us 0.990; 16 .. 23 rows 0.979 and 0.986 (the best 0.932); larger steps 0.997 .. 1.000.
 
 // The rows of a wave and the place of its lanes in them.
 template <int DT, int D, int RPW>
@@ -1851,18 +1869,7 @@ struct WaveRows {
             for (int c = 0; c < 4; ++c) o[c] = x[c];
         }
     }
-    // normalised, rounded
-    __device__ __forceinline__ void store(float l, const float (&sum)[CPL]) const
-    {
-        const float inv = 1.f / l;
-        if constexpr (CPL == 1) {
-            *reinterpret_cast<unsigned short *>(out) = static_cast<unsigned short>(pack2<DT>(sum[0] * inv, 0.f) & 0xFFFFu);
-        } else {
-#pragma unroll
-            for (int c = 0; c < CPL; c += 2)
-                *reinterpret_cast<unsigned int *>(out + c * 2) = pack2<DT>(sum[c] * inv, sum[c + 1] * inv);
-        }
-    }
+    __device__ __forceinline__ void store(float l, const float (&sum)[CPL]) const { store_finished<DT>(out, l, sum); }
 };
 
 // blockIdx.x is the KV head.  Workgroups are dealt to the eight XCDs in turn, here and in the attention kernel, so
@@ -1922,12 +1929,10 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
             if constexpr (LONG == 2) load_next();
 #pragma unroll 1
             for (;;) {
-                const float mm = y.top(M, total - base), before = weight(M, mm);
+                const float mm = y.top(M, total - base);
                 float l, sum[CPL];
                 y.sum_up(total - base, mm, l, sum);
-                L = __builtin_fmaf(L, before, l);
-#pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(acc[c], before, sum[c]);
+                add_chunk(M, L, acc, mm, l, sum);
                 M = mm;
                 base += kFoldChunk;
                 if (base >= total) break;
@@ -2001,10 +2006,11 @@ __global__ void __launch_bounds__(WAVES * 64) merge_split_kernel(const MergePara
 #pragma unroll
             for (int w = 0; w < WAVES - 1; ++w) {
                 if (base + w * kFoldChunk >= total) break;
-                const float m = sums[w][CPL + 1][wave_lane], before = weight(M, m);
-                L = __builtin_fmaf(L, before, sums[w][CPL][wave_lane]);
+                const float m = sums[w][CPL + 1][wave_lane];
+                float sum[CPL];
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) acc[c] = __builtin_fmaf(acc[c], before, sums[w][c][wave_lane]);
+                for (int c = 0; c < CPL; ++c) sum[c] = sums[w][c][wave_lane];
+                add_chunk(M, L, acc, m, sums[w][CPL][wave_lane], sum);
                 M = m;
             }
         }

@@ -1881,8 +1881,13 @@ struct WaveRows {
 // heads 0.988, 51 with one head, for which the order is the same, 1.002 (0.987 .. 1.020).
 //
 // LONG: what of a list follows its first fifteen rows.  0: nothing, in no list of the plan.  1: rows sixteen to 23 are read
-// beside the first fifteen.  2: one after the other, for large launches, as 1 takes half as many registers again and the
-// waves of a CU are then fewer (1040 requests of 32 heads, lists of three rows, reduction alone 11.4 us, 13.1 with 1).
+// beside the first fifteen.  2: one after the other, for large launches, most of whose lists are short as a rule: 1 takes 110
+// registers, 2 at most 98, of which a SIMD holds a wave more.  us, reduction alone, 0.1 % of the lists of 20 rows
+// and the others of three, 1 / 2: 1040 requests with 32 / 8 heads 11.6 / 10.8, with 28 / 4 15.1 / 11.7, 2080 with 32 / 8
+// 20.2 / 18.8; half of them of 20 rows 29.9 / 30.5, 29.4 / 29.7, 77.6 / 78.8; all of 16 rows and 28 / 4 heads 37.3 / 39.7.
+// Lists of more than fifteen rows have a branch and a Chunk of their own: with the chunk of the lists of nine to fifteen rows, and its
+// loads under a condition, both forms took up to 165 registers and three waves fit on a SIMD (13.3, 17.5, 22.9 in the
+// first three of these cases).
 template <int DT, int D, int RPW, int LONG>
 __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergeParams P)
 {
@@ -1907,37 +1912,44 @@ __global__ void __launch_bounds__(kMergeWaves * 64) merge_kernel(const MergePara
         Chunk<kFoldChunk, CPL> x;
         x.load(P, at, first, total);
         x.sum_up(total, x.top(-INFINITY, total), L, acc);
-    } else {
+    } else if (LONG == 0 || total <= kInlineParts) {
         Chunk<kInlineParts, CPL> x;
-        const int cnt = total < kInlineParts ? total : kInlineParts;
-        x.load(P, at, first, cnt);
-        if (LONG == 0 || total <= kInlineParts) {
-            x.sum_up(cnt, x.top(-INFINITY, cnt), L, acc);
-        } else {
-            const int32_t *list = P.req_part + list_off;
-            int base = kInlineParts;
-            Chunk<kFoldChunk, CPL> y;
-            auto load_next = [&]() {
-                int rows[kFoldChunk];
+        x.load(P, at, first, total);
+        x.sum_up(total, x.top(-INFINITY, total), L, acc);
+    } else {
+        const int32_t *list = P.req_part + list_off;
+        auto load_next = [&](Chunk<kFoldChunk, CPL> &y, int base) {
+            int rows[kFoldChunk];
 #pragma unroll
-                for (int j = 0; j < kFoldChunk; ++j) rows[j] = list[base + j];  // behind the list: what follows it in the metadata, unused
-                y.load(P, at, rows, total - base);
-            };
-            if constexpr (LONG == 1) load_next();
-            M = x.top(-INFINITY, cnt);
-            x.sum_up(cnt, M, L, acc);
-            if constexpr (LONG == 2) load_next();
+            for (int j = 0; j < kFoldChunk; ++j) rows[j] = list[base + j];  // behind the list: what follows it in the metadata, unused
+            y.load(P, at, rows, total - base);
+        };
+        auto add_next = [&](const Chunk<kFoldChunk, CPL> &y, int cnt) {
+            const float mm = y.top(M, cnt);
+            float l, sum[CPL];
+            y.sum_up(cnt, mm, l, sum);
+            add_chunk(M, L, acc, mm, l, sum);
+            M = mm;
+        };
+        int base = kInlineParts;
+        Chunk<kInlineParts, CPL> x;
+        x.load_all(P, at, first);
+        if constexpr (LONG == 1) {
+            Chunk<kFoldChunk, CPL> y;
+            load_next(y, base);
+            M = x.top(-INFINITY, kInlineParts);
+            x.sum_up(kInlineParts, M, L, acc);
+            add_next(y, total - base);
+            base += kFoldChunk;
+        } else {
+            M = x.top(-INFINITY, kInlineParts);
+            x.sum_up(kInlineParts, M, L, acc);
+        }
 #pragma unroll 1
-            for (;;) {
-                const float mm = y.top(M, total - base);
-                float l, sum[CPL];
-                y.sum_up(total - base, mm, l, sum);
-                add_chunk(M, L, acc, mm, l, sum);
-                M = mm;
-                base += kFoldChunk;
-                if (base >= total) break;
-                load_next();
-            }
+        for (; base < total; base += kFoldChunk) {
+            Chunk<kFoldChunk, CPL> y;
+            load_next(y, base);
+            add_next(y, total - base);
         }
     }
     at.store(L, acc);

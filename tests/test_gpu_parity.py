@@ -831,6 +831,27 @@ def test_split_reduction(parts, d, hq, hkv, requests):
     assert np.array_equal(one, got)
 
 
+@pytest.mark.parametrize("longest", [16, 23, 24, 40, 75])
+@pytest.mark.parametrize("d,hq,hkv,requests", [(128, 32, 8, 1040), (128, 28, 4, 600), (64, 32, 8, 2080), (64, 12, 4, 1400), (256, 16, 8, 1040)])
+def test_large_reductions_of_mixed_lists(longest, d, hq, hkv, requests):
+    """Launches of more than 16383 waves, in every width of a wave's rows: lists of one to fifteen rows beside a few of up
+    to `longest`, folded by one wave each.  Two launches and one agree bit for bit."""
+    nodes = 40
+    parts = [1 + i % 15 for i in range(nodes - 3)] + [longest - 1 if longest > 16 else 16, longest, 15]
+    f = Forest(np.full(nodes, -1), np.array([32 * n - n % 3 for n in parts]), np.arange(requests) % nodes)
+    w = make_workload(f"mixed-{longest}-{d}", f, HeadConfig(hq, hkv, d, DTYPE_FP16 if longest % 2 and d > 64 else DTYPE_BF16), seed=1750 + longest + d,
+                      poison=True, layout="htd")
+    opts = {"num_slots": 8, "split_align": 32, "fixed_slices": longest}
+    sel = [(r, h) for r in (0, 7, 8, 14, 36, 37, 38, 39, requests - 1) for h in (0, hq - 1)]
+    got, view = check(w, sel=sel, **opts)
+    lists = np.diff(view["req_part_off"])
+    assert sorted(set(lists)) == sorted(set(parts)) and int(lists.max()) == longest
+    rows = 256 // d if (hq // hkv) % (256 // d) == 0 else 1
+    assert requests * (hq // rows) * (1 if longest < 24 else 4 if longest < 40 else 8) > 16383
+    one, _ = run_gpu(w, 1, fused=1, **opts)
+    assert np.array_equal(one, got)
+
+
 @pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 16, 2), (64, 3, 3)])
 def test_split_reduction_of_very_long_lists(d, hq, hkv):
     """Many rounds of the split form: right, and four times the rows take at most six times as long (a wave that reads the

@@ -109,21 +109,26 @@ constexpr bool heads_in_turn(int64_t tasks, int32_t kv_heads, int64_t makespan, 
 constexpr int32_t kInlineParts = 15;
 
 // Waves that share a list in the split form of the reduction (merge_split_kernel), the first fifteen rows and eight each
-// round; less than four: one wave folds a list, see LONG of merge_kernel.  By the longest list and by the waves of the launch, as a wave whose part of a list is
-// empty still has to start.  Drawn plans, whole steps, time with the split form over time with one wave per list:
-// lists of 16 .. 23 rows (two waves) 73 plans 0.997 (0.915 .. 1.043), 24 .. 39 rows (four) 37 plans 0.965 (0.873 .. 1.016),
-// more (eight) 13 plans 0.88 (0.62 .. 0.98).  By waves, a variant with up to eight waves: 2048 .. 16383 217 plans 0.964
-// (0.593 .. 1.015), 16384 .. 32767 69 plans 0.997 (up to 1.030), 32768 .. 65535 59 plans 1.018 (up to 1.128), more 1.13
-// (up to 1.60).
+// round; less than four: one wave folds a list, see LONG of merge_kernel.  By the longest list and by the waves of the launch:
+// the chip holds about 4096 of them at once, and a wave whose part of a list is empty still has to start.  Drawn plans, whole
+// steps, time with the split form over time with one wave per list: lists of 16 .. 23 rows (two waves) 73 plans 0.997
+// (0.915 .. 1.043); 24 .. 39 rows (four), up to 4096 waves 14 plans 0.930 (0.867 .. 0.981), up to 6143 14 plans 0.973 (0.913 ..
+// 1.012), 7000 .. 9700 27 plans 1.007 (0.970 .. 1.034); more rows (eight), up to 5000 waves 14 plans 0.828 (0.667 .. 0.934), up to
+// 8191 13 plans 0.913 (0.723 .. 0.992).  Beyond, where no plan was drawn, the reduction alone, its rows in L2, 0.02, 0.3 or
+// all of the lists long: eight waves, 10600 waves 0.69 .. 1.18 of the time, 13100 waves 0.65 .. 1.27.
 constexpr int32_t kSplitMinList = 24;
-constexpr int64_t kSplitMaxWaves = 16383;
+constexpr int64_t kSplitMaxWavesOfFour = 6143, kSplitMaxWavesOfEight = 8191;
+// Most waves of a launch that reads rows sixteen to 23 beside the first fifteen.
+constexpr int64_t kReadAheadMaxWaves = 16383;
 constexpr int32_t split_rows(int32_t waves) { return kInlineParts + 8 * (waves - 1); }     // of a list, that a round reads
 constexpr int32_t split_waves(int32_t longest_list, int32_t num_requests, int32_t h_q, int32_t group, int32_t head_dim)
 {
     if (longest_list <= kInlineParts) return 0;
-    const int32_t waves = longest_list < kSplitMinList ? 1 : longest_list <= split_rows(4) ? 4 : 8;
     const int32_t heads = 256 / head_dim > 1 && group % (256 / head_dim) == 0 ? 256 / head_dim : 1;  // rows of a wave
-    return int64_t(num_requests) * (h_q / heads) * waves <= kSplitMaxWaves ? waves : 2;
+    const int64_t lists = int64_t(num_requests) * (h_q / heads);
+    const int32_t waves = longest_list <= split_rows(4) ? 4 : 8;
+    if (longest_list >= kSplitMinList && lists * waves <= (waves == 4 ? kSplitMaxWavesOfFour : kSplitMaxWavesOfEight)) return waves;
+    return lists <= kReadAheadMaxWaves ? 1 : 2;
 }
 // Words of a request's line for the split form: its list's length and first rows.
 constexpr int32_t split_line_words(int32_t waves) { return (1 + split_rows(waves) + 15) / 16 * 16; }

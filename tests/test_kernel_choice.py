@@ -27,7 +27,7 @@ def test_reduction_forms_that_do_not_exist_are_refused():
 @pytest.mark.parametrize("d,hq,hkv,wide", [(128, 32, 8, 2), (128, 7, 1, 1), (64, 16, 2, 4), (64, 6, 3, 1), (256, 10, 2, 1)])
 def test_reduction_form_by_the_longest_list_and_the_launch(d, hq, hkv, wide):
     """One wave per list without the code behind fifteen rows, with rows sixteen to 23 beside them, or, in large launches,
-    one after the other; four or eight waves per list.  Large: more than 16383 waves."""
+    one after the other (more than 16383 waves); four or eight waves per list in launches of up to 6143 and 8191."""
     head = HeadConfig(hq, hkv, d, DTYPE_FP16)
     lists = [1, 2, 15, 16, 23, 24, 39, 40, 71, 72, 300]
     few = [_case(Forest(np.array([-1]), np.array([32 * n]), np.zeros(2, np.int64)), head, split_align=32, fixed_slices=n,
@@ -40,9 +40,9 @@ def test_reduction_form_by_the_longest_list_and_the_launch(d, hq, hkv, wide):
         assert got["decode"][1:] == (got["reduction"] if n > 1 else [])
     per_request = hq // wide
     many, want = [], []
-    for n, waves in ((20, 1), (30, 4), (50, 8)):
-        most = 16383 // (per_request * waves)
-        for b, form in ((most, waves), (most + 1, 2)):
+    for n, waves, line, beyond in ((20, 1, 16383, 2), (30, 4, 6143, 1), (50, 8, 8191, 1), (30, 1, 16383, 2), (50, 1, 16383, 2)):
+        most = line // (per_request * waves)
+        for b, form in ((most, waves), (most + 1, beyond)):
             many.append(_case(Forest(np.array([-1]), np.array([32 * n]), np.zeros(b, np.int64)), head, split_align=32,
                               fixed_slices=n, num_slots=4))
             want.append(("merge_split_kernel" if form >= 4 else "merge_kernel", (DTYPE_FP16, d, wide, form)))

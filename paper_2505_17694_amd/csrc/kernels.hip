@@ -1668,7 +1668,9 @@ __device__ __forceinline__ void run_tile(const PacParams &P, const DevTask &t, i
 // of one request (hq .. hq + RPW - 1, all of one KV head) in list order.  Partials are taken in chunks, the first fifteen
 // of a list, then eight at a time: their loads are issued together, they are summed up against the maximum so far, and
 // the sum is added to what the chunks before came to (by associativity of the reduction this equals any binary
-// bracketing).  All forms of the reduction have the same chunks and the same rounding: they agree bit for bit.
+// bracketing).  All forms of the reduction have the same chunks and the same rounding and agree bit for bit, but
+// for fp16 of 64 channels: the forms with one row per wave multiply and round a value in one instruction, those with
+// four rows in two (68 of 1064960 values differ, in their last bit).
 //
 constexpr int kFoldChunk = 8;
 
